@@ -275,8 +275,7 @@ size_t usp_workspace_bytes(const usp_grid* grid, int64_t capacity);
    in_offsets (device int64[M+1], may be NULL, may alias offsets): when the
    input's first in_offsets[M] particles are the output of an earlier bin
    with these offsets (updated in place since, as usp_step does, with any
-   later particles appended), the fast route that exploits it is taken.
-   On that route the prefix particles' in->cell must be current (the cell of
+   later particles appended), the bin exploits it.  Then the prefix particles' in->cell must be current (the cell of
    the position, or -1 if removed, as usp_advect and usp_update leave it):
    their cells are taken from in->cell, not recomputed from positions.
    Appended particles, and every particle when in_offsets is NULL, are
@@ -452,7 +451,7 @@ usp_status usp_batch(const usp_grid* grid, const usp_gas* gas, double dt, const 
    step's pre-collision state on return).  in_offsets (may be NULL, may
    alias offsets) is passed to the first step's usp_bin: when *p is the
    state a previous step or bin left (segments in in_offsets), the first
-   bin takes the fast route too; later steps always do. */
+   bin exploits it too; later steps always do. */
 usp_status usp_step(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, double dt,
                     const double* dt_cell, usp_particles* p, usp_particles* p_alt,
                     int64_t* offsets, const int64_t* in_offsets, double* mom, double* cs,

@@ -1,11 +1,12 @@
 // usp_bin.hip -- binning: stable counting sort of particles by cell.
 //
 // The output order is fixed by definition: particles sorted by cell, in
-// input order inside a cell, removed particles dropped.  Two routes give it:
+// input order inside a cell, removed particles dropped.  Unordered inputs,
+// small grids and small states take the counting sort of usp_sort.hip (see
+// sort_route); the rest of this file is the neighbour-group route:
 //
-// * Binned input (the usual case: the previous step's sorted state, whose
-//   segment offsets are passed in, followed by a tail of injected
-//   particles).  A particle of old cell k lands in k + d with d in a small
+// * Binned input (the previous step's sorted state, whose segment offsets
+//   are passed in, followed by a tail of injected particles).  A particle of old cell k lands in k + d with d in a small
 //   neighbour set, so a new cell's particles come from at most 9 source
 //   segments, which appear in ascending order in the input.  One wave per
 //   source segment ranks its particles inside each group with ballots
@@ -13,12 +14,13 @@
 //   positions, interleaving the rare far moves by input index
 //   (k_cell_bases); one wave per source segment then writes every particle
 //   straight to its final slot (k_bin_scatter).  No atomics, no sorting.
-// * The tail, and every particle when no input offsets are given: slots are
+// * The tail (and every particle of a grid past the sort's cells when no
+//   input offsets are given): slots are
 //   claimed after the cell's prefix particles with one integer atomic per
 //   run of equal keys, and each cell's claimed indices are sorted ascending
 //   (restoring input order) before the copy.
 // All results are deterministic.
-#include "usp_device.h"
+#include "usp_binkey.h"
 
 namespace usp {
 
@@ -26,28 +28,11 @@ constexpr int BIN_BLOCK = 256;
 constexpr int SCAN_ITEMS = 4;
 constexpr int SCAN_TILE = BIN_BLOCK * SCAN_ITEMS;
 constexpr int SORT_LDS = 4096;
-constexpr int BIN_U = 4;
-// grids of at most this many cells launch independent bin kernels together
-constexpr int64_t BIN_MERGE_MAX = 4096;  // chunks of 64 particles per load batch of the grouped bin
+constexpr int BIN_U = 4;  // chunks of 64 particles per load batch of the grouped bin
 
 __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
-}
-
-// Runs of equal keys in consecutive lanes of a wave (particles arrive
-// mostly sorted by cell, so a wave holds a few long runs).  Returns the
-// lane of this lane's run head and, for heads, the run length.
-__device__ __forceinline__ void wave_runs(int32_t key, int* head_lane, int* run_len) {
-  const int lane = threadIdx.x & 63;
-  const int32_t prev = __shfl_up(key, 1, 64);
-  const bool head = lane == 0 || key != prev;
-  const uint64_t heads = __ballot(head);
-  const uint64_t upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
-  *head_lane = 63 - __clzll(heads & upto);
-  const uint64_t above = heads & ~upto;
-  const int next = above ? (__ffsll((long long)above) - 1) : 64;
-  *run_len = head ? next - lane : 0;
 }
 
 // ---- exclusive scan of int32 counts into int64 offsets -------------------
@@ -194,30 +179,6 @@ __device__ __forceinline__ int nbr_group(const GridP& g, const Nbr& nb, int64_t 
   return (q >= 0 && q < nb.n) ? (int)q : GRP_FAR;
 }
 
-template <typename S>
-__device__ __forceinline__ int32_t new_key(const GridP& g, const PartP<S>& in, int64_t i,
-                                           bool* solid) {
-  int32_t c = in.cell[i];
-  *solid = false;
-  if (c >= 0) {
-    if (g.dim == 0) {
-      if (c >= g.M) c = -1;
-    } else {
-      c = cell_of<S>(g, g.dim == 2 ? in.x[i] : S(0), in.y[i]);
-    }
-  }
-  if (c >= 0 && g.flags && (g.flags[c] & USP_FLAG_SOLID)) {
-    c = -1;
-    *solid = true;
-  }
-  return c;
-}
-
-__device__ __forceinline__ int64_t sorted_len(const int64_t* old_off, int64_t M, const int64_t* count) {
-  const int64_t a = old_off[M], b = count[0];
-  return a < b ? (a > 0 ? a : 0) : b;
-}
-
 // A: one wave per old cell k.  New cell of every particle of the segment,
 // its group, and its rank among the earlier particles of the segment in the
 // same group (64 at a time with ballots).  Writes grp[i] = rank << 4 | group,
@@ -346,27 +307,6 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_tail_key(GridP g, PartP<S> in, co
               gridDim.x);
 }
 
-// On small grids, where the step is launch-bound, the two run side by side
-// in one launch (they touch disjoint arrays): the first ngroup blocks group
-// the binned prefix, the rest key the tail.  (On large grids the separate
-// launches are faster.)
-template <typename S>
-__global__ __launch_bounds__(BIN_BLOCK) void k_bin_group_tail(GridP g, Nbr nb, PartP<S> in,
-                                                              const int64_t* old_off, int32_t* key,
-                                                              int32_t* T9, int32_t* far_cnt,
-                                                              int32_t* far_c, int32_t* far_i,
-                                                              int32_t* far_total, int32_t* tail_cnt,
-                                                              int32_t* tail_cells,
-                                                              int32_t* n_tail_cells,
-                                                              int64_t* counters, int64_t ngroup) {
-  const int64_t blk = blockIdx.x;
-  if (blk < ngroup)
-    bin_group<S>(g, nb, in, old_off, key, T9, far_cnt, far_c, far_i, far_total, counters, blk);
-  else
-    tail_key<S>(g, in, old_off, key, tail_cnt, tail_cells, n_tail_cells, counters, blk - ngroup,
-                (int64_t)gridDim.x - ngroup);
-}
-
 // Far moves into per-cell lists (the order inside a list is fixed later).
 __global__ __launch_bounds__(BIN_BLOCK) void k_far_place(const int32_t* far_total,
                                                          const int32_t* far_c, const int32_t* far_i,
@@ -468,34 +408,6 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_cell_bases(GridP g, Nbr nb, const
   while (fp < f1) far_base[fp++] = run++;
   nontail[c] = run;
   cnt_total[c] = run + tail_cnt[c];
-}
-
-template <typename S>
-__device__ __forceinline__ void copy_particle(const PartP<S>& in, const PartP<S>& out, int64_t i,
-                                              int64_t p, int32_t c, bool has_x, bool has_y) {
-  if (has_x) out.x[p] = in.x[i];
-  if (has_y) out.y[p] = in.y[i];
-  out.cx[p] = in.cx[i];
-  out.cy[p] = in.cy[i];
-  out.cz[p] = in.cz[i];
-  out.erot[p] = in.erot[i];
-  out.vib[p] = in.vib[i];
-  out.pid[p] = in.pid[i];
-  out.cell[p] = c;
-}
-
-// Output slot p of input particle i: copied (G = false), or, for a binning
-// that leaves the particles where they are (G = true), recorded as
-// gperm[p] = i with the new cell in out.cell[p].
-template <bool G, typename S>
-__device__ __forceinline__ void place(const PartP<S>& in, const PartP<S>& out, uint32_t* gperm,
-                                      int64_t i, int64_t p, int32_t c, bool has_x, bool has_y) {
-  if constexpr (G) {
-    gperm[p] = (uint32_t)i;
-    out.cell[p] = c;
-  } else {
-    copy_particle<S>(in, out, i, p, c, has_x, has_y);
-  }
 }
 
 // E: one wave per old cell; every grouped particle goes straight to
@@ -609,29 +521,6 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_tail_claim(int64_t M, const int64
   tail_claim(M, old_off, count, key, offsets, nontail, cursor, perm, blockIdx.x, gridDim.x);
 }
 
-// Far moves and tail claims side by side in one launch on small grids
-// (disjoint slots): the first nfar blocks place the far moves, the rest
-// claim the tail's slots.
-template <typename S, bool G>
-__global__ __launch_bounds__(BIN_BLOCK) void k_far_tail(GridP g, PartP<S> in, PartP<S> out,
-                                                        uint32_t* gperm, const int32_t* far_total,
-                                                        const int32_t* far_c, const int32_t* far_i,
-                                                        const int64_t* far_off,
-                                                        const int32_t* far_list,
-                                                        const int32_t* far_base,
-                                                        const int64_t* old_off, const int32_t* key,
-                                                        const int64_t* offsets,
-                                                        const int32_t* nontail, int32_t* cursor,
-                                                        uint32_t* perm, int nfar) {
-  const int blk = blockIdx.x;
-  if (blk < nfar)
-    far_scatter<S, G>(g, in, out, gperm, far_total, far_c, far_i, far_off, far_list, far_base,
-                      offsets, blk, nfar);
-  else
-    tail_claim(g.M, old_off, in.count, key, offsets, nontail, cursor, perm, blk - nfar,
-               (int64_t)gridDim.x - nfar);
-}
-
 // One wave sorts one cell's tail slot list (distinct input indices) by rank
 // counting and copies each particle to its rank's slot: each lane holds K
 // entries; an entry's rank is the number of entries below it, counted
@@ -734,42 +623,9 @@ __global__ void k_bin_init(const int64_t* src, int64_t* dst, int64_t M, int32_t*
   if (i == 0) { *scalar = 0; *scalar2 = 0; }
 }
 
-// The three scan passes in one block, for M <= SCAN_TILE (the 1D and 0D
-// grids, where the step is launch-bound); same results as the three kernels.
-__global__ __launch_bounds__(BIN_BLOCK) void k_scan_small(const int32_t* counts, int64_t M,
-                                                          int64_t* offsets, int64_t* out_count,
-                                                          const int64_t* in_count) {
-  const int64_t base = (int64_t)threadIdx.x * SCAN_ITEMS;
-  int32_t v[SCAN_ITEMS];
-  int64_t s = 0;
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
-    const int64_t j = base + k;
-    v[k] = j < M ? counts[j] : 0;
-    s += v[k];
-  }
-  int64_t tot;
-  int64_t run = block_exclusive_scan(s, &tot);
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
-    const int64_t j = base + k;
-    if (j < M) offsets[j] = run;
-    run += v[k];
-  }
-  if (threadIdx.x == 0) {
-    offsets[M] = tot;
-    if (out_count) {
-      out_count[0] = tot;
-      out_count[1] = in_count[1];
-    }
-  }
-}
-
 static void launch_scan(const int32_t* cnt, int64_t M, int64_t* out_off, int64_t* blocksums,
                         int64_t* out_count, const int64_t* in_count, hipStream_t st) {
   const int64_t nb = cdiv(M, SCAN_TILE);
-  if (nb <= 1) {
-    k_scan_small<<<1, BIN_BLOCK, 0, st>>>(cnt, M, out_off, out_count, in_count);
-    return;
-  }
   k_scan_reduce<<<nb, BIN_BLOCK, 0, st>>>(cnt, M, blocksums);
   k_scan_down<<<nb, BIN_BLOCK, 0, st>>>(cnt, M, blocksums, out_off, out_count, in_count);
 }
@@ -802,18 +658,11 @@ static hipError_t bin_launches(const GridP& g, const PartP<S>& in, const PartP<S
   const int TAIL_GRID = 512;
   k_bin_init<<<cdiv(M + 1, 256), 256, 0, st>>>(in_offsets, old_off, M, tail_cnt, cursor, far_cnt,
                                                 far_cur, far_total, n_tail_cells);
-  const bool merged = M <= BIN_MERGE_MAX;
   const int64_t ngroup = cdiv(M, BIN_BLOCK / 64);
-  if (merged) {
-    k_bin_group_tail<S><<<ngroup + TAIL_GRID, BIN_BLOCK, 0, st>>>(
-        g, nb, in, old_off, key, T9, far_cnt, far_c, far_i, far_total, tail_cnt, tail_cells,
-        n_tail_cells, counters, ngroup);
-  } else {
-    k_bin_group<S><<<ngroup, BIN_BLOCK, 0, st>>>(g, nb, in, old_off, key, T9, far_cnt, far_c, far_i,
-                                                 far_total, counters);
-    k_tail_key<S><<<TAIL_GRID, BIN_BLOCK, 0, st>>>(g, in, old_off, key, tail_cnt, tail_cells,
-                                                   n_tail_cells, counters);
-  }
+  k_bin_group<S><<<ngroup, BIN_BLOCK, 0, st>>>(g, nb, in, old_off, key, T9, far_cnt, far_c, far_i,
+                                               far_total, counters);
+  k_tail_key<S><<<TAIL_GRID, BIN_BLOCK, 0, st>>>(g, in, old_off, key, tail_cnt, tail_cells,
+                                                 n_tail_cells, counters);
   launch_scan(far_cnt, M, far_off, blocksums, nullptr, nullptr, st);
   k_far_place<<<64, BIN_BLOCK, 0, st>>>(far_total, far_c, far_i, far_off, far_cur, far_list);
   const int far_cpw = M >= 64 * 1024 ? 64 : 1;
@@ -826,16 +675,10 @@ static hipError_t bin_launches(const GridP& g, const PartP<S>& in, const PartP<S
   k_bin_scatter<S, G><<<cdiv(M, BIN_BLOCK / 64), BIN_BLOCK, 0, st>>>(g, nb, in, out, perm, old_off, key, T9,
                                                                    offsets);
   const int FAR_GRID = 64;
-  if (merged) {
-    k_far_tail<S, G><<<FAR_GRID + TAIL_GRID, BIN_BLOCK, 0, st>>>(
-        g, in, out, perm, far_total, far_c, far_i, far_off, far_list, far_base, old_off, key,
-        offsets, nontail, cursor, perm, FAR_GRID);
-  } else {
-    k_far_scatter<S, G><<<FAR_GRID, BIN_BLOCK, 0, st>>>(g, in, out, perm, far_total, far_c, far_i,
-                                                       far_off, far_list, far_base, offsets);
-    k_tail_claim<<<TAIL_GRID, BIN_BLOCK, 0, st>>>(M, old_off, in.count, key, offsets, nontail,
-                                                  cursor, perm);
-  }
+  k_far_scatter<S, G><<<FAR_GRID, BIN_BLOCK, 0, st>>>(g, in, out, perm, far_total, far_c, far_i,
+                                                     far_off, far_list, far_base, offsets);
+  k_tail_claim<<<TAIL_GRID, BIN_BLOCK, 0, st>>>(M, old_off, in.count, key, offsets, nontail,
+                                                cursor, perm);
   k_tail_sort_copy<S, G><<<TAIL_GRID, BIN_BLOCK, 0, st>>>(g, in, out, offsets, nontail, perm,
                                                        tail_cells, n_tail_cells);
   k_tail_sort_copy_big<S, G><<<TAIL_GRID, BIN_BLOCK, 0, st>>>(g, in, out, offsets, nontail, perm,
@@ -850,6 +693,12 @@ template <typename S>
 hipError_t launch_bin(const GridP& g, const PartP<S>& in, const PartP<S>& out, int64_t* offsets,
                       const int64_t* in_offsets, char* ws, const WsLayout& L, int64_t* counters,
                       hipStream_t st, uint32_t* gather_perm) {
+  if (sort_route(g.M, in.capacity, in_offsets != nullptr, gather_perm != nullptr))
+    return gather_perm
+               ? sort_launches<S, true>(g, in, out, offsets, in_offsets, ws, L, gather_perm,
+                                        counters, st)
+               : sort_launches<S, false>(g, in, out, offsets, in_offsets, ws, L, nullptr, counters,
+                                         st);
   if (gather_perm)
     return bin_launches<S, true>(g, in, out, offsets, in_offsets, ws, L, gather_perm, counters, st);
   return bin_launches<S, false>(g, in, out, offsets, in_offsets, ws, L, (uint32_t*)(ws + L.perm),

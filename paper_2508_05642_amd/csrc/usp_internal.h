@@ -135,7 +135,7 @@ template <typename S> PartP<S> make_parts(const usp_particles* p);
 // workspace layout (byte offsets into the caller's scratch buffer)
 struct WsLayout {
   size_t key, perm, blocksums, t9, cell_i32, old_off, far_off, far, face_cnt, face_off, misc,
-      tiles, chunk_off, chunk_part, cons_scal, total;
+      tiles, chunk_off, chunk_part, cons_scal, sort_t, sort_tot, total;
 };
 // Cells split into chunks for the per-cell reductions (grids whose cells
 // are far larger than a workgroup's share): slots per chunk, partial sums
@@ -153,6 +153,39 @@ constexpr int UPDATE_STAGE_F32 = 2048;
 constexpr int UPDATE_STAGE_F64 = 1024;
 constexpr int UPDATE_TILE_MIN = 128;
 WsLayout ws_layout(int64_t M, int64_t capacity, int nfaces);
+
+// The bin as a counting sort of input chunks (usp_sort.hip): nb digits (the
+// cell, or a bucket of 2^shift cells), nchunks chunks of `chunk` slots.
+constexpr int SORT_BUCKETS = 1024;
+constexpr int64_t SORT_CHUNKS = 1024;
+constexpr int64_t SORT_CHUNK_MIN = 2048;
+constexpr int64_t SORT_SELF_SCAN = 32768;
+struct SortPlan {
+  int shift, nb, bits, self_scan;
+  int64_t chunk, nchunks;
+};
+SortPlan sort_plan(int64_t M, int64_t capacity);
+// Which route the bin takes.  An input without segments is sorted (its
+// order is unknown; 3.0M particles in random order: 1.0 ms against 2.2 ms
+// through the appended-particle path).  A binned input is sorted on grids of
+// at most SORT_BUCKETS cells (one pass, two launches: 19 against 73 us at
+// 1e5 to 1e6 particles, and moves over any number of cells cost the same)
+// and below a state size: the neighbour-group route moves fewer bytes per
+// particle but takes twelve more launches.  Measured on cylinder grids,
+// sort against group route: recording the order, 59 against 62 us at 1.7M
+// particles, 111 against 94 at 4.6M, 133 against 92 at 6.6M; copying, 222
+// against 325 at 4.6M and 289 against 250 at 6.6M.  The state size known
+// on the host is the capacity (1.6 times the particles there).
+constexpr int64_t SORT_GATHER_CAP = 5 << 20;
+constexpr int64_t SORT_COPY_CAP = 8 << 20;
+inline bool sort_route(int64_t M, int64_t capacity, bool binned, bool gather) {
+  if (M > (int64_t)SORT_BUCKETS * SORT_BUCKETS) return false;
+  return !binned || M <= SORT_BUCKETS || capacity <= (gather ? SORT_GATHER_CAP : SORT_COPY_CAP);
+}
+template <typename S, bool G>
+hipError_t sort_launches(const GridP& g, const PartP<S>& in, const PartP<S>& out, int64_t* offsets,
+                         const int64_t* in_offsets, char* ws, const WsLayout& L, uint32_t* perm,
+                         int64_t* counters, hipStream_t st);
 int n_faces(const GridP& g);
 
 // launchers (return hipError_t of the last launch)

@@ -1,0 +1,503 @@
+// usp_sort.hip -- binning as a stable counting sort of input chunks (the
+// order of usp_bin: by cell, in input order inside a cell, removed particles
+// dropped), for inputs whose order is not known and for small grids.
+//
+// A workgroup owns a chunk of consecutive input slots and counts the digits
+// of its particles (k_sort_count: the cell, or with more than SORT_BUCKETS
+// cells a bucket of 2^shift consecutive cells).  A particle's slot is then
+// the digit's start, plus the digit's particles in earlier chunks, plus
+// those in earlier waves of its chunk, plus its rank in its own wave (lanes
+// of equal digit found by ballots): no atomics on memory, nothing to clear
+// beforehand, and the result does not depend on the launch.  k_sort_place
+// writes the final order, or (buckets) the list of (index, cell) pairs in
+// bucket order, which k_sort_fine orders by cell, a workgroup per bucket.
+#include "usp_binkey.h"
+
+namespace usp {
+
+constexpr int SORT_BLOCK = 512;
+constexpr int SORT_WAVES = SORT_BLOCK / 64;
+constexpr int SORT_U = 4;  // 64-particle groups whose keys are loaded together
+constexpr int COUNT_U = 8;
+
+// Key of input slot i: the cell it holds on entry for the binned prefix
+// (i < ns), else from its position; -1 for a removed particle.
+template <typename S>
+__device__ __forceinline__ int32_t sort_key(const GridP& g, const PartP<S>& in, int64_t i,
+                                            int64_t ns, bool* solid) {
+  *solid = false;
+  if (i >= ns) return new_key<S>(g, in, i, solid);
+  int32_t c = in.cell[i];
+  if (c >= g.M) c = -1;
+  if (c >= 0 && g.flags && (g.flags[c] & USP_FLAG_SOLID)) {
+    c = -1;
+    *solid = true;
+  }
+  return c;
+}
+
+// Adds the wave's digits (d < 0: none) to an LDS histogram, one atomic per
+// run of equal digits.
+__device__ __forceinline__ void count_digits(uint32_t* hist, int32_t d) {
+  int hl, len;
+  wave_runs(d, &hl, &len);
+  if (len > 0 && d >= 0) atomicAdd(&hist[d], (uint32_t)len);
+}
+
+// The lanes of the wave that hold the same digit as this lane (d < 0: an
+// idle lane, result unused): up to three distinct values one by one, then,
+// where more are present (an unordered input), one ballot per bit.
+__device__ __forceinline__ uint64_t same_digit(int32_t d, int bits) {
+  uint64_t rest = __ballot(d >= 0), same = 0ull;
+  for (int t = 0; t < 3 && rest; ++t) {
+    const int32_t v = __builtin_amdgcn_readlane(d, __ffsll((long long)rest) - 1);
+    const uint64_t m = __ballot(d == v);
+    if (d == v) same = m;
+    rest &= ~m;
+  }
+  if (rest) {
+    uint64_t m = rest;
+    for (int b = 0; b < bits; ++b) {
+      const bool bit = ((uint32_t)d >> b) & 1u;
+      const uint64_t bm = __ballot(bit);
+      m &= bit ? bm : ~bm;
+    }
+    if ((rest >> (threadIdx.x & 63)) & 1ull) same = m;
+  }
+  return same;
+}
+
+// Position of this lane's particle in digit order: next[d] counts up as the
+// wave walks its slots in input order.
+__device__ __forceinline__ uint32_t take_slot(uint32_t* next, int32_t d, int bits) {
+  const uint64_t same = same_digit(d, bits);
+  const int lane = threadIdx.x & 63;
+  const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  uint32_t p = 0;
+  if (d >= 0) {
+    const uint32_t base = next[d];
+    p = base + (uint32_t)__popcll(same & lt);
+    // the last lane of the digit moves it on
+    if ((same >> lane) == 1ull) next[d] = p + 1u;
+  }
+  // the next group of lanes reads what this one wrote
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  return p;
+}
+
+// Exclusive scan of v[0, n) (n <= SORT_BUCKETS, LDS) in place over the
+// workgroup; returns the total.
+__device__ __forceinline__ uint32_t scan_lds(uint32_t* v, int n) {
+  __shared__ uint32_t wsum[SORT_WAVES];
+  constexpr int PER = SORT_BUCKETS / SORT_BLOCK;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  uint32_t a[PER], s = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int j = threadIdx.x * PER + k;
+    a[k] = j < n ? v[j] : 0u;
+    s += a[k];
+  }
+  uint32_t x = s;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[wid] = x;
+  __syncthreads();
+  uint32_t base = 0, tot = 0;
+  for (int w = 0; w < SORT_WAVES; ++w) {
+    if (w < wid) base += wsum[w];
+    tot += wsum[w];
+  }
+  uint32_t run = base + x - s;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int j = threadIdx.x * PER + k;
+    if (j < n) v[j] = run;
+    run += a[k];
+  }
+  __syncthreads();
+  return tot;
+}
+
+// Digit counts of chunk blockIdx.x, row blockIdx.x of T.  Keys of the slots
+// past the binned prefix are kept in key[]; *ns_out receives the prefix
+// length (the output offsets may overwrite old_off later).
+template <typename S>
+__global__ __launch_bounds__(SORT_BLOCK) void k_sort_count(GridP g, PartP<S> in,
+                                                           const int64_t* old_off, int32_t* key,
+                                                           uint32_t* T, SortPlan sp, int64_t* ns_out,
+                                                           int64_t* counters) {
+  __shared__ uint32_t hist[SORT_BUCKETS];
+  for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) hist[d] = 0u;
+  __syncthreads();
+  const int64_t n = in.count[0];
+  const int64_t ns = old_off ? sorted_len(old_off, g.M, in.count) : 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *ns_out = ns;
+  const int64_t i0 = (int64_t)blockIdx.x * sp.chunk;
+  if (i0 >= n) return;
+  const int64_t i1 = i0 + sp.chunk < n ? i0 + sp.chunk : n;
+  const int lane = threadIdx.x & 63;
+  for (int64_t b = i0 + (threadIdx.x & ~63); b < i1; b += COUNT_U * SORT_BLOCK) {
+    int32_t c[COUNT_U];
+#pragma unroll
+    for (int u = 0; u < COUNT_U; ++u) {
+      const int64_t i = b + u * SORT_BLOCK + lane;
+      bool solid = false;
+      c[u] = -1;
+      if (i < i1) {
+        c[u] = sort_key<S>(g, in, i, ns, &solid);
+        if (i >= ns) key[i] = c[u];
+      }
+      if (solid) count_event(counters, USP_CNT_SOLID_DROP);
+    }
+#pragma unroll
+    for (int u = 0; u < COUNT_U; ++u) count_digits(hist, c[u] < 0 ? -1 : c[u] >> sp.shift);
+  }
+  __syncthreads();
+  for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) T[(int64_t)blockIdx.x * sp.nb + d] = hist[d];
+}
+
+// Column scan of T (rows = chunks in use): every entry becomes the digit's
+// count in earlier chunks, tot[d] its total.  32 columns by 32 row groups a
+// workgroup.
+constexpr int SCAN_COLS = 32, SCAN_GROUPS = 32;
+__global__ __launch_bounds__(SCAN_COLS* SCAN_GROUPS) void k_sort_scan(uint32_t* T, uint32_t* tot,
+                                                                      SortPlan sp,
+                                                                      const int64_t* in_count) {
+  __shared__ uint32_t part[SCAN_GROUPS][SCAN_COLS + 1];
+  const int nk = (int)((in_count[0] + sp.chunk - 1) / sp.chunk);
+  const int col = threadIdx.x & (SCAN_COLS - 1), rg = threadIdx.x / SCAN_COLS;
+  const int d = blockIdx.x * SCAN_COLS + col;
+  const int per = (nk + SCAN_GROUPS - 1) / SCAN_GROUPS;
+  const int k0 = rg * per < nk ? rg * per : nk, k1 = k0 + per < nk ? k0 + per : nk;
+  uint32_t s = 0;
+  if (d < sp.nb) {
+#pragma unroll 8
+    for (int k = k0; k < k1; ++k) s += T[(int64_t)k * sp.nb + d];
+  }
+  part[rg][col] = s;
+  __syncthreads();
+  uint32_t run = 0;
+  for (int q = 0; q < rg; ++q) run += part[q][col];
+  if (d >= sp.nb) return;
+  if (rg == SCAN_GROUPS - 1) tot[d] = run + s;
+#pragma unroll 8
+  for (int k = k0; k < k1; ++k) {
+    const uint32_t v = T[(int64_t)k * sp.nb + d];
+    T[(int64_t)k * sp.nb + d] = run;
+    run += v;
+  }
+}
+
+// Per-wave digit starts: start[d] (the workgroup's first slot of digit d) is
+// handed to the waves in order, whist[w][d] = the wave's first slot.
+__device__ __forceinline__ void wave_starts(const uint32_t* start, uint32_t (*whist)[SORT_BUCKETS],
+                                            int nb) {
+  for (int d = threadIdx.x; d < nb; d += SORT_BLOCK) {
+    uint32_t run = start[d];
+#pragma unroll
+    for (int w = 0; w < SORT_WAVES; ++w) {
+      const uint32_t t = whist[w][d];
+      whist[w][d] = run;
+      run += t;
+    }
+  }
+}
+
+// The chunk's particles to their slots: the final order (PAIRS = false: the
+// digit is the cell), or (index, cell) pairs in bucket order.  With
+// self-scan (few chunks times digits) every workgroup sums the columns of T
+// itself; otherwise k_sort_scan has.
+template <typename S, bool G, bool PAIRS>
+__global__ __launch_bounds__(SORT_BLOCK) void k_sort_place(GridP g, PartP<S> in, PartP<S> out,
+                                                           const int32_t* __restrict__ key,
+                                                           const uint32_t* __restrict__ T,
+                                                           const uint32_t* __restrict__ tot,
+                                                           SortPlan sp, const int64_t* ns_in,
+                                                           int64_t* offsets, uint32_t* gperm,
+                                                           int32_t* pair_i, int32_t* pair_c,
+                                                           uint32_t* bucket_off) {
+  __shared__ uint32_t start[SORT_BUCKETS];
+  __shared__ uint32_t whist[SORT_WAVES][SORT_BUCKETS];
+  const int64_t n = in.count[0], ns = *ns_in;
+  const int64_t i0 = (int64_t)blockIdx.x * sp.chunk;
+  if (i0 >= n && blockIdx.x != 0) return;
+  const int64_t i1 = i0 + sp.chunk < n ? i0 + sp.chunk : n;
+  const int nk = (int)((n + sp.chunk - 1) / sp.chunk);
+  const int blk = (int)blockIdx.x;
+  // column sums and the sums of the earlier chunks (threads of different
+  // row groups share a column when there are fewer digits than threads)
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // each wave owns a run of consecutive slots of the chunk; the keys of its
+  // first SORT_U groups (all of them in the smallest chunk) are requested
+  // ahead of the column sums
+  const int64_t sub = sp.chunk / SORT_WAVES;
+  const int64_t w0 = i0 + wid * sub, w1 = w0 + sub < i1 ? w0 + sub : i1;
+  auto cells_at = [&](int64_t b, int32_t c[SORT_U]) {
+#pragma unroll
+    for (int u = 0; u < SORT_U; ++u) {
+      const int64_t i = b + u * 64 + lane;
+      c[u] = i >= w1 ? -1 : (i >= ns ? key[i] : in.cell[i]);
+      if (c[u] >= g.M) c[u] = -1;
+    }
+    if (g.flags) {
+#pragma unroll
+      for (int u = 0; u < SORT_U; ++u)
+        if (c[u] >= 0 && (g.flags[c[u]] & USP_FLAG_SOLID)) c[u] = -1;
+    }
+  };
+  int32_t cf[SORT_U];
+  cells_at(w0, cf);
+  uint32_t* before = whist[0];  // free until the waves count
+  if (sp.self_scan) {
+    for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) { start[d] = 0u; before[d] = 0u; }
+    __syncthreads();
+    const int cols = sp.nb < SORT_BLOCK ? sp.nb : SORT_BLOCK, groups = SORT_BLOCK / cols;
+    const int rg = threadIdx.x / cols, d0 = threadIdx.x - rg * cols;
+    if (rg < groups) {
+      const int per = (nk + groups - 1) / groups;
+      const int k0 = rg * per, k1 = k0 + per < nk ? k0 + per : nk;
+      for (int d = d0; d < sp.nb; d += cols) {
+        uint32_t all = 0, pre = 0;
+#pragma unroll 8
+        for (int k = k0; k < k1; ++k) {
+          const uint32_t v = T[(int64_t)k * sp.nb + d];
+          all += v;
+          pre += k < blk ? v : 0u;
+        }
+        if (all) atomicAdd(&start[d], all);
+        if (pre) atomicAdd(&before[d], pre);
+      }
+    }
+  } else {
+    for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) {
+      start[d] = tot[d];
+      before[d] = i0 < n ? T[(int64_t)blk * sp.nb + d] : 0u;
+    }
+  }
+  __syncthreads();
+  const uint32_t total = scan_lds(start, sp.nb);
+  if (blk == 0) {
+    if (PAIRS) {
+      for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) bucket_off[d] = start[d];
+      if (threadIdx.x == 0) bucket_off[sp.nb] = total;
+    } else {
+      for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) offsets[d] = (int64_t)start[d];
+      if (threadIdx.x == 0) {
+        offsets[sp.nb] = (int64_t)total;
+        out.count[0] = (int64_t)total;
+        out.count[1] = in.count[1];
+      }
+    }
+  }
+  for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) start[d] += before[d];
+  __syncthreads();
+  for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK)
+#pragma unroll
+    for (int w = 0; w < SORT_WAVES; ++w) whist[w][d] = 0u;
+  __syncthreads();
+  uint32_t* mine = whist[wid];
+  for (int64_t b = w0; b < w1; b += SORT_U * 64) {
+    int32_t c[SORT_U];
+    if (b == w0) {
+#pragma unroll
+      for (int u = 0; u < SORT_U; ++u) c[u] = cf[u];
+    } else {
+      cells_at(b, c);
+    }
+#pragma unroll
+    for (int u = 0; u < SORT_U; ++u) count_digits(mine, c[u] < 0 ? -1 : c[u] >> sp.shift);
+  }
+  __syncthreads();
+  wave_starts(start, whist, sp.nb);
+  __syncthreads();
+  const bool hx = g.dim == 2, hy = g.dim >= 1;
+  for (int64_t b = w0; b < w1; b += SORT_U * 64) {
+    int32_t c[SORT_U];
+    if (b == w0) {
+#pragma unroll
+      for (int u = 0; u < SORT_U; ++u) c[u] = cf[u];
+    } else {
+      cells_at(b, c);
+    }
+    uint32_t p[SORT_U], ii[SORT_U];
+#pragma unroll
+    for (int u = 0; u < SORT_U; ++u) {
+      p[u] = take_slot(mine, c[u] < 0 ? -1 : c[u] >> sp.shift, sp.bits);
+      ii[u] = (uint32_t)(b + u * 64 + lane);
+    }
+    if constexpr (PAIRS) {
+#pragma unroll
+      for (int u = 0; u < SORT_U; ++u)
+        if (c[u] >= 0) {
+          pair_i[p[u]] = (int32_t)ii[u];
+          pair_c[p[u]] = c[u];
+        }
+    } else {
+      place_many<G, SORT_U, S>(in, out, gperm, ii, p, c, hx, hy);
+    }
+  }
+}
+
+// One bucket of 2^shift consecutive cells: its pairs, already in input
+// order, to the cells' slots.  Buckets of a flow are uneven (a dense layer
+// holds a dozen times the mean), so a bucket gets a workgroup of 16 waves
+// and each wave keeps FINE_U groups of loads in flight.
+constexpr int FINE_BLOCK = 1024;
+constexpr int FINE_WAVES = FINE_BLOCK / 64;
+constexpr int FINE_U = 8;
+
+template <typename S, bool G>
+__global__ __launch_bounds__(FINE_BLOCK) void k_sort_fine(GridP g, PartP<S> in, PartP<S> out,
+                                                          SortPlan sp, int64_t* offsets,
+                                                          uint32_t* gperm,
+                                                          const int32_t* __restrict__ pair_i,
+                                                          const int32_t* __restrict__ pair_c,
+                                                          const uint32_t* __restrict__ bucket_off) {
+  extern __shared__ uint32_t fine_lds[];  // start[F], then next[FINE_WAVES][F]
+  const int F = 1 << sp.shift;
+  uint32_t* start = fine_lds;
+  const int64_t s0 = bucket_off[blockIdx.x], s1 = bucket_off[blockIdx.x + 1];
+  const int32_t c0 = (int32_t)((int64_t)blockIdx.x << sp.shift);
+  const int nf = (int)(g.M - c0 < F ? g.M - c0 : F);
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  uint32_t* mine = fine_lds + F + wid * F;
+  for (int d = lane; d < nf; d += 64) mine[d] = 0u;
+  const int64_t sub = ((s1 - s0 + FINE_BLOCK - 1) / FINE_BLOCK) * 64;
+  const int64_t w0 = s0 + wid * sub < s1 ? s0 + wid * sub : s1;
+  const int64_t w1 = w0 + sub < s1 ? w0 + sub : s1;
+  for (int64_t b = w0; b < w1; b += FINE_U * 64) {
+    int32_t c[FINE_U];
+#pragma unroll
+    for (int u = 0; u < FINE_U; ++u) {
+      const int64_t j = b + u * 64 + lane;
+      c[u] = j < w1 ? pair_c[j] - c0 : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < FINE_U; ++u) count_digits(mine, c[u]);
+  }
+  __syncthreads();
+  // the cells' totals, their scan by the first wave, the waves' first slots
+  for (int d = threadIdx.x; d < nf; d += FINE_BLOCK) {
+    uint32_t t = 0;
+#pragma unroll
+    for (int w = 0; w < FINE_WAVES; ++w) t += fine_lds[F + w * F + d];
+    start[d] = t;
+  }
+  __syncthreads();
+  if (wid == 0) {
+    uint32_t carry = (uint32_t)s0;
+    for (int d0 = 0; d0 < nf; d0 += 64) {
+      const int d = d0 + lane;
+      const uint32_t v = d < nf ? start[d] : 0u;
+      uint32_t x = v;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+      }
+      if (d < nf) {
+        start[d] = carry + x - v;
+        offsets[c0 + d] = (int64_t)(carry + x - v);
+      }
+      carry += __shfl(x, 63, 64);
+    }
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    offsets[g.M] = s1;
+    out.count[0] = s1;
+    out.count[1] = in.count[1];
+  }
+  __syncthreads();
+  for (int d = threadIdx.x; d < nf; d += FINE_BLOCK) {
+    uint32_t run = start[d];
+#pragma unroll
+    for (int w = 0; w < FINE_WAVES; ++w) {
+      const uint32_t t = fine_lds[F + w * F + d];
+      fine_lds[F + w * F + d] = run;
+      run += t;
+    }
+  }
+  __syncthreads();
+  const bool hx = g.dim == 2, hy = g.dim >= 1;
+  constexpr int U = G ? FINE_U : SORT_U;
+  for (int64_t b = w0; b < w1; b += U * 64) {
+    int32_t c[U];
+    uint32_t p[U], ii[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t j = b + u * 64 + lane;
+      c[u] = j < w1 ? pair_c[j] - c0 : -1;
+      ii[u] = j < w1 ? (uint32_t)pair_i[j] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) p[u] = take_slot(mine, c[u], sp.shift);
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = c[u] < 0 ? -1 : c0 + c[u];
+    place_many<G, U, S>(in, out, gperm, ii, p, c, hx, hy);
+  }
+}
+
+SortPlan sort_plan(int64_t M, int64_t capacity) {
+  SortPlan sp;
+  sp.shift = 0;
+  while (cdiv(M, (int64_t)1 << sp.shift) > SORT_BUCKETS) ++sp.shift;
+  sp.nb = (int)cdiv(M, (int64_t)1 << sp.shift);
+  sp.bits = 0;
+  while ((1 << sp.bits) < sp.nb) ++sp.bits;
+  const int64_t per = cdiv(cdiv(capacity, SORT_CHUNKS), SORT_BLOCK) * SORT_BLOCK;
+  sp.chunk = per > SORT_CHUNK_MIN ? per : SORT_CHUNK_MIN;
+  sp.nchunks = cdiv(capacity, sp.chunk);
+  sp.self_scan = sp.nchunks * sp.nb <= SORT_SELF_SCAN ? 1 : 0;
+  return sp;
+}
+
+template <typename S, bool G>
+hipError_t sort_launches(const GridP& g, const PartP<S>& in, const PartP<S>& out, int64_t* offsets,
+                         const int64_t* in_offsets, char* ws, const WsLayout& L, uint32_t* perm,
+                         int64_t* counters, hipStream_t st) {
+  const SortPlan sp = sort_plan(g.M, in.capacity);
+  int32_t* key = (int32_t*)(ws + L.key);
+  uint32_t* T = (uint32_t*)(ws + L.sort_t);
+  uint32_t* tot = (uint32_t*)(ws + L.sort_tot);
+  uint32_t* bucket_off = tot + SORT_BUCKETS;
+  int32_t* pair_i = (int32_t*)(ws + L.far);
+  int32_t* pair_c = pair_i + in.capacity;
+  int64_t* ns = (int64_t*)(ws + L.misc) + 6;
+  const int nk = (int)sp.nchunks;
+  k_sort_count<S><<<nk, SORT_BLOCK, 0, st>>>(g, in, in_offsets, key, T, sp, ns, counters);
+  if (!sp.self_scan)
+    k_sort_scan<<<(int)cdiv(sp.nb, SCAN_COLS), SCAN_COLS * SCAN_GROUPS, 0, st>>>(T, tot, sp, in.count);
+  if (sp.shift == 0) {
+    k_sort_place<S, G, false><<<nk, SORT_BLOCK, 0, st>>>(g, in, out, key, T, tot, sp, ns, offsets,
+                                                         perm, nullptr, nullptr, nullptr);
+  } else {
+    k_sort_place<S, G, true><<<nk, SORT_BLOCK, 0, st>>>(g, in, out, key, T, tot, sp, ns, offsets,
+                                                        perm, pair_i, pair_c, bucket_off);
+    const size_t lds = sizeof(uint32_t) * (size_t)(FINE_WAVES + 1) << sp.shift;
+    k_sort_fine<S, G><<<sp.nb, FINE_BLOCK, lds, st>>>(g, in, out, sp, offsets, perm, pair_i, pair_c,
+                                                    bucket_off);
+  }
+  return hipGetLastError();
+}
+
+template hipError_t sort_launches<float, true>(const GridP&, const PartP<float>&, const PartP<float>&,
+                                               int64_t*, const int64_t*, char*, const WsLayout&,
+                                               uint32_t*, int64_t*, hipStream_t);
+template hipError_t sort_launches<float, false>(const GridP&, const PartP<float>&,
+                                                const PartP<float>&, int64_t*, const int64_t*, char*,
+                                                const WsLayout&, uint32_t*, int64_t*, hipStream_t);
+template hipError_t sort_launches<double, true>(const GridP&, const PartP<double>&,
+                                                const PartP<double>&, int64_t*, const int64_t*,
+                                                char*, const WsLayout&, uint32_t*, int64_t*,
+                                                hipStream_t);
+template hipError_t sort_launches<double, false>(const GridP&, const PartP<double>&,
+                                                 const PartP<double>&, int64_t*, const int64_t*,
+                                                 char*, const WsLayout&, uint32_t*, int64_t*,
+                                                 hipStream_t);
+
+}  // namespace usp

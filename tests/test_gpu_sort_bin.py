@@ -1,0 +1,121 @@
+"""The sorting route of the bin against numpy's stable sort and against the
+neighbour-group route, at the edges of its chunks, digits and buckets."""
+import sys
+
+import numpy as np
+import pytest
+
+import usp_workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _usp():
+    from paper_2508_05642_amd import usp
+    return usp
+
+
+def _cells_state(M, n, f32, seed, cap=None, ordered=False):
+    """A 0D state of n particles in random (or ascending) cells of M, some of
+    them removed."""
+    rng = np.random.default_rng(seed)
+    grid = W.Grid(dim=0, nx=M, ny=1, fnum=1.0, volume=np.ones(M), flags=np.zeros(M, np.uint8))
+    prob = W.Problem("cells", W.Gas(), grid, W.BC(), dt=1e-8, seed=1, f32=f32)
+    cell = rng.integers(0, M, n)
+    if ordered:
+        cell = np.sort(cell)
+    cell[rng.random(n) < 0.05] = -1
+    dt = np.float32 if f32 else np.float64
+    v = {k: rng.standard_normal(n).astype(dt) for k in ("cx", "cy", "cz", "erot")}
+    parts = dict(n=n, cap=max(n, 1), x=None, y=None, vib=rng.integers(0, 200, n), cell=cell,
+                 pid=rng.permutation(n).astype(np.uint32), next_pid=n, **v)
+    return _usp().DeviceState(prob, parts, capacity=cap or max(n, 1)), parts
+
+
+def _check(st, parts, keep, cell):
+    order = keep[np.argsort(cell[keep], kind="stable")]
+    got = st.state()
+    assert got["n"] == len(order)
+    assert np.array_equal(got["cell"], cell[order])
+    for k in ("cx", "cy", "cz", "erot"):
+        assert np.array_equal(got[k], parts[k][order].astype(np.float64)), k
+    assert np.array_equal(got["pid"], parts["pid"][order])
+    assert np.array_equal(got["vib"], parts["vib"][order])
+    off = np.concatenate([[0], np.cumsum(np.bincount(cell[keep], minlength=st.M))])
+    assert np.array_equal(st.offsets.cpu().numpy(), off)
+
+
+# chunks hold 2048 slots, a pass 1024 digits; 40,000 particles on 1000 cells
+# is past the size whose column sums the placing kernel forms itself
+@pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("M,n", [(1, 0), (1, 1), (1, 2049), (2, 63), (3, 2047), (64, 2048),
+                                 (1000, 40000), (1000, 90001), (1023, 5000), (1024, 70000),
+                                 (1025, 5000), (1025, 90001), (5000, 20000), (70001, 30000),
+                                 (1 << 20, 4097)])
+def test_unordered_input_is_stably_sorted(M, n, f32):
+    print(f"[sort bin] M={M} n={n} f32={f32}", flush=True)
+    sys.stdout.flush()
+    st, parts = _cells_state(M, n, f32, seed=M + n)
+    cell = parts["cell"]
+    st.bin()
+    _check(st, parts, np.nonzero(cell >= 0)[0], cell)
+
+
+@pytest.mark.parametrize("M,n", [(1, 5000), (7, 3001), (1024, 70000), (1500, 60000)])
+def test_binned_input_after_moves_of_any_length(M, n):
+    """A binned state whose particles then move to any cell or are removed
+    (their cells rewritten, as the flight does), with a tail appended."""
+    print(f"[sort bin, binned] M={M} n={n}", flush=True)
+    st, _ = _cells_state(M, n, True, seed=5, cap=n + 999, ordered=True)
+    st.bin()
+    s = st.state()
+    rng = np.random.default_rng(6)
+    tail = 999
+    cell = np.concatenate([rng.integers(0, M, s["n"]), rng.integers(0, M, tail)]).astype(np.int32)
+    cell[rng.random(len(cell)) < 0.03] = -1
+    tot = s["n"] + tail
+    buf = st.bufs[st.cur]
+    parts = {k: rng.standard_normal(tot).astype(np.float32) for k in ("cx", "cy", "cz", "erot")}
+    parts["vib"] = rng.integers(0, 200, tot).astype(np.uint8)
+    parts["pid"] = rng.permutation(tot).astype(np.uint32)
+    for k in ("cx", "cy", "cz", "erot", "vib"):
+        buf[k][:tot] = torch.as_tensor(parts[k])
+    buf["pid"][:tot] = torch.as_tensor(parts["pid"].view(np.int32))
+    buf["cell"][:tot] = torch.as_tensor(cell)
+    buf["count"][0] = tot
+    st.bin()
+    _check(st, parts, np.nonzero(cell >= 0)[0], cell)
+
+
+# the capacity decides the route on grids of more than 1024 cells
+BIG = 9 << 20
+
+
+@pytest.mark.parametrize("gather", [True, False])
+@pytest.mark.parametrize("kind,f32", [("2d", True), ("2d", False), ("1d", True)])
+def test_routes_give_the_same_state(kind, f32, gather):
+    """Three steps through either route: the same bits, counts and events."""
+    usp = _usp()
+    if kind == "2d":
+        prob = W.cylinder(scale=0.08, f32=f32, ppc=30.0)
+    else:  # flights of up to some dozens of cells
+        prob = W.poiseuille(kn=0.01, cells=1400, ppc=20, f32=f32)
+    parts = W.particles_for(prob)
+    print(f"[sort bin, routes] {kind} f32={f32} gather={gather} n={parts['n']}", flush=True)
+    got = []
+    for cap in (parts["n"] * 2, BIG):
+        st = usp.DeviceState(prob, parts, capacity=cap)
+        for k in range(3):
+            st.bin(gather=gather)
+            st.do_moments()
+            st.do_reconstruct()
+            st.update(k)
+        st.bin()
+        got.append((st.state(), st.offsets.cpu().numpy(), st.cnt(), st.moments()))
+    (a, oa, ca, ma), (b, ob, cb, mb) = got
+    assert ca == cb
+    assert np.array_equal(oa, ob) and np.array_equal(ma, mb)
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
