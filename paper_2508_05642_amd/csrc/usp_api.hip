@@ -183,7 +183,7 @@ usp_status do_step(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, d
   // per cell above it) would give whole cells to single workgroups: such
   // grids run the separate phase kernels, which spread every particle over
   // the chip, after a copying bin, with the moments and the conservation's
-  // sums split over chunks of each cell.
+  // sums split over chunks of each cell (usp_bigcell.hip).
   const int stage = sizeof(S) == 4 ? UPDATE_STAGE_F32 : UPDATE_STAGE_F64;
   const bool big_cells = cdiv(cap, g.M) > stage;
   for (int32_t s = 0; s < nsteps; ++s) {
@@ -198,17 +198,17 @@ usp_status do_step(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, d
         const usp_particles tmp = *p;
         *p = *p_alt;
         *p_alt = tmp;
+        if ((e = launch_chunks(g, offsets, w, L, st)) != hipSuccess) return USP_EDEVICE;
       }
-      // the per-cell reductions split over chunks of each cell
       const PartP<S> q = make_parts<S>(p);
-      if ((e = launch_moments_split<S>(g, q, offsets, mom, w, L, st)) != hipSuccess)
+      // in 0D the scalings of a step wait for the next step's moments
+      if ((e = launch_cells_split<S>(g, gp, q, offsets, mom, dt, dt_cell, cs, g.dim == 0 && s > 0, w,
+                                     L, counters, st)) != hipSuccess)
         return USP_EDEVICE;
-      if ((e = launch_reconstruct(g, gp, mom, dt, dt_cell, cs, counters, st)) != hipSuccess)
-        return USP_EDEVICE;
-      if ((e = launch_collide<S>(g, gp, cs, offsets, q, seed, sn, counters, st)) != hipSuccess)
-        return USP_EDEVICE;
-      if ((e = launch_conserve_split<S>(g, gp, cs, offsets, q, seed, sn, w, L, counters, st)) !=
+      if ((e = launch_collide_split<S>(g, gp, cs, offsets, q, seed, sn, w, L, counters, st)) !=
           hipSuccess)
+        return USP_EDEVICE;
+      if ((g.dim != 0 || s == nsteps - 1) && (e = launch_cons_apply<S>(q, w, L, st)) != hipSuccess)
         return USP_EDEVICE;
       if (g.dim != 0 &&
           (e = launch_advect<S>(g, gp, bp, dt, q, seed, sn, w, L, counters, st)) != hipSuccess)

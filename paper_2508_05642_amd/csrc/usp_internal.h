@@ -143,7 +143,7 @@ struct WsLayout {
 // binned state of `capacity` slots in M cells can have.
 constexpr int BIG_CHUNK = 512;
 constexpr int BIG_PARTS = 20;
-constexpr size_t CONS_SCALAR_BYTES = 80;
+constexpr size_t CONS_SCALAR_BYTES = 96;
 inline int64_t chunks_max(int64_t capacity, int64_t M) {
   return (capacity + BIG_CHUNK - 1) / BIG_CHUNK + M;
 }
@@ -206,17 +206,28 @@ template <typename S>
 hipError_t launch_collide(const GridP& g, const GasP& gas, const double* cs, const int64_t* offsets,
                           const PartP<S>& p, uint64_t seed, uint64_t step, int64_t* counters,
                           hipStream_t st);
-// The moments and the conservation with every cell split into chunks of
-// BIG_CHUNK slots (same quantities, partial sums combined in chunk order;
-// the conservation reuses the chunk index of the moments).
+// The stencils of the reconstruction (1D, 2D) and, under the per-cell
+// reading, the cells' coefficients, after the cell state.
+hipError_t launch_stencil(const GridP& g, const GasP& gas, double* cs, hipStream_t st);
+// A step of a grid whose cells are split into chunks of BIG_CHUNK slots
+// (partial sums combined in chunk order), on a binned state: the chunk
+// index of the cells; the moments, cell state and stencils (apply: the
+// scalings of the collision before are applied on the way); the particle
+// update and the conservation's picks and scalars; the scalings alone.
+hipError_t launch_chunks(const GridP& g, const int64_t* offsets, char* ws, const WsLayout& L,
+                         hipStream_t st);
 template <typename S>
-hipError_t launch_moments_split(const GridP& g, const PartP<S>& p, const int64_t* offsets,
-                                double* mom, char* ws, const WsLayout& L, hipStream_t st);
+hipError_t launch_cells_split(const GridP& g, const GasP& gas, const PartP<S>& p,
+                              const int64_t* offsets, double* mom, double dt, const double* dt_cell,
+                              double* cs, bool apply, char* ws, const WsLayout& L,
+                              int64_t* counters, hipStream_t st);
 template <typename S>
-hipError_t launch_conserve_split(const GridP& g, const GasP& gas, const double* cs,
-                                 const int64_t* offsets, const PartP<S>& p, uint64_t seed,
-                                 uint64_t step, char* ws, const WsLayout& L, int64_t* counters,
-                                 hipStream_t st);
+hipError_t launch_collide_split(const GridP& g, const GasP& gas, const double* cs,
+                                const int64_t* offsets, const PartP<S>& p, uint64_t seed,
+                                uint64_t step, char* ws, const WsLayout& L, int64_t* counters,
+                                hipStream_t st);
+template <typename S>
+hipError_t launch_cons_apply(const PartP<S>& p, char* ws, const WsLayout& L, hipStream_t st);
 template <typename S>
 hipError_t launch_conserve(const GridP& g, const GasP& gas, const double* cs,
                            const int64_t* offsets, const PartP<S>& p, uint64_t seed, uint64_t step,

@@ -148,6 +148,12 @@ hipError_t launch_moments(const GridP& g, const PartP<S>& p, const int64_t* offs
   return hipGetLastError();
 }
 
+hipError_t launch_stencil(const GridP& g, const GasP& gas, double* cs, hipStream_t st) {
+  if (g.dim != 0) k_stencil<<<cdiv(g.M, 256), 256, 0, st>>>(g, cs);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_cell_coef(g, gas, cs, st);
+}
+
 hipError_t launch_reconstruct(const GridP& g, const GasP& gas, const double* mom, double dt,
                               const double* dt_cell, double* cs, int64_t* counters, hipStream_t st) {
   if (g.M <= CELL_SMALL) {

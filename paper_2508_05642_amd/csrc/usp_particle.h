@@ -893,17 +893,17 @@ __device__ __forceinline__ void cons_sums(const double Un[3], int64_t i0, int64_
   }
 }
 
-// The conservation of cell c from its wave-reduced sums s (uniform on the
-// wave) and largest level lmax: (i) the vibrational correction, |I_delta|
-// single-level moves by wave_picks on the cell's levels lv, (ii) the
-// rotational factor to the cell target, (iii) the velocity factor about U*
-// toward U^n that restores momentum and total energy with the energies
-// actually reached.  Called by a whole wave; the result is uniform.
-__device__ __forceinline__ ConsScalars cons_scalars(const GasP& gas, const ConsIn& in, int64_t c,
-                                                    int64_t N, const double s[6], int lmax,
-                                                    uint8_t* lv, uint64_t seed, uint32_t step,
-                                                    int64_t* counters) {
-  const int lane = threadIdx.x & 63;
+// The conservation of a cell of N particles from its post-collision sums s:
+// (i) the vibrational correction, |I_delta| single-level moves by pick(I_delta,
+// &sum of levels), which returns 1 if any level changed, (ii) the rotational
+// factor to the cell target, (iii) the velocity factor about U* toward U^n
+// that restores momentum and total energy with the energies actually
+// reached.  s is the same on every caller; `lead` (one caller) counts the
+// skipped scalings.
+template <typename PICK>
+__device__ __forceinline__ ConsScalars cons_scalars_of(const GasP& gas, const ConsIn& in, int64_t N,
+                                                       const double s[6], bool lead,
+                                                       int64_t* counters, PICK pick) {
   ConsScalars r;
   r.Un[0] = in.Un[0]; r.Un[1] = in.Un[1]; r.Un[2] = in.Un[2];
   const double evib_t = in.evib_t, erot_t = in.erot_t, E0 = in.E0;
@@ -918,11 +918,8 @@ __device__ __forceinline__ ConsScalars cons_scalars(const GasP& gas, const ConsI
   // sampled and conserves momentum and total energy through the velocities
   const bool fpm = gas.scheme == USP_SCHEME_FPM;
   const int64_t Id0 = fpm ? 0 : (int64_t)floor(X + in.u0);
-  // no level can reach VIB_MAX through these increments
-  const int64_t need0 = Id0 > 0 ? Id0 : 0;
-  const bool low = !__ballot((int64_t)lmax + need0 >= VIB_MAX);
-  r.moved = wave_picks(lv, N, Id0, &SI, (uint32_t)c, step, seed, low, counters);
-  // the cell scalars, the same on every lane (wave-uniform inputs)
+  r.moved = pick(Id0, &SI);
+  // the cell scalars, the same on every caller
   r.frot = 0.0; r.sc = 0.0;
   const double etr_s = 0.5 * (s[3] * iN - (m1[0] * m1[0] + m1[1] * m1[1] + m1[2] * m1[2]));
   // (ii) rotational scaling to the cell target
@@ -942,10 +939,30 @@ __device__ __forceinline__ ConsScalars cons_scalars(const GasP& gas, const ConsI
   const double s2 = (E0 - erot_a - evib_a) / etr_s;
   if (etr_s > 0.0 && s2 > 0.0) r.sc = sqrt(s2);
   else ++skips;
-  if (lane == 0)
+  if (lead)
     for (int k = 0; k < skips; ++k) count_event(counters, USP_CNT_CONS_SKIP);
   r.Us[0] = r.Un[0] + m1[0]; r.Us[1] = r.Un[1] + m1[1]; r.Us[2] = r.Un[2] + m1[2];
   return r;
+}
+
+// No level of a set whose largest is lmax can reach VIB_MAX through these
+// moves.
+__device__ __forceinline__ bool moves_stay_low(int lmax, int64_t Id) {
+  const int64_t need = Id > 0 ? Id : 0;
+  return (int64_t)lmax + need < VIB_MAX;
+}
+
+// The same by one wave: s reduced over it, lmax each lane's largest level,
+// lv the cell's levels.  The result is uniform.
+__device__ __forceinline__ ConsScalars cons_scalars(const GasP& gas, const ConsIn& in, int64_t c,
+                                                    int64_t N, const double s[6], int lmax,
+                                                    uint8_t* lv, uint64_t seed, uint32_t step,
+                                                    int64_t* counters) {
+  const int lane = threadIdx.x & 63;
+  return cons_scalars_of(gas, in, N, s, lane == 0, counters, [&](int64_t Id, int64_t* SI) {
+    const bool low = !__ballot(!moves_stay_low(lmax, Id));
+    return wave_picks(lv, N, Id, SI, (uint32_t)c, step, seed, low, counters);
+  });
 }
 
 // The conservation's scalings of particle i (vx[i - base] etc.).
