@@ -238,8 +238,9 @@ static hipError_t step_taped(const GridP& g, const GasP& gas, const BcP& bc, dou
   cb.add(tape + T.cell, out.cell, (size_t)cap * 4);
   cb.add(tape + T.pid, out.pid, (size_t)cap * 4);
   cb.launch(st, &ce);
-  if ((e = launch_moments<double>(g, out, offsets, mom, st)) != hipSuccess) return e;
-  if ((e = launch_reconstruct(g, gas, mom, dt, nullptr, cs, counters, st)) != hipSuccess) return e;
+  if ((e = launch_cells<double>(g, gas, out, offsets, mom, dt, nullptr, cs, counters, st)) !=
+      hipSuccess)
+    return e;
   cb.add(tape + T.offsets, offsets, (size_t)(g.M + 1) * 8);
   cb.add(tape + T.cs, cs, cellstate_bytes(g.M));
   cb.launch(st, &ce);

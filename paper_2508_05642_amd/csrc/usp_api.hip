@@ -225,14 +225,16 @@ usp_status do_step(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, d
       // particle phase writes the whole state in the new order to p_alt
       uint32_t* gperm = (uint32_t*)(w + L.perm);
       const PartP<S> in = make_parts<S>(p), out = make_parts<S>(p_alt);
+      // (the bin makes the particle phase's tile index beside its offsets)
       if ((e = launch_bin<S>(g, in, out, offsets, s > 0 ? offsets : in_offsets, w, L, counters, st,
-                             gperm)) != hipSuccess)
+                             gperm, TileIndex{(int32_t*)(w + L.tiles),
+                                              update_ntiles(stage, cap, g.M), stage})) != hipSuccess)
         return USP_EDEVICE;
-      if ((e = launch_moments<S>(g, in, offsets, mom, st, gperm)) != hipSuccess) return USP_EDEVICE;
-      if ((e = launch_reconstruct(g, gp, mom, dt, dt_cell, cs, counters, st)) != hipSuccess)
+      if ((e = launch_cells<S>(g, gp, in, offsets, mom, dt, dt_cell, cs, counters, st, gperm)) !=
+          hipSuccess)
         return USP_EDEVICE;
       if ((e = launch_update<S>(g, gp, bp, dt, cs, offsets, out, seed, sn, w, L, counters, st, &in,
-                                gperm)) != hipSuccess)
+                                gperm, nullptr, nullptr, true)) != hipSuccess)
         return USP_EDEVICE;
       const usp_particles tmp = *p;
       *p = *p_alt;
@@ -240,9 +242,11 @@ usp_status do_step(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, d
       continue;
     }
     const PartP<S> q = make_parts<S>(p);
-    if ((e = launch_moments<S>(g, q, offsets, mom, st)) != hipSuccess) return USP_EDEVICE;
-    if ((e = launch_reconstruct(g, gp, mom, dt, dt_cell, cs, counters, st)) != hipSuccess) return USP_EDEVICE;
-    if ((e = launch_update<S>(g, gp, bp, dt, cs, offsets, q, seed, sn, w, L, counters, st)) != hipSuccess)
+    if ((e = launch_cells<S>(g, gp, q, offsets, mom, dt, dt_cell, cs, counters, st)) != hipSuccess)
+      return USP_EDEVICE;
+    // the first step's tile index stands: nothing has moved
+    if ((e = launch_update<S>(g, gp, bp, dt, cs, offsets, q, seed, sn, w, L, counters, st, nullptr,
+                              nullptr, nullptr, nullptr, true)) != hipSuccess)
       return USP_EDEVICE;
   }
   return USP_OK;

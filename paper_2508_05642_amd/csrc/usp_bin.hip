@@ -72,15 +72,22 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_scan_reduce(const int32_t* counts
 
 // Each block adds up the totals of the blocks before it (at most a few
 // hundred, read from L2), then scans its own tile; the last block writes the
-// total to offsets[M] and the output particle count.
+// total to offsets[M] and the output particle count.  With ti the tile
+// index of the update is made on the way.
 __global__ __launch_bounds__(BIN_BLOCK) void k_scan_down(const int32_t* counts, int64_t M,
                                                          const int64_t* blocksums,
                                                          int64_t* offsets, int64_t* out_count,
-                                                         const int64_t* in_count) {
-  int64_t before = 0;
+                                                         const int64_t* in_count, TileIndex ti) {
+  int64_t before = 0, all = 0;
   for (int64_t b = threadIdx.x; b < (int64_t)blockIdx.x; b += BIN_BLOCK) before += blocksums[b];
   int64_t block_base;
   block_exclusive_scan(before, &block_base);
+  if (ti.first) {  // the tile window comes from the total
+    for (int64_t b = threadIdx.x; b < (int64_t)gridDim.x; b += BIN_BLOCK) all += blocksums[b];
+    int64_t t;
+    block_exclusive_scan(all, &t);
+    all = t;
+  }
   // blocked arrangement: thread t owns SCAN_ITEMS consecutive entries
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
   int32_t v[SCAN_ITEMS];
@@ -92,11 +99,17 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_scan_down(const int32_t* counts, 
   }
   int64_t tot;
   int64_t run = block_base + block_exclusive_scan(s, &tot);
+  const int64_t W = ti.first ? update_tile(ti.stage, all, M) : 1;
   for (int k = 0; k < SCAN_ITEMS; ++k) {
     const int64_t j = base + k;
-    if (j < M) offsets[j] = run;
+    if (j < M) {
+      offsets[j] = run;
+      if (ti.first) mark_tiles(ti, W, j, run, run + v[k]);
+    }
     run += v[k];
   }
+  if (ti.first && blockIdx.x == gridDim.x - 1)
+    mark_last_tiles(ti, W, M, all, threadIdx.x, BIN_BLOCK);
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
     offsets[M] = block_base + tot;
     if (out_count) {
@@ -624,17 +637,18 @@ __global__ void k_bin_init(const int64_t* src, int64_t* dst, int64_t M, int32_t*
 }
 
 static void launch_scan(const int32_t* cnt, int64_t M, int64_t* out_off, int64_t* blocksums,
-                        int64_t* out_count, const int64_t* in_count, hipStream_t st) {
+                        int64_t* out_count, const int64_t* in_count, hipStream_t st,
+                        const TileIndex& ti = TileIndex{nullptr, 0, 0}) {
   const int64_t nb = cdiv(M, SCAN_TILE);
   k_scan_reduce<<<nb, BIN_BLOCK, 0, st>>>(cnt, M, blocksums);
-  k_scan_down<<<nb, BIN_BLOCK, 0, st>>>(cnt, M, blocksums, out_off, out_count, in_count);
+  k_scan_down<<<nb, BIN_BLOCK, 0, st>>>(cnt, M, blocksums, out_off, out_count, in_count, ti);
 }
 
 template <typename S, bool G>
 static hipError_t bin_launches(const GridP& g, const PartP<S>& in, const PartP<S>& out,
                                int64_t* offsets, const int64_t* in_offsets, char* ws,
                                const WsLayout& L, uint32_t* perm, int64_t* counters,
-                               hipStream_t st) {
+                               hipStream_t st, const TileIndex& ti) {
   int32_t* key = (int32_t*)(ws + L.key);
   int64_t* blocksums = (int64_t*)(ws + L.blocksums);
   int32_t* T9 = (int32_t*)(ws + L.t9);
@@ -671,7 +685,7 @@ static hipError_t bin_launches(const GridP& g, const PartP<S>& in, const PartP<S
   k_cell_bases<<<cdiv(M, BIN_BLOCK), BIN_BLOCK, 0, st>>>(g, nb, old_off, in.count, T9, far_off,
                                                           far_list, far_base, tail_cnt, nontail,
                                                           cnt_total);
-  launch_scan(cnt_total, M, offsets, blocksums, out.count, in.count, st);
+  launch_scan(cnt_total, M, offsets, blocksums, out.count, in.count, st, ti);
   k_bin_scatter<S, G><<<cdiv(M, BIN_BLOCK / 64), BIN_BLOCK, 0, st>>>(g, nb, in, out, perm, old_off, key, T9,
                                                                    offsets);
   const int FAR_GRID = 64;
@@ -692,24 +706,24 @@ static hipError_t bin_launches(const GridP& g, const PartP<S>& in, const PartP<S
 template <typename S>
 hipError_t launch_bin(const GridP& g, const PartP<S>& in, const PartP<S>& out, int64_t* offsets,
                       const int64_t* in_offsets, char* ws, const WsLayout& L, int64_t* counters,
-                      hipStream_t st, uint32_t* gather_perm) {
+                      hipStream_t st, uint32_t* gather_perm, TileIndex ti) {
   if (sort_route(g.M, in.capacity, in_offsets != nullptr, gather_perm != nullptr))
     return gather_perm
                ? sort_launches<S, true>(g, in, out, offsets, in_offsets, ws, L, gather_perm,
-                                        counters, st)
+                                        counters, st, ti)
                : sort_launches<S, false>(g, in, out, offsets, in_offsets, ws, L, nullptr, counters,
-                                         st);
+                                         st, ti);
   if (gather_perm)
-    return bin_launches<S, true>(g, in, out, offsets, in_offsets, ws, L, gather_perm, counters, st);
+    return bin_launches<S, true>(g, in, out, offsets, in_offsets, ws, L, gather_perm, counters, st, ti);
   return bin_launches<S, false>(g, in, out, offsets, in_offsets, ws, L, (uint32_t*)(ws + L.perm),
-                                counters, st);
+                                counters, st, ti);
 }
 
 template hipError_t launch_bin<float>(const GridP&, const PartP<float>&, const PartP<float>&,
                                       int64_t*, const int64_t*, char*, const WsLayout&, int64_t*,
-                                      hipStream_t, uint32_t*);
+                                      hipStream_t, uint32_t*, TileIndex);
 template hipError_t launch_bin<double>(const GridP&, const PartP<double>&, const PartP<double>&,
                                        int64_t*, const int64_t*, char*, const WsLayout&, int64_t*,
-                                       hipStream_t, uint32_t*);
+                                       hipStream_t, uint32_t*, TileIndex);
 
 }  // namespace usp

@@ -73,6 +73,23 @@ __device__ __forceinline__ void place(const PartP<S>& in, const PartP<S>& out, u
   }
 }
 
+// Tile index entries that cell c, with the output segment [o, o1), decides:
+// the tiles whose window starts past the cell's first slot and not past
+// its end begin at the next cell (window W); cell 0 also opens tile 0.
+__device__ __forceinline__ void mark_tiles(const TileIndex& ti, int64_t W, int64_t c, int64_t o,
+                                           int64_t o1) {
+  if (c == 0) ti.first[0] = 0;
+  int64_t hi = o1 / W;
+  if (hi > ti.ntiles) hi = ti.ntiles;
+  for (int64_t t = o / W + 1; t <= hi; ++t) ti.first[t] = (int32_t)(c + 1);
+}
+
+// The tiles past the last particle begin at cell M (by `stride` threads).
+__device__ __forceinline__ void mark_last_tiles(const TileIndex& ti, int64_t W, int64_t M,
+                                                int64_t total, int64_t thread, int64_t stride) {
+  for (int64_t t = total / W + 1 + thread; t <= ti.ntiles; t += stride) ti.first[t] = (int32_t)M;
+}
+
 // U particles i[u] of a lane to the slots p[u] (c[u] < 0: none).  Copied
 // array by array: all U loads of an array, and of the arrays around it, are
 // in flight before the stores (an idle entry reads particle 0 of a non-empty

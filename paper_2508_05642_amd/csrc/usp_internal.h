@@ -182,17 +182,28 @@ inline bool sort_route(int64_t M, int64_t capacity, bool binned, bool gather) {
   if (M > (int64_t)SORT_BUCKETS * SORT_BUCKETS) return false;
   return !binned || M <= SORT_BUCKETS || capacity <= (gather ? SORT_GATHER_CAP : SORT_COPY_CAP);
 }
+struct TileIndex;
 template <typename S, bool G>
 hipError_t sort_launches(const GridP& g, const PartP<S>& in, const PartP<S>& out, int64_t* offsets,
                          const int64_t* in_offsets, char* ws, const WsLayout& L, uint32_t* perm,
-                         int64_t* counters, hipStream_t st);
+                         int64_t* counters, hipStream_t st, const TileIndex& ti);
 int n_faces(const GridP& g);
+
+// Tile index of the fused particle phase, made by the bin beside its
+// offsets when first is not null: first[t] (t = 0..ntiles) as launch_tiles
+// gives it.
+struct TileIndex {
+  int32_t* first;
+  int64_t ntiles;
+  int stage;
+};
 
 // launchers (return hipError_t of the last launch)
 template <typename S>
 hipError_t launch_bin(const GridP& g, const PartP<S>& in, const PartP<S>& out, int64_t* offsets,
                       const int64_t* in_offsets, char* ws, const WsLayout& L, int64_t* counters,
-                      hipStream_t st, uint32_t* gather_perm = nullptr);
+                      hipStream_t st, uint32_t* gather_perm = nullptr,
+                      TileIndex ti = TileIndex{nullptr, 0, 0});
 template <typename S>
 hipError_t launch_moments(const GridP& g, const PartP<S>& p, const int64_t* offsets, double* mom,
                           hipStream_t st, const uint32_t* gather_perm = nullptr);
@@ -201,6 +212,12 @@ hipError_t launch_moments(const GridP& g, const PartP<S>& p, const int64_t* offs
 hipError_t launch_cell_coef(const GridP& g, const GasP& gas, double* cs, hipStream_t st);
 hipError_t launch_reconstruct(const GridP& g, const GasP& gas, const double* mom, double dt,
                               const double* dt_cell, double* cs, int64_t* counters, hipStream_t st);
+// launch_moments followed by launch_reconstruct, in fewer launches on grids
+// of few cells.
+template <typename S>
+hipError_t launch_cells(const GridP& g, const GasP& gas, const PartP<S>& p, const int64_t* offsets,
+                        double* mom, double dt, const double* dt_cell, double* cs,
+                        int64_t* counters, hipStream_t st, const uint32_t* gather_perm = nullptr);
 hipError_t launch_sample_fields(const GridP& g, const double* mom, double* acc, hipStream_t st);
 template <typename S>
 hipError_t launch_collide(const GridP& g, const GasP& gas, const double* cs, const int64_t* offsets,
@@ -251,7 +268,7 @@ hipError_t launch_update(const GridP& g, const GasP& gas, const BcP& bc, double 
                          uint64_t seed, uint64_t step, char* ws, const WsLayout& L,
                          int64_t* counters, hipStream_t st, const PartP<S>* src = nullptr,
                          const uint32_t* gather_perm = nullptr, hipEvent_t ev_begin = nullptr,
-                         hipEvent_t ev_end = nullptr);
+                         hipEvent_t ev_end = nullptr, bool tiles_done = false);
 // Adds to *found the number of NaN or infinite values among the live
 // particles' floating arrays and, when given, the moment and FP64
 // cell-state planes of the occupied cells.
@@ -279,15 +296,29 @@ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // first particle lies in one window, so it spans the window plus the part
 // of its last cell past the window's end.  The window is the stage less
 // 13/8 of the mean particles per cell (n / M), kept within [stage/8,
-// 7 stage/8], so that most tiles fit the stage.  It shrinks as n grows:
-// the window of the capacity bounds the number of tiles any count needs.
+// 7 stage/8], so that most tiles fit the stage; a state too small to fill
+// the chip with such windows is cut into UPDATE_TILES of them (two
+// workgroups on each of 256 CUs, one round): the particle phase of 960
+// particles in 16 cells took 21 us as one tile and takes 15 as eight.
+constexpr int64_t UPDATE_TILES = 512;
 __host__ __device__ inline int64_t update_tile(int stage, int64_t n, int64_t M) {
   const int64_t ppc = M > 0 ? (n + M - 1) / M : stage;
   int64_t t = stage - ppc - ppc / 2 - ppc / 8;
   const int64_t lo = stage / 8, hi = stage - stage / 8;
   if (t < lo) t = lo;
   if (t > hi) t = hi;
+  const int64_t even = (n + UPDATE_TILES - 1) / UPDATE_TILES;
+  if (t > even) t = even;
   return t < UPDATE_TILE_MIN ? UPDATE_TILE_MIN : t;
+}
+// Tiles that any count up to `capacity` needs: the count over its window
+// grows with the count, except that an evenly cut state needs UPDATE_TILES
+// (and no window is below UPDATE_TILE_MIN).
+inline int64_t update_ntiles(int stage, int64_t capacity, int64_t M) {
+  const int64_t n = cdiv(capacity, update_tile(stage, capacity, M));
+  const int64_t most = cdiv(capacity, UPDATE_TILE_MIN);
+  const int64_t even = n > UPDATE_TILES ? n : UPDATE_TILES;
+  return even < most ? even : most;
 }
 
 }  // namespace usp

@@ -42,7 +42,7 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 template <typename S>
 size_t noalloc_layout(const GridP& g, int64_t capacity, WsLayout* L) {
   const int stage = sizeof(S) == 4 ? UPDATE_STAGE_F32 : UPDATE_STAGE_F64;
-  const int64_t ntiles = cdiv(capacity, update_tile(stage, capacity, g.M));
+  const int64_t ntiles = update_ntiles(stage, capacity, g.M);
   const int nf = n_faces(g);
   size_t o = 0;
   *L = WsLayout{};

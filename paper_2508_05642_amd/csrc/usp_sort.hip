@@ -220,7 +220,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort_place(GridP g, PartP<S> in,
                                                            SortPlan sp, const int64_t* ns_in,
                                                            int64_t* offsets, uint32_t* gperm,
                                                            int32_t* pair_i, int32_t* pair_c,
-                                                           uint32_t* bucket_off) {
+                                                           uint32_t* bucket_off, TileIndex ti) {
   __shared__ uint32_t start[SORT_BUCKETS];
   __shared__ uint32_t whist[SORT_WAVES][SORT_BUCKETS];
   const int64_t n = in.count[0], ns = *ns_in;
@@ -292,7 +292,14 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort_place(GridP g, PartP<S> in,
         out.count[0] = (int64_t)total;
         out.count[1] = in.count[1];
       }
+      if (ti.first) {
+        const int64_t W = update_tile(ti.stage, total, g.M);
+        for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK)
+          mark_tiles(ti, W, d, start[d], d + 1 < sp.nb ? start[d + 1] : total);
+        mark_last_tiles(ti, W, g.M, total, threadIdx.x, SORT_BLOCK);
+      }
     }
+    __syncthreads();  // start changes below
   }
   for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) start[d] += before[d];
   __syncthreads();
@@ -357,7 +364,8 @@ __global__ __launch_bounds__(FINE_BLOCK) void k_sort_fine(GridP g, PartP<S> in, 
                                                           uint32_t* gperm,
                                                           const int32_t* __restrict__ pair_i,
                                                           const int32_t* __restrict__ pair_c,
-                                                          const uint32_t* __restrict__ bucket_off) {
+                                                          const uint32_t* __restrict__ bucket_off,
+                                                          TileIndex ti) {
   extern __shared__ uint32_t fine_lds[];  // start[F], then next[FINE_WAVES][F]
   const int F = 1 << sp.shift;
   uint32_t* start = fine_lds;
@@ -413,6 +421,12 @@ __global__ __launch_bounds__(FINE_BLOCK) void k_sort_fine(GridP g, PartP<S> in, 
     out.count[1] = in.count[1];
   }
   __syncthreads();
+  if (ti.first) {
+    const int64_t total = bucket_off[sp.nb], W = update_tile(ti.stage, total, g.M);
+    for (int d = threadIdx.x; d < nf; d += FINE_BLOCK)
+      mark_tiles(ti, W, c0 + d, start[d], d + 1 < nf ? start[d + 1] : s1);
+    if (blockIdx.x == gridDim.x - 1) mark_last_tiles(ti, W, g.M, total, threadIdx.x, FINE_BLOCK);
+  }
   for (int d = threadIdx.x; d < nf; d += FINE_BLOCK) {
     uint32_t run = start[d];
 #pragma unroll
@@ -459,7 +473,7 @@ SortPlan sort_plan(int64_t M, int64_t capacity) {
 template <typename S, bool G>
 hipError_t sort_launches(const GridP& g, const PartP<S>& in, const PartP<S>& out, int64_t* offsets,
                          const int64_t* in_offsets, char* ws, const WsLayout& L, uint32_t* perm,
-                         int64_t* counters, hipStream_t st) {
+                         int64_t* counters, hipStream_t st, const TileIndex& ti) {
   const SortPlan sp = sort_plan(g.M, in.capacity);
   int32_t* key = (int32_t*)(ws + L.key);
   uint32_t* T = (uint32_t*)(ws + L.sort_t);
@@ -474,30 +488,25 @@ hipError_t sort_launches(const GridP& g, const PartP<S>& in, const PartP<S>& out
     k_sort_scan<<<(int)cdiv(sp.nb, SCAN_COLS), SCAN_COLS * SCAN_GROUPS, 0, st>>>(T, tot, sp, in.count);
   if (sp.shift == 0) {
     k_sort_place<S, G, false><<<nk, SORT_BLOCK, 0, st>>>(g, in, out, key, T, tot, sp, ns, offsets,
-                                                         perm, nullptr, nullptr, nullptr);
+                                                         perm, nullptr, nullptr, nullptr, ti);
   } else {
     k_sort_place<S, G, true><<<nk, SORT_BLOCK, 0, st>>>(g, in, out, key, T, tot, sp, ns, offsets,
-                                                        perm, pair_i, pair_c, bucket_off);
+                                                        perm, pair_i, pair_c, bucket_off, ti);
     const size_t lds = sizeof(uint32_t) * (size_t)(FINE_WAVES + 1) << sp.shift;
     k_sort_fine<S, G><<<sp.nb, FINE_BLOCK, lds, st>>>(g, in, out, sp, offsets, perm, pair_i, pair_c,
-                                                    bucket_off);
+                                                    bucket_off, ti);
   }
   return hipGetLastError();
 }
 
-template hipError_t sort_launches<float, true>(const GridP&, const PartP<float>&, const PartP<float>&,
-                                               int64_t*, const int64_t*, char*, const WsLayout&,
-                                               uint32_t*, int64_t*, hipStream_t);
-template hipError_t sort_launches<float, false>(const GridP&, const PartP<float>&,
-                                                const PartP<float>&, int64_t*, const int64_t*, char*,
-                                                const WsLayout&, uint32_t*, int64_t*, hipStream_t);
-template hipError_t sort_launches<double, true>(const GridP&, const PartP<double>&,
-                                                const PartP<double>&, int64_t*, const int64_t*,
-                                                char*, const WsLayout&, uint32_t*, int64_t*,
-                                                hipStream_t);
-template hipError_t sort_launches<double, false>(const GridP&, const PartP<double>&,
-                                                 const PartP<double>&, int64_t*, const int64_t*,
-                                                 char*, const WsLayout&, uint32_t*, int64_t*,
-                                                 hipStream_t);
+#define USP_INST(S, G)                                                                            \
+  template hipError_t sort_launches<S, G>(const GridP&, const PartP<S>&, const PartP<S>&, int64_t*, \
+                                          const int64_t*, char*, const WsLayout&, uint32_t*,        \
+                                          int64_t*, hipStream_t, const TileIndex&)
+USP_INST(float, true);
+USP_INST(float, false);
+USP_INST(double, true);
+USP_INST(double, false);
+#undef USP_INST
 
 }  // namespace usp

@@ -319,13 +319,14 @@ hipError_t launch_update(const GridP& g, const GasP& gas, const BcP& bc, double 
                          const double* cs, const int64_t* offsets, const PartP<S>& p,
                          uint64_t seed, uint64_t step, char* ws, const WsLayout& L,
                          int64_t* counters, hipStream_t st, const PartP<S>* src,
-                         const uint32_t* gather_perm, hipEvent_t ev_begin, hipEvent_t ev_end) {
+                         const uint32_t* gather_perm, hipEvent_t ev_begin, hipEvent_t ev_end,
+                         bool tiles_done) {
   // the launch covers a full state; the window itself comes from the
   // binned count on the device
   const int64_t T = update_tile(UpdCfg<S>::STAGE, p.capacity, g.M);
-  const int64_t ntiles = cdiv(p.capacity, T);
+  const int64_t ntiles = update_ntiles(UpdCfg<S>::STAGE, p.capacity, g.M);
   int32_t* first = (int32_t*)(ws + L.tiles);
-  if (launch_tiles(offsets, g.M, T, ntiles, first, st, UpdCfg<S>::STAGE) != hipSuccess)
+  if (!tiles_done && launch_tiles(offsets, g.M, T, ntiles, first, st, UpdCfg<S>::STAGE) != hipSuccess)
     return hipGetLastError();
   const uint32_t s32 = (uint32_t)step;
   const int adv = g.dim != 0 ? 1 : 0;
@@ -355,11 +356,11 @@ template hipError_t launch_update<float>(const GridP&, const GasP&, const BcP&, 
                                          const double*, const int64_t*, const PartP<float>&,
                                          uint64_t, uint64_t, char*, const WsLayout&, int64_t*,
                                          hipStream_t, const PartP<float>*, const uint32_t*,
-                                         hipEvent_t, hipEvent_t);
+                                         hipEvent_t, hipEvent_t, bool);
 template hipError_t launch_update<double>(const GridP&, const GasP&, const BcP&, double,
                                           const double*, const int64_t*, const PartP<double>&,
                                           uint64_t, uint64_t, char*, const WsLayout&, int64_t*,
                                           hipStream_t, const PartP<double>*, const uint32_t*,
-                                          hipEvent_t, hipEvent_t);
+                                          hipEvent_t, hipEvent_t, bool);
 
 }  // namespace usp
