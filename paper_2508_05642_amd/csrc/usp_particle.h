@@ -977,19 +977,20 @@ __device__ __forceinline__ void cons_apply(const ConsScalars& r, int64_t j, PS* 
   }
 }
 
-// Conservation of one cell by one wave (Sec. IV.C).  The cell's particles
-// are [o0, o1); their post-collision values sit at vx[i - base] etc.
-// (LDS or global).  The vibrational picks run on `lv`, the cell's levels
-// (LDS or global); if `copy` is set, vx's levels are first copied to lv and
-// copied back after the picks.
-template <typename S, typename PS>
-__device__ __forceinline__ void conserve_cell(const GasP& gas, const ConsIn& in, int64_t c,
-                                              int64_t o0, int64_t o1, PS* vcx, PS* vcy, PS* vcz,
-                                              PS* verot, uint8_t* vvib, int64_t base, uint8_t* lv,
-                                              bool copy, uint64_t seed, uint32_t step,
-                                              int64_t* counters) {
+// Conservation of one cell by one wave (Sec. IV.C), less its scalings.  The
+// cell's particles are [o0, o1); their post-collision values sit at vx[i -
+// base] etc. (LDS or global).  The vibrational picks run on `lv`, the cell's
+// levels (LDS or global); if `copy` is set, vx's levels are first copied to
+// lv.
+template <typename PS>
+__device__ __forceinline__ ConsScalars conserve_scalars(const GasP& gas, const ConsIn& in, int64_t c,
+                                                        int64_t o0, int64_t o1, const PS* vcx,
+                                                        const PS* vcy, const PS* vcz,
+                                                        const PS* verot, const uint8_t* vvib,
+                                                        int64_t base, uint8_t* lv, bool copy,
+                                                        uint64_t seed, uint32_t step,
+                                                        int64_t* counters) {
   const int lane = threadIdx.x & 63;
-  const int64_t N = o1 - o0;
   double s[6] = {0, 0, 0, 0, 0, 0};
   int lmax = 0;
   cons_sums<PS>(in.Un, o0 + lane, o1, 64, vcx, vcy, vcz, verot, vvib, base, lv, o0, copy, s,
@@ -997,7 +998,20 @@ __device__ __forceinline__ void conserve_cell(const GasP& gas, const ConsIn& in,
 #pragma unroll
   for (int k = 0; k < 6; ++k) s[k] = wave_sum(s[k]);
   wave_sync_lds();
-  const ConsScalars r = cons_scalars(gas, in, c, N, s, lmax, lv, seed, step, counters);
+  return cons_scalars(gas, in, c, o1 - o0, s, lmax, lv, seed, step, counters);
+}
+
+// The whole conservation of one cell by one wave; with `copy` the levels are
+// copied back from lv after the picks.
+template <typename S, typename PS>
+__device__ __forceinline__ void conserve_cell(const GasP& gas, const ConsIn& in, int64_t c,
+                                              int64_t o0, int64_t o1, PS* vcx, PS* vcy, PS* vcz,
+                                              PS* verot, uint8_t* vvib, int64_t base, uint8_t* lv,
+                                              bool copy, uint64_t seed, uint32_t step,
+                                              int64_t* counters) {
+  const int lane = threadIdx.x & 63;
+  const ConsScalars r = conserve_scalars<PS>(gas, in, c, o0, o1, vcx, vcy, vcz, verot, vvib, base,
+                                             lv, copy, seed, step, counters);
   wave_sync_lds();
   for (int64_t i = o0 + lane; i < o1; i += 64) {
     const int64_t j = i - base;

@@ -67,7 +67,11 @@ __global__ __launch_bounds__(256) void k_tiles_small(const int64_t* __restrict__
 // The fused kernel's workgroup: 8 waves, two workgroups per CU (their LDS
 // stages fill it), 4 waves per SIMD.
 constexpr int KU_BLOCK = 512;
-constexpr int KU_WAVES = KU_BLOCK / 64;
+// On a grid of at most KU_WIDE_CELLS cells, each larger than that workgroup,
+// a tile is one cell and has a CU to itself: 16 waves, a workgroup per cell
+// (no tile index).  200 cells of 1000 particles, FP32: 30.5 -> 25 us.
+constexpr int KU_WIDE = 1024;
+constexpr int64_t KU_WIDE_CELLS = 256;
 
 // Positions, ids and new cells of a gathered tile's slots, in LDS next to
 // the stage (slot i at i - base): the update and the flight read them there
@@ -95,17 +99,17 @@ struct PosStage {
 // flight at once.
 constexpr int GATHER_U = 4;
 
-template <typename S, bool POS>
+template <typename S, bool POS, int BLOCK>
 __device__ __forceinline__ void tile_gather(const GridP& g, const PartP<S>& src,
                                             const uint32_t* __restrict__ perm, const PartP<S>& p,
                                             int64_t i0, int64_t i1, const Stage<S>& st,
                                             const PosStage<S>& ps) {
-  for (int64_t b = i0 + threadIdx.x; b < i1; b += GATHER_U * KU_BLOCK) {
+  for (int64_t b = i0 + threadIdx.x; b < i1; b += GATHER_U * BLOCK) {
     uint32_t j[GATHER_U];
     int32_t cl[GATHER_U];
 #pragma unroll
     for (int k = 0; k < GATHER_U; ++k) {
-      const int64_t i = b + k * KU_BLOCK;
+      const int64_t i = b + k * BLOCK;
       j[k] = i < i1 ? perm[i] : 0u;
       if (POS) cl[k] = i < i1 ? p.cell[i] : 0;
     }
@@ -143,7 +147,7 @@ __device__ __forceinline__ void tile_gather(const GridP& g, const PartP<S>& src,
     for (int k = 0; k < GATHER_U; ++k) id[k] = src.pid[j[k]];
 #pragma unroll
     for (int k = 0; k < GATHER_U; ++k) {
-      const int64_t i = b + k * KU_BLOCK;
+      const int64_t i = b + k * BLOCK;
       if (i < i1) {
         st.store(i, v[k]);
         if (POS) {
@@ -168,24 +172,30 @@ __device__ __forceinline__ void tile_gather(const GridP& g, const PartP<S>& src,
 //      the FP32 first pass lists get the FP64 second pass);
 //   B  conservation, wave per cell, on the stage;
 //   C  free flight, thread per particle, writing the state once.
-template <typename S, bool STAGED, int CAP, int MODE, bool G, bool POS>
+// A tile of one cell (BLOCK = KU_WIDE, staged) keeps the conservation's
+// scalars in *cons and applies the scalings in C, to each particle as it is
+// taken up: a pass of one wave over its cell would leave the others idle
+// (200 cells of 1000: 13.5 -> 7.7 thousand cycles for B).  In the many-cell
+// kernel the pass in place is even, and reading scalars back cost 0.6 to 2%.
+template <typename S, bool STAGED, int CAP, int MODE, bool G, bool POS, int BLOCK>
 __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const BcP& bc,
                                           double dt, const double* __restrict__ cs,
                                           const int64_t* __restrict__ offsets, const PartP<S>& p,
                                           int64_t c0, int64_t c1, int64_t i0, int64_t i1,
                                           const Stage<S>& st, const PosStage<S>& ps,
-                                          uint16_t* esc_list, int* nesc, uint64_t seed,
-                                          uint32_t step, bool advect, int64_t* counters,
-                                          WgCounters wc) {
+                                          ConsScalars* cons, uint16_t* esc_list, int* nesc,
+                                          uint64_t seed, uint32_t step, bool advect,
+                                          int64_t* counters, WgCounters wc) {
   // A: inputs from the stage the gather filled, or from the arrays of p
   // (in place when the tile is past the stage)
   constexpr bool SAME = !STAGED || G;
+  constexpr bool SOLO = STAGED && BLOCK == KU_WIDE;
   const Stage<S> src = (G && STAGED) ? st : global_stage(p);
   for (int64_t cb = i0; cb < i1; cb += CAP) {
     const int64_t ce = cb + CAP < i1 ? cb + CAP : i1;
     if (threadIdx.x == 0) *nesc = 0;
     __syncthreads();
-    for (int64_t i = cb + threadIdx.x; i < ce; i += KU_BLOCK) {
+    for (int64_t i = cb + threadIdx.x; i < ce; i += BLOCK) {
       const int32_t c = POS ? ps.cell[i - ps.base] : p.cell[i];
       const PartNew<S> in = src.load(i);
       uint32_t ev = 0;
@@ -209,7 +219,7 @@ __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const
     }
     __syncthreads();
     const int ne = *nesc;
-    for (int k = threadIdx.x; k < ne; k += KU_BLOCK) {
+    for (int k = threadIdx.x; k < ne; k += BLOCK) {
       const int64_t i = cb + esc_list[k];
       const PartNew<S> in = src.load(i);
       uint32_t ev = 0;
@@ -226,18 +236,30 @@ __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const
   // the wave's index, made wave-uniform so that the per-cell work of the
   // conservation (loads, draws, integer arithmetic) runs on the scalar unit
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int64_t c = c0 + wid; c < c1; c += KU_WAVES) {
+  for (int64_t c = c0 + wid; c < c1; c += BLOCK / 64) {
     const int64_t o0 = offsets[c], o1 = offsets[c + 1];
     const ConsIn in = cons_in(cs, g.M, c, step, seed);
-    if (o1 == o0 || !in.collide) continue;
-    conserve_cell<S, S>(gas, in, c, o0, o1, st.cx, st.cy, st.cz, st.erot, st.vib, st.base,
-                        st.vib + (o0 - st.base), false, seed, step, counters);
+    if constexpr (SOLO) {
+      ConsScalars r;
+      r.frot = 0.0; r.sc = 0.0;
+      if (o1 != o0 && in.collide)
+        r = conserve_scalars<S>(gas, in, c, o0, o1, st.cx, st.cy, st.cz, st.erot, st.vib, st.base,
+                                st.vib + (o0 - st.base), false, seed, step, counters);
+      if ((threadIdx.x & 63) == 0) *cons = r;
+    } else {
+      if (o1 == o0 || !in.collide) continue;
+      conserve_cell<S, S>(gas, in, c, o0, o1, st.cx, st.cy, st.cz, st.erot, st.vib, st.base,
+                          st.vib + (o0 - st.base), false, seed, step, counters);
+    }
   }
   __syncthreads();
   // C: free flight (1D and 2D), state written back once
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += KU_BLOCK) {
-    const PartNew<S> v = st.load(i);
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += BLOCK) {
+    PartNew<S> v = st.load(i);
     const int32_t c = POS ? ps.cell[i - ps.base] : p.cell[i];
+    if constexpr (SOLO) {
+      if (c >= 0) cons_apply<S, S>(*cons, 0, &v.cx, &v.cy, &v.cz, &v.erot);
+    }
     if (advect && c >= 0) {
       const PartPos<S> q = POS ? ps.load(i) : load_pos(p, i, g.dim);
       advect_one<S, POS>(g, gas, bc, dt, p, i, q, v.cx, v.cy, v.cz, v.erot, v.vib, seed, step,
@@ -254,8 +276,8 @@ __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const
   }
 }
 
-template <typename S, int MODE, bool G>
-__global__ __launch_bounds__(KU_BLOCK, 4) void k_update(GridP g, GasP gas, BcP bc, double dt,
+template <typename S, int MODE, bool G, int BLOCK>
+__global__ __launch_bounds__(BLOCK, 4) void k_update(GridP g, GasP gas, BcP bc, double dt,
                                                      const double* __restrict__ cs,
                                                      const int64_t* __restrict__ offsets,
                                                      const int32_t* __restrict__ first,
@@ -267,13 +289,14 @@ __global__ __launch_bounds__(KU_BLOCK, 4) void k_update(GridP g, GasP gas, BcP b
   __shared__ S scx[CAP], scy[CAP], scz[CAP], ser[CAP];
   __shared__ uint8_t svb[CAP];
   __shared__ uint16_t esc_list[CAP];
+  __shared__ ConsScalars cons;
   __shared__ S spx[PCAP], spy[PCAP];
   __shared__ uint32_t spid[PCAP];
   __shared__ int32_t scell[PCAP];
   __shared__ int nesc;
   __shared__ unsigned long long wcnt[USP_NCOUNTERS];
   const int64_t t = blockIdx.x;
-  const int64_t c0 = first[t], c1 = first[t + 1];
+  const int64_t c0 = BLOCK == KU_WIDE ? t : first[t], c1 = BLOCK == KU_WIDE ? t + 1 : first[t + 1];
   if (c0 >= c1) return;
   const int64_t i0 = offsets[c0], i1 = offsets[c1];
   wg_counters_init(wcnt);  // ordered before use by the first barrier of A
@@ -284,19 +307,19 @@ __global__ __launch_bounds__(KU_BLOCK, 4) void k_update(GridP g, GasP gas, BcP b
     Stage<S> st;
     st.cx = scx; st.cy = scy; st.cz = scz; st.erot = ser; st.vib = svb; st.base = i0;
     if constexpr (G) {
-      tile_gather<S, true>(g, src, perm, p, i0, i1, st, ps);
-      tile_pass<S, true, CAP, MODE, G, true>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st, ps,
-                                            esc_list, &nesc, seed, step, advect != 0, counters,
+      tile_gather<S, true, BLOCK>(g, src, perm, p, i0, i1, st, ps);
+      tile_pass<S, true, CAP, MODE, G, true, BLOCK>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st, ps,
+                                            &cons, esc_list, &nesc, seed, step, advect != 0, counters,
                                             wc);
     } else {
-      tile_pass<S, true, CAP, MODE, G, false>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st,
-                                             ps, esc_list, &nesc, seed, step, advect != 0,
+      tile_pass<S, true, CAP, MODE, G, false, BLOCK>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st,
+                                             ps, &cons, esc_list, &nesc, seed, step, advect != 0,
                                              counters, wc);
     }
   } else {
-    if constexpr (G) tile_gather<S, false>(g, src, perm, p, i0, i1, global_stage(p), ps);
-    tile_pass<S, false, CAP, MODE, G, false>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1,
-                                            global_stage(p), ps, esc_list, &nesc, seed, step,
+    if constexpr (G) tile_gather<S, false, BLOCK>(g, src, perm, p, i0, i1, global_stage(p), ps);
+    tile_pass<S, false, CAP, MODE, G, false, BLOCK>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1,
+                                            global_stage(p), ps, &cons, esc_list, &nesc, seed, step,
                                             advect != 0, counters, wc);
   }
   __syncthreads();
@@ -326,24 +349,31 @@ hipError_t launch_update(const GridP& g, const GasP& gas, const BcP& bc, double 
   const int64_t T = update_tile(UpdCfg<S>::STAGE, p.capacity, g.M);
   const int64_t ntiles = update_ntiles(UpdCfg<S>::STAGE, p.capacity, g.M);
   int32_t* first = (int32_t*)(ws + L.tiles);
-  if (!tiles_done && launch_tiles(offsets, g.M, T, ntiles, first, st, UpdCfg<S>::STAGE) != hipSuccess)
+  const bool wide = g.M <= KU_WIDE_CELLS && p.capacity > KU_BLOCK * g.M;
+  if (!tiles_done && !wide && launch_tiles(offsets, g.M, T, ntiles, first, st, UpdCfg<S>::STAGE) != hipSuccess)
     return hipGetLastError();
   const uint32_t s32 = (uint32_t)step;
   const int adv = g.dim != 0 ? 1 : 0;
   const int mode = update_mode(gas);
   const PartP<S> sp = src ? *src : p;
   if (ev_begin && hipEventRecord(ev_begin, st) != hipSuccess) return hipGetLastError();
-#define USP_K_UPDATE(MODE, G, PERM)                                                             \
-  k_update<S, MODE, G><<<ntiles, KU_BLOCK, 0, st>>>(g, gas, bc, dt, cs, offsets, first, p, seed, \
-                                                   s32, adv, counters, sp, PERM)
+#define USP_K_UPDATE(MODE, G, PERM)                                                               \
+  if (wide)                                                                                       \
+    k_update<S, MODE, G, KU_WIDE><<<g.M, KU_WIDE, 0, st>>>(g, gas, bc, dt, cs, offsets, first, \
+                                                              p, seed, s32, adv, counters, sp,    \
+                                                              PERM);                              \
+  else                                                                                            \
+    k_update<S, MODE, G, KU_BLOCK><<<ntiles, KU_BLOCK, 0, st>>>(g, gas, bc, dt, cs, offsets,      \
+                                                                first, p, seed, s32, adv,         \
+                                                                counters, sp, PERM)
   if (gather_perm) {
-    if (mode == MODE_FPM) USP_K_UPDATE(MODE_FPM, true, gather_perm);
-    else if (mode == MODE_CELL) USP_K_UPDATE(MODE_CELL, true, gather_perm);
-    else USP_K_UPDATE(MODE_USP, true, gather_perm);
+    if (mode == MODE_FPM) { USP_K_UPDATE(MODE_FPM, true, gather_perm); }
+    else if (mode == MODE_CELL) { USP_K_UPDATE(MODE_CELL, true, gather_perm); }
+    else { USP_K_UPDATE(MODE_USP, true, gather_perm); }
   } else {
-    if (mode == MODE_FPM) USP_K_UPDATE(MODE_FPM, false, nullptr);
-    else if (mode == MODE_CELL) USP_K_UPDATE(MODE_CELL, false, nullptr);
-    else USP_K_UPDATE(MODE_USP, false, nullptr);
+    if (mode == MODE_FPM) { USP_K_UPDATE(MODE_FPM, false, nullptr); }
+    else if (mode == MODE_CELL) { USP_K_UPDATE(MODE_CELL, false, nullptr); }
+    else { USP_K_UPDATE(MODE_USP, false, nullptr); }
   }
 #undef USP_K_UPDATE
   hipError_t e = hipGetLastError();
