@@ -89,7 +89,7 @@ WsLayout ws_layout(int64_t M, int64_t capacity, int nfaces) {
   L.cons_scal = o; o = align256(o + CONS_SCALAR_BYTES * (size_t)M);
   // a smaller state of the same grid may have more (smaller) chunks
   const int64_t chunks = std::min(cdiv(capacity, SORT_CHUNK_MIN), SORT_CHUNKS);
-  L.sort_t = o; o = align256(o + sizeof(uint32_t) * (size_t)(chunks * std::min<int64_t>(M, SORT_BUCKETS)));
+  L.sort_t = o; o = align256(o + sizeof(uint32_t) * (size_t)(chunks * std::min<int64_t>((M + 3) / 4 * 4, SORT_BUCKETS)));
   L.sort_tot = o; o = align256(o + sizeof(uint32_t) * (size_t)(2 * SORT_BUCKETS + 1));
   L.total = o;
   return L;

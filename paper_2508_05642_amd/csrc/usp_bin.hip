@@ -104,7 +104,7 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_scan_down(const int32_t* counts, 
     const int64_t j = base + k;
     if (j < M) {
       offsets[j] = run;
-      if (ti.first) mark_tiles(ti, W, j, run, run + v[k]);
+      if (ti.first) mark_tiles(ti, (uint32_t)W, j, (uint32_t)run, (uint32_t)(run + v[k]));
     }
     run += v[k];
   }

@@ -76,12 +76,13 @@ __device__ __forceinline__ void place(const PartP<S>& in, const PartP<S>& out, u
 // Tile index entries that cell c, with the output segment [o, o1), decides:
 // the tiles whose window starts past the cell's first slot and not past
 // its end begin at the next cell (window W); cell 0 also opens tile 0.
-__device__ __forceinline__ void mark_tiles(const TileIndex& ti, int64_t W, int64_t c, int64_t o,
-                                           int64_t o1) {
+// (slots fit 32 bits, and a 32-bit division is a fifth of a 64-bit one)
+__device__ __forceinline__ void mark_tiles(const TileIndex& ti, uint32_t W, int64_t c, uint32_t o,
+                                           uint32_t o1) {
   if (c == 0) ti.first[0] = 0;
   int64_t hi = o1 / W;
   if (hi > ti.ntiles) hi = ti.ntiles;
-  for (int64_t t = o / W + 1; t <= hi; ++t) ti.first[t] = (int32_t)(c + 1);
+  for (int64_t t = (int64_t)(o / W) + 1; t <= hi; ++t) ti.first[t] = (int32_t)(c + 1);
 }
 
 // The tiles past the last particle begin at cell M (by `stride` threads).

@@ -161,7 +161,7 @@ constexpr int64_t SORT_CHUNKS = 1024;
 constexpr int64_t SORT_CHUNK_MIN = 2048;
 constexpr int64_t SORT_SELF_SCAN = 32768;
 struct SortPlan {
-  int shift, nb, bits, self_scan;
+  int shift, nb, ld, bits, self_scan;  // ld: row stride of the digit counts
   int64_t chunk, nchunks;
 };
 SortPlan sort_plan(int64_t M, int64_t capacity);

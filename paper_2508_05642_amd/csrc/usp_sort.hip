@@ -19,6 +19,7 @@ constexpr int SORT_BLOCK = 512;
 constexpr int SORT_WAVES = SORT_BLOCK / 64;
 constexpr int SORT_U = 4;  // 64-particle groups whose keys are loaded together
 constexpr int COUNT_U = 8;
+constexpr int SUM_U = 10;  // rows of counts a thread has in flight
 
 // Key of input slot i: the cell it holds on entry for the binned prefix
 // (i < ns), else from its position; -1 for a removed particle.
@@ -34,6 +35,11 @@ __device__ __forceinline__ int32_t sort_key(const GridP& g, const PartP<S>& in, 
     *solid = true;
   }
   return c;
+}
+
+// Chunks that n particles fill (n and the chunk fit 32 bits).
+__device__ __forceinline__ int chunks_used(int64_t n, const SortPlan& sp) {
+  return n > 0 ? (int)((uint32_t)(n - 1) / (uint32_t)sp.chunk) + 1 : 0;
 }
 
 // Adds the wave's digits (d < 0: none) to an LDS histogram, one atomic per
@@ -132,7 +138,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort_count(GridP g, PartP<S> in,
                                                            uint32_t* T, SortPlan sp, int64_t* ns_out,
                                                            int64_t* counters) {
   __shared__ uint32_t hist[SORT_BUCKETS];
-  for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) hist[d] = 0u;
+  for (int d = threadIdx.x; d < sp.ld; d += SORT_BLOCK) hist[d] = 0u;
   __syncthreads();
   const int64_t n = in.count[0];
   const int64_t ns = old_off ? sorted_len(old_off, g.M, in.count) : 0;
@@ -158,7 +164,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort_count(GridP g, PartP<S> in,
     for (int u = 0; u < COUNT_U; ++u) count_digits(hist, c[u] < 0 ? -1 : c[u] >> sp.shift);
   }
   __syncthreads();
-  for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) T[(int64_t)blockIdx.x * sp.nb + d] = hist[d];
+  for (int d = threadIdx.x; d < sp.ld; d += SORT_BLOCK) T[(int64_t)blockIdx.x * sp.ld + d] = hist[d];
 }
 
 // Column scan of T (rows = chunks in use): every entry becomes the digit's
@@ -169,7 +175,7 @@ __global__ __launch_bounds__(SCAN_COLS* SCAN_GROUPS) void k_sort_scan(uint32_t* 
                                                                       SortPlan sp,
                                                                       const int64_t* in_count) {
   __shared__ uint32_t part[SCAN_GROUPS][SCAN_COLS + 1];
-  const int nk = (int)((in_count[0] + sp.chunk - 1) / sp.chunk);
+  const int nk = chunks_used(in_count[0], sp);
   const int col = threadIdx.x & (SCAN_COLS - 1), rg = threadIdx.x / SCAN_COLS;
   const int d = blockIdx.x * SCAN_COLS + col;
   const int per = (nk + SCAN_GROUPS - 1) / SCAN_GROUPS;
@@ -177,7 +183,7 @@ __global__ __launch_bounds__(SCAN_COLS* SCAN_GROUPS) void k_sort_scan(uint32_t* 
   uint32_t s = 0;
   if (d < sp.nb) {
 #pragma unroll 8
-    for (int k = k0; k < k1; ++k) s += T[(int64_t)k * sp.nb + d];
+    for (int k = k0; k < k1; ++k) s += T[(int64_t)k * sp.ld + d];
   }
   part[rg][col] = s;
   __syncthreads();
@@ -187,8 +193,8 @@ __global__ __launch_bounds__(SCAN_COLS* SCAN_GROUPS) void k_sort_scan(uint32_t* 
   if (rg == SCAN_GROUPS - 1) tot[d] = run + s;
 #pragma unroll 8
   for (int k = k0; k < k1; ++k) {
-    const uint32_t v = T[(int64_t)k * sp.nb + d];
-    T[(int64_t)k * sp.nb + d] = run;
+    const uint32_t v = T[(int64_t)k * sp.ld + d];
+    T[(int64_t)k * sp.ld + d] = run;
     run += v;
   }
 }
@@ -222,15 +228,17 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort_place(GridP g, PartP<S> in,
                                                            int32_t* pair_i, int32_t* pair_c,
                                                            uint32_t* bucket_off, TileIndex ti) {
   __shared__ uint32_t start[SORT_BUCKETS];
-  __shared__ uint32_t whist[SORT_WAVES][SORT_BUCKETS];
+  alignas(16) __shared__ uint32_t whist[SORT_WAVES][SORT_BUCKETS];
   const int64_t n = in.count[0], ns = *ns_in;
+  // the last workgroup has no chunk: it writes the offsets (and the tile
+  // index), so that no placing one does both
+  const bool index = blockIdx.x == gridDim.x - 1;
   const int64_t i0 = (int64_t)blockIdx.x * sp.chunk;
-  if (i0 >= n && blockIdx.x != 0) return;
+  if (i0 >= n && !index) return;
   const int64_t i1 = i0 + sp.chunk < n ? i0 + sp.chunk : n;
-  const int nk = (int)((n + sp.chunk - 1) / sp.chunk);
+  const int nk = chunks_used(n, sp);
   const int blk = (int)blockIdx.x;
-  // column sums and the sums of the earlier chunks (threads of different
-  // row groups share a column when there are fewer digits than threads)
+  // column sums and the sums of the earlier chunks
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   // each wave owns a run of consecutive slots of the chunk; the keys of its
   // first SORT_U groups (all of them in the smallest chunk) are requested
@@ -254,34 +262,59 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort_place(GridP g, PartP<S> in,
   cells_at(w0, cf);
   uint32_t* before = whist[0];  // free until the waves count
   if (sp.self_scan) {
-    for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) { start[d] = 0u; before[d] = 0u; }
-    __syncthreads();
-    const int cols = sp.nb < SORT_BLOCK ? sp.nb : SORT_BLOCK, groups = SORT_BLOCK / cols;
-    const int rg = threadIdx.x / cols, d0 = threadIdx.x - rg * cols;
+    // four columns a load, the row groups' loads all in flight at once;
+    // the groups' sums meet in LDS
+    const int quads = sp.ld / 4, most = SORT_BLOCK / quads, groups = nk < most ? nk : most;
+    const int rg = threadIdx.x / quads, q = threadIdx.x - rg * quads;
+    uint4* part = (uint4*)&whist[0][0];  // [group][all, pre][quads]
     if (rg < groups) {
-      const int per = (nk + groups - 1) / groups;
-      const int k0 = rg * per, k1 = k0 + per < nk ? k0 + per : nk;
-      for (int d = d0; d < sp.nb; d += cols) {
-        uint32_t all = 0, pre = 0;
-#pragma unroll 8
-        for (int k = k0; k < k1; ++k) {
-          const uint32_t v = T[(int64_t)k * sp.nb + d];
-          all += v;
-          pre += k < blk ? v : 0u;
+      uint4 all = {0, 0, 0, 0}, pre = {0, 0, 0, 0};
+      const uint4* col = (const uint4*)T + q;
+      for (int k = rg; k < nk; k += SUM_U * groups) {
+        uint4 v[SUM_U];
+#pragma unroll
+        for (int u = 0; u < SUM_U; ++u) {
+          const int r = k + u * groups;
+          v[u] = col[(int64_t)(r < nk ? r : k) * quads];
         }
-        if (all) atomicAdd(&start[d], all);
-        if (pre) atomicAdd(&before[d], pre);
+#pragma unroll
+        for (int u = 0; u < SUM_U; ++u) {
+          const int r = k + u * groups;
+          const uint32_t m = r < nk ? ~0u : 0u, b = r < blk ? m : 0u;
+          all.x += v[u].x & m; all.y += v[u].y & m; all.z += v[u].z & m; all.w += v[u].w & m;
+          pre.x += v[u].x & b; pre.y += v[u].y & b; pre.z += v[u].z & b; pre.w += v[u].w & b;
+        }
       }
+      part[(rg * 2) * quads + q] = all;
+      part[(rg * 2 + 1) * quads + q] = pre;
+    }
+    __syncthreads();
+    uint32_t all[SORT_BUCKETS / SORT_BLOCK] = {0}, pre[SORT_BUCKETS / SORT_BLOCK] = {0};
+    const uint32_t* flat = &whist[0][0];
+#pragma unroll
+    for (int u = 0; u < SORT_BUCKETS / SORT_BLOCK; ++u) {
+      const int d = threadIdx.x + u * SORT_BLOCK;
+      if (d < sp.nb)
+        for (int k = 0; k < groups; ++k) {
+          all[u] += flat[(k * 2) * sp.ld + d];
+          pre[u] += flat[(k * 2 + 1) * sp.ld + d];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < SORT_BUCKETS / SORT_BLOCK; ++u) {
+      const int d = threadIdx.x + u * SORT_BLOCK;
+      if (d < sp.nb) { start[d] = all[u]; before[d] = pre[u]; }
     }
   } else {
     for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) {
       start[d] = tot[d];
-      before[d] = i0 < n ? T[(int64_t)blk * sp.nb + d] : 0u;
+      before[d] = i0 < n ? T[(int64_t)blk * sp.ld + d] : 0u;
     }
   }
   __syncthreads();
   const uint32_t total = scan_lds(start, sp.nb);
-  if (blk == 0) {
+  if (index) {
     if (PAIRS) {
       for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) bucket_off[d] = start[d];
       if (threadIdx.x == 0) bucket_off[sp.nb] = total;
@@ -293,13 +326,13 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort_place(GridP g, PartP<S> in,
         out.count[1] = in.count[1];
       }
       if (ti.first) {
-        const int64_t W = update_tile(ti.stage, total, g.M);
+        const uint32_t W = (uint32_t)update_tile(ti.stage, total, g.M);
         for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK)
           mark_tiles(ti, W, d, start[d], d + 1 < sp.nb ? start[d + 1] : total);
         mark_last_tiles(ti, W, g.M, total, threadIdx.x, SORT_BLOCK);
       }
     }
-    __syncthreads();  // start changes below
+    return;
   }
   for (int d = threadIdx.x; d < sp.nb; d += SORT_BLOCK) start[d] += before[d];
   __syncthreads();
@@ -422,9 +455,10 @@ __global__ __launch_bounds__(FINE_BLOCK) void k_sort_fine(GridP g, PartP<S> in, 
   }
   __syncthreads();
   if (ti.first) {
-    const int64_t total = bucket_off[sp.nb], W = update_tile(ti.stage, total, g.M);
+    const int64_t total = bucket_off[sp.nb];
+    const uint32_t W = (uint32_t)update_tile(ti.stage, total, g.M);
     for (int d = threadIdx.x; d < nf; d += FINE_BLOCK)
-      mark_tiles(ti, W, c0 + d, start[d], d + 1 < nf ? start[d + 1] : s1);
+      mark_tiles(ti, W, c0 + d, start[d], d + 1 < nf ? start[d + 1] : (uint32_t)s1);
     if (blockIdx.x == gridDim.x - 1) mark_last_tiles(ti, W, g.M, total, threadIdx.x, FINE_BLOCK);
   }
   for (int d = threadIdx.x; d < nf; d += FINE_BLOCK) {
@@ -461,12 +495,13 @@ SortPlan sort_plan(int64_t M, int64_t capacity) {
   sp.shift = 0;
   while (cdiv(M, (int64_t)1 << sp.shift) > SORT_BUCKETS) ++sp.shift;
   sp.nb = (int)cdiv(M, (int64_t)1 << sp.shift);
+  sp.ld = (sp.nb + 3) / 4 * 4;
   sp.bits = 0;
   while ((1 << sp.bits) < sp.nb) ++sp.bits;
   const int64_t per = cdiv(cdiv(capacity, SORT_CHUNKS), SORT_BLOCK) * SORT_BLOCK;
   sp.chunk = per > SORT_CHUNK_MIN ? per : SORT_CHUNK_MIN;
   sp.nchunks = cdiv(capacity, sp.chunk);
-  sp.self_scan = sp.nchunks * sp.nb <= SORT_SELF_SCAN ? 1 : 0;
+  sp.self_scan = sp.nchunks * sp.ld <= SORT_SELF_SCAN ? 1 : 0;
   return sp;
 }
 
@@ -487,10 +522,10 @@ hipError_t sort_launches(const GridP& g, const PartP<S>& in, const PartP<S>& out
   if (!sp.self_scan)
     k_sort_scan<<<(int)cdiv(sp.nb, SCAN_COLS), SCAN_COLS * SCAN_GROUPS, 0, st>>>(T, tot, sp, in.count);
   if (sp.shift == 0) {
-    k_sort_place<S, G, false><<<nk, SORT_BLOCK, 0, st>>>(g, in, out, key, T, tot, sp, ns, offsets,
+    k_sort_place<S, G, false><<<nk + 1, SORT_BLOCK, 0, st>>>(g, in, out, key, T, tot, sp, ns, offsets,
                                                          perm, nullptr, nullptr, nullptr, ti);
   } else {
-    k_sort_place<S, G, true><<<nk, SORT_BLOCK, 0, st>>>(g, in, out, key, T, tot, sp, ns, offsets,
+    k_sort_place<S, G, true><<<nk + 1, SORT_BLOCK, 0, st>>>(g, in, out, key, T, tot, sp, ns, offsets,
                                                         perm, pair_i, pair_c, bucket_off, ti);
     const size_t lds = sizeof(uint32_t) * (size_t)(FINE_WAVES + 1) << sp.shift;
     k_sort_fine<S, G><<<sp.nb, FINE_BLOCK, lds, st>>>(g, in, out, sp, offsets, perm, pair_i, pair_c,
