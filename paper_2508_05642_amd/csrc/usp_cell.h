@@ -230,6 +230,38 @@ __device__ __forceinline__ void cell_state(const GridP& g, const GasP& gas, cons
   }
 }
 
+// Quadrant stencils of the reconstruction (Sec. III.B), one thread per
+// cell, after the cell state: quadrant q = (x >= x_i) + 2 (y >= y_j) keeps
+// the x neighbour direction tx and y direction ty (toward the quadrant,
+// else the opposite side, else none) and whether the diagonal cell
+// completes the cross term.  Field: 2 bits tx (1: +1, 2: -1), 2 bits ty,
+// 1 bit cross, 5 bits per quadrant.
+__device__ __forceinline__ void stencil_cell(const GridP& g, double* cs, int64_t c) {
+  const int64_t M = g.M;
+  const int nx = g.nx;
+  const int ci = g.dim == 2 ? (int)(c % nx) : 0;
+  const int cj = g.dim == 2 ? (int)(c / nx) : (int)c;
+  auto ok = [&](int ii, int jj) -> bool {
+    if (ii < 0 || jj < 0 || ii >= g.nx || jj >= g.ny) return false;
+    return cs[CS_NBR_OK * M + (int64_t)jj * nx + ii] != 0.0;
+  };
+  int32_t bits = 0;
+  for (int q = 0; q < 4; ++q) {
+    const int sx = (q & 1) ? 1 : -1, sy = (q & 2) ? 1 : -1;
+    int ty = 0, tx = 0;
+    if (ok(ci, cj + sy)) ty = sy;
+    else if (ok(ci, cj - sy)) ty = -sy;
+    if (g.dim == 2) {
+      if (ok(ci + sx, cj)) tx = sx;
+      else if (ok(ci - sx, cj)) tx = -sx;
+    }
+    const int cross = (tx && ty && ok(ci + tx, cj + ty)) ? 1 : 0;
+    const int f = (tx == 1 ? 1 : tx == -1 ? 2 : 0) | ((ty == 1 ? 1 : ty == -1 ? 2 : 0) << 2) | (cross << 4);
+    bits |= f << (5 * q);
+  }
+  cell_records(cs, M)[c].stencil = bits;
+}
+
 // The FP64 planes of cell c and its packed record (stencil word 0; the
 // stencil pass fills it in 1D and 2D).
 __device__ __forceinline__ void store_cell_state(double* cs, int64_t M, int64_t c,

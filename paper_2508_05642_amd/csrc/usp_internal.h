@@ -213,11 +213,13 @@ hipError_t launch_cell_coef(const GridP& g, const GasP& gas, double* cs, hipStre
 hipError_t launch_reconstruct(const GridP& g, const GasP& gas, const double* mom, double dt,
                               const double* dt_cell, double* cs, int64_t* counters, hipStream_t st);
 // launch_moments followed by launch_reconstruct, in fewer launches on grids
-// of few cells.
+// of few cells.  Without `stencils` (grids that update_solo takes) the
+// stencil words are left to the particle phase.
 template <typename S>
 hipError_t launch_cells(const GridP& g, const GasP& gas, const PartP<S>& p, const int64_t* offsets,
                         double* mom, double dt, const double* dt_cell, double* cs,
-                        int64_t* counters, hipStream_t st, const uint32_t* gather_perm = nullptr);
+                        int64_t* counters, hipStream_t st, const uint32_t* gather_perm = nullptr,
+                        bool stencils = true);
 hipError_t launch_sample_fields(const GridP& g, const double* mom, double* acc, hipStream_t st);
 template <typename S>
 hipError_t launch_collide(const GridP& g, const GasP& gas, const double* cs, const int64_t* offsets,
@@ -258,7 +260,11 @@ template <typename S>
 hipError_t launch_inject(const GridP& g, const GasP& gas, const BcP& bc, double dt,
                          const PartP<S>& p, uint64_t seed, uint64_t step, char* ws,
                          const WsLayout& L, int64_t* counters, hipStream_t st);
-// The fused particle phase on p (binned), or, with gather_perm, on the
+// Grids whose particle phase takes one cell a workgroup (at most one on a
+// CU).
+inline bool update_solo(const GridP& g) { return g.M <= 256; }
+// The fused particle phase (in_step: the tile index is made already, and on
+// update_solo grids the stencils are not) on p (binned), or, with gather_perm, on the
 // particles of `src` in the order gather_perm gives (slot j holds
 // src[gather_perm[j]]), the results written to p (whose cells the
 // gathering bin has set).
@@ -268,7 +274,7 @@ hipError_t launch_update(const GridP& g, const GasP& gas, const BcP& bc, double 
                          uint64_t seed, uint64_t step, char* ws, const WsLayout& L,
                          int64_t* counters, hipStream_t st, const PartP<S>* src = nullptr,
                          const uint32_t* gather_perm = nullptr, hipEvent_t ev_begin = nullptr,
-                         hipEvent_t ev_end = nullptr, bool tiles_done = false);
+                         hipEvent_t ev_end = nullptr, bool in_step = false);
 // Adds to *found the number of NaN or infinite values among the live
 // particles' floating arrays and, when given, the moment and FP64
 // cell-state planes of the occupied cells.

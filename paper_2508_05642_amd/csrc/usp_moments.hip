@@ -135,38 +135,6 @@ __global__ void k_reconstruct(GridP g, GasP gas, const double* mom, double dt,
   if (c < g.M) reconstruct_cell(g, gas, mom, dt, dt_cell, cs, counters, c);
 }
 
-// Quadrant stencils of the reconstruction (Sec. III.B), one thread per
-// cell, after the cell state: quadrant q = (x >= x_i) + 2 (y >= y_j) keeps
-// the x neighbour direction tx and y direction ty (toward the quadrant,
-// else the opposite side, else none) and whether the diagonal cell
-// completes the cross term.  Field: 2 bits tx (1: +1, 2: -1), 2 bits ty,
-// 1 bit cross, 5 bits per quadrant.
-__device__ __forceinline__ void stencil_cell(const GridP& g, double* cs, int64_t c) {
-  const int64_t M = g.M;
-  const int nx = g.nx;
-  const int ci = g.dim == 2 ? (int)(c % nx) : 0;
-  const int cj = g.dim == 2 ? (int)(c / nx) : (int)c;
-  auto ok = [&](int ii, int jj) -> bool {
-    if (ii < 0 || jj < 0 || ii >= g.nx || jj >= g.ny) return false;
-    return cs[CS_NBR_OK * M + (int64_t)jj * nx + ii] != 0.0;
-  };
-  int32_t bits = 0;
-  for (int q = 0; q < 4; ++q) {
-    const int sx = (q & 1) ? 1 : -1, sy = (q & 2) ? 1 : -1;
-    int ty = 0, tx = 0;
-    if (ok(ci, cj + sy)) ty = sy;
-    else if (ok(ci, cj - sy)) ty = -sy;
-    if (g.dim == 2) {
-      if (ok(ci + sx, cj)) tx = sx;
-      else if (ok(ci - sx, cj)) tx = -sx;
-    }
-    const int cross = (tx && ty && ok(ci + tx, cj + ty)) ? 1 : 0;
-    const int f = (tx == 1 ? 1 : tx == -1 ? 2 : 0) | ((ty == 1 ? 1 : ty == -1 ? 2 : 0) << 2) | (cross << 4);
-    bits |= f << (5 * q);
-  }
-  cell_records(cs, M)[c].stencil = bits;
-}
-
 __global__ void k_stencil(GridP g, double* cs) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c < g.M && g.dim != 0) stencil_cell(g, cs, c);
@@ -274,7 +242,8 @@ hipError_t launch_reconstruct(const GridP& g, const GasP& gas, const double* mom
 template <typename S>
 hipError_t launch_cells(const GridP& g, const GasP& gas, const PartP<S>& p, const int64_t* offsets,
                         double* mom, double dt, const double* dt_cell, double* cs,
-                        int64_t* counters, hipStream_t st, const uint32_t* gather_perm) {
+                        int64_t* counters, hipStream_t st, const uint32_t* gather_perm,
+                        bool stencils) {
   const int waves = moment_waves(g);
   if (!waves) {
     const hipError_t e = launch_moments<S>(g, p, offsets, mom, st, gather_perm);
@@ -282,15 +251,16 @@ hipError_t launch_cells(const GridP& g, const GasP& gas, const PartP<S>& p, cons
   }
   const hipError_t e = (waves == 4 ? moments_wide<S, 4> : moments_wide<S, 1>)(
       g, gas, p, offsets, mom, dt, dt_cell, cs, counters, st, gather_perm, 1);
-  return e != hipSuccess ? e : launch_stencil(g, gas, cs, st);
+  if (e != hipSuccess) return e;
+  return stencils ? launch_stencil(g, gas, cs, st) : launch_cell_coef(g, gas, cs, st);
 }
 
 template hipError_t launch_cells<float>(const GridP&, const GasP&, const PartP<float>&,
                                         const int64_t*, double*, double, const double*, double*,
-                                        int64_t*, hipStream_t, const uint32_t*);
+                                        int64_t*, hipStream_t, const uint32_t*, bool);
 template hipError_t launch_cells<double>(const GridP&, const GasP&, const PartP<double>&,
                                          const int64_t*, double*, double, const double*, double*,
-                                         int64_t*, hipStream_t, const uint32_t*);
+                                         int64_t*, hipStream_t, const uint32_t*, bool);
 template hipError_t launch_moments<float>(const GridP&, const PartP<float>&, const int64_t*,
                                           double*, hipStream_t, const uint32_t*);
 template hipError_t launch_moments<double>(const GridP&, const PartP<double>&, const int64_t*,

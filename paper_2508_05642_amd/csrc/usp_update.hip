@@ -67,11 +67,11 @@ __global__ __launch_bounds__(256) void k_tiles_small(const int64_t* __restrict__
 // The fused kernel's workgroup: 8 waves, two workgroups per CU (their LDS
 // stages fill it), 4 waves per SIMD.
 constexpr int KU_BLOCK = 512;
-// On a grid of at most KU_WIDE_CELLS cells, each larger than that workgroup,
-// a tile is one cell and has a CU to itself: 16 waves, a workgroup per cell
-// (no tile index).  200 cells of 1000 particles, FP32: 30.5 -> 25 us.
+// On a grid of at most 256 cells (update_solo) a tile is one cell and has a
+// CU to itself: a workgroup per cell (no tile index), of 16 waves where the
+// mean cell is larger than 8 of them.  200 cells of 1000 particles, FP32:
+// 30.5 -> 24.5 us.
 constexpr int KU_WIDE = 1024;
-constexpr int64_t KU_WIDE_CELLS = 256;
 
 // Positions, ids and new cells of a gathered tile's slots, in LDS next to
 // the stage (slot i at i - base): the update and the flight read them there
@@ -172,12 +172,13 @@ __device__ __forceinline__ void tile_gather(const GridP& g, const PartP<S>& src,
 //      the FP32 first pass lists get the FP64 second pass);
 //   B  conservation, wave per cell, on the stage;
 //   C  free flight, thread per particle, writing the state once.
-// A tile of one cell (BLOCK = KU_WIDE, staged) keeps the conservation's
+// A tile of one cell (ALONE, staged) keeps the conservation's
 // scalars in *cons and applies the scalings in C, to each particle as it is
 // taken up: a pass of one wave over its cell would leave the others idle
 // (200 cells of 1000: 13.5 -> 7.7 thousand cycles for B).  In the many-cell
 // kernel the pass in place is even, and reading scalars back cost 0.6 to 2%.
-template <typename S, bool STAGED, int CAP, int MODE, bool G, bool POS, int BLOCK>
+template <typename S, bool STAGED, int CAP, int MODE, bool G, bool POS, int BLOCK,
+          bool ALONE>
 __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const BcP& bc,
                                           double dt, const double* __restrict__ cs,
                                           const int64_t* __restrict__ offsets, const PartP<S>& p,
@@ -189,7 +190,7 @@ __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const
   // A: inputs from the stage the gather filled, or from the arrays of p
   // (in place when the tile is past the stage)
   constexpr bool SAME = !STAGED || G;
-  constexpr bool SOLO = STAGED && BLOCK == KU_WIDE;
+  constexpr bool SOLO = STAGED && ALONE;
   const Stage<S> src = (G && STAGED) ? st : global_stage(p);
   for (int64_t cb = i0; cb < i1; cb += CAP) {
     const int64_t ce = cb + CAP < i1 ? cb + CAP : i1;
@@ -276,14 +277,15 @@ __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const
   }
 }
 
-template <typename S, int MODE, bool G, int BLOCK>
+template <typename S, int MODE, bool G, int BLOCK, bool ALONE>
 __global__ __launch_bounds__(BLOCK, 4) void k_update(GridP g, GasP gas, BcP bc, double dt,
                                                      const double* __restrict__ cs,
                                                      const int64_t* __restrict__ offsets,
                                                      const int32_t* __restrict__ first,
                                                      PartP<S> p, uint64_t seed, uint32_t step,
                                                      int advect, int64_t* counters, PartP<S> src,
-                                                     const uint32_t* __restrict__ perm) {
+                                                     const uint32_t* __restrict__ perm,
+                                                     double* stencils) {
   constexpr int CAP = UpdCfg<S>::STAGE;
   constexpr int PCAP = G ? CAP : 1;
   __shared__ S scx[CAP], scy[CAP], scz[CAP], ser[CAP];
@@ -296,8 +298,13 @@ __global__ __launch_bounds__(BLOCK, 4) void k_update(GridP g, GasP gas, BcP bc, 
   __shared__ int nesc;
   __shared__ unsigned long long wcnt[USP_NCOUNTERS];
   const int64_t t = blockIdx.x;
-  const int64_t c0 = BLOCK == KU_WIDE ? t : first[t], c1 = BLOCK == KU_WIDE ? t + 1 : first[t + 1];
+  const int64_t c0 = ALONE ? t : first[t], c1 = ALONE ? t + 1 : first[t + 1];
   if (c0 >= c1) return;
+  if constexpr (ALONE) {
+    // the cell's stencil word, where the cell state came without (the only
+    // reader is this workgroup, past the first barrier of the gather or of A)
+    if (stencils && threadIdx.x == 0) stencil_cell(g, stencils, c0);
+  }
   const int64_t i0 = offsets[c0], i1 = offsets[c1];
   wg_counters_init(wcnt);  // ordered before use by the first barrier of A
   const WgCounters wc{counters ? wcnt : nullptr};
@@ -308,17 +315,17 @@ __global__ __launch_bounds__(BLOCK, 4) void k_update(GridP g, GasP gas, BcP bc, 
     st.cx = scx; st.cy = scy; st.cz = scz; st.erot = ser; st.vib = svb; st.base = i0;
     if constexpr (G) {
       tile_gather<S, true, BLOCK>(g, src, perm, p, i0, i1, st, ps);
-      tile_pass<S, true, CAP, MODE, G, true, BLOCK>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st, ps,
+      tile_pass<S, true, CAP, MODE, G, true, BLOCK, ALONE>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st, ps,
                                             &cons, esc_list, &nesc, seed, step, advect != 0, counters,
                                             wc);
     } else {
-      tile_pass<S, true, CAP, MODE, G, false, BLOCK>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st,
+      tile_pass<S, true, CAP, MODE, G, false, BLOCK, ALONE>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st,
                                              ps, &cons, esc_list, &nesc, seed, step, advect != 0,
                                              counters, wc);
     }
   } else {
     if constexpr (G) tile_gather<S, false, BLOCK>(g, src, perm, p, i0, i1, global_stage(p), ps);
-    tile_pass<S, false, CAP, MODE, G, false, BLOCK>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1,
+    tile_pass<S, false, CAP, MODE, G, false, BLOCK, ALONE>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1,
                                             global_stage(p), ps, &cons, esc_list, &nesc, seed, step,
                                             advect != 0, counters, wc);
   }
@@ -343,39 +350,43 @@ hipError_t launch_update(const GridP& g, const GasP& gas, const BcP& bc, double 
                          uint64_t seed, uint64_t step, char* ws, const WsLayout& L,
                          int64_t* counters, hipStream_t st, const PartP<S>* src,
                          const uint32_t* gather_perm, hipEvent_t ev_begin, hipEvent_t ev_end,
-                         bool tiles_done) {
+                         bool in_step) {
   // the launch covers a full state; the window itself comes from the
   // binned count on the device
   const int64_t T = update_tile(UpdCfg<S>::STAGE, p.capacity, g.M);
   const int64_t ntiles = update_ntiles(UpdCfg<S>::STAGE, p.capacity, g.M);
   int32_t* first = (int32_t*)(ws + L.tiles);
-  const bool wide = g.M <= KU_WIDE_CELLS && p.capacity > KU_BLOCK * g.M;
-  if (!tiles_done && !wide && launch_tiles(offsets, g.M, T, ntiles, first, st, UpdCfg<S>::STAGE) != hipSuccess)
+  const bool solo = update_solo(g), wide = p.capacity > KU_BLOCK * g.M;
+  // (the cell state is an input; its stencil words are finished in place)
+  double* stencils = in_step && solo && g.dim != 0 ? const_cast<double*>(cs) : nullptr;
+  if (!in_step && !solo && launch_tiles(offsets, g.M, T, ntiles, first, st, UpdCfg<S>::STAGE) != hipSuccess)
     return hipGetLastError();
   const uint32_t s32 = (uint32_t)step;
   const int adv = g.dim != 0 ? 1 : 0;
   const int mode = update_mode(gas);
   const PartP<S> sp = src ? *src : p;
   if (ev_begin && hipEventRecord(ev_begin, st) != hipSuccess) return hipGetLastError();
-#define USP_K_UPDATE(MODE, G, PERM)                                                               \
-  if (wide)                                                                                       \
-    k_update<S, MODE, G, KU_WIDE><<<g.M, KU_WIDE, 0, st>>>(g, gas, bc, dt, cs, offsets, first, \
-                                                              p, seed, s32, adv, counters, sp,    \
-                                                              PERM);                              \
-  else                                                                                            \
-    k_update<S, MODE, G, KU_BLOCK><<<ntiles, KU_BLOCK, 0, st>>>(g, gas, bc, dt, cs, offsets,      \
-                                                                first, p, seed, s32, adv,         \
-                                                                counters, sp, PERM)
+#define USP_K_LAUNCH(MODE, G, PERM, BLOCK, ALONE, NB)                                              \
+  k_update<S, MODE, G, BLOCK, ALONE><<<NB, BLOCK, 0, st>>>(g, gas, bc, dt, cs, offsets, first, p,  \
+                                                           seed, s32, adv, counters, sp, PERM,     \
+                                                           stencils)
+#define USP_K_UPDATE(MODE, G, PERM)                                                                \
+  do {                                                                                             \
+    if (solo && wide) USP_K_LAUNCH(MODE, G, PERM, KU_WIDE, true, g.M);                             \
+    else if (solo) USP_K_LAUNCH(MODE, G, PERM, KU_BLOCK, true, g.M);                               \
+    else USP_K_LAUNCH(MODE, G, PERM, KU_BLOCK, false, ntiles);                                     \
+  } while (0)
   if (gather_perm) {
-    if (mode == MODE_FPM) { USP_K_UPDATE(MODE_FPM, true, gather_perm); }
-    else if (mode == MODE_CELL) { USP_K_UPDATE(MODE_CELL, true, gather_perm); }
-    else { USP_K_UPDATE(MODE_USP, true, gather_perm); }
+    if (mode == MODE_FPM) USP_K_UPDATE(MODE_FPM, true, gather_perm);
+    else if (mode == MODE_CELL) USP_K_UPDATE(MODE_CELL, true, gather_perm);
+    else USP_K_UPDATE(MODE_USP, true, gather_perm);
   } else {
-    if (mode == MODE_FPM) { USP_K_UPDATE(MODE_FPM, false, nullptr); }
-    else if (mode == MODE_CELL) { USP_K_UPDATE(MODE_CELL, false, nullptr); }
-    else { USP_K_UPDATE(MODE_USP, false, nullptr); }
+    if (mode == MODE_FPM) USP_K_UPDATE(MODE_FPM, false, nullptr);
+    else if (mode == MODE_CELL) USP_K_UPDATE(MODE_CELL, false, nullptr);
+    else USP_K_UPDATE(MODE_USP, false, nullptr);
   }
 #undef USP_K_UPDATE
+#undef USP_K_LAUNCH
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && ev_end) e = hipEventRecord(ev_end, st);
   if (e != hipSuccess || g.dim == 0) return e;
