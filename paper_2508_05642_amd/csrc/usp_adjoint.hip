@@ -13,21 +13,18 @@
 // whose flight meets a boundary keeps its post-flight state as a
 // constant).  The random normals are the run's own draws.
 //
-// Forward: usp_step_taped runs one step with the separate phase kernels
-// (same bits as usp_step) and keeps a tape: the bin permutation, the binned
-// pre-collision state, the cell state, and the states after the collision
-// and after the conservation.  Reverse (usp_adjoint_step), per step:
-//   K1  wave per cell: flight and conservation reversed;
-//   K2  thread per particle: the particle update reversed (the scalar chain
-//       of the relaxation temperatures through Dual<6> Jacobians), giving
-//       adjoints of the particle and of the fields of its stencil cells;
-//   K3  a wave per (objective, field, cell) sums the stencil contributions
-//       in a fixed order; then a thread per cell reverses the cell state
-//       (Dual<6> Jacobian of its coefficients), giving adjoints of the
-//       moments and per-cell parameter partials;
-//   K4  thread per particle: moments reversed, mass-flow source, and the
-//       bin permutation undone;
-//   K5  one workgroup: parameter partials summed in a fixed order.
+// Forward: usp_step_taped runs one step with the kernels of usp_step and
+// keeps a tape: the bin permutation, the binned pre-collision state, the cell
+// state, and the states after the collision and after the conservation.  Reverse (usp_adjoint_step), per step:
+//   K1  flight and conservation reversed;
+//   K2  the particle update reversed (the scalar chain of the relaxation
+//       temperatures through Dual<6> Jacobians), giving adjoints of the
+//       particle and the cell's sums of those of the fields it reads;
+//   K3  the cell state reversed (Dual<6> Jacobian of its coefficients),
+//       giving adjoints of the moments and per-cell parameter partials; the
+//       moments reversed, mass-flow source, the bin permutation undone, and
+//       the parameter partials summed in a fixed order;
+// a workgroup per cell each, a thread per particle.
 // No floating-point atomics: the result is deterministic.
 #include "usp_dual.h"
 #include "usp_particle.h"
@@ -71,8 +68,15 @@ enum { AM_U = 0, AM_P = 3, AM_EROT = 9, NAMOM = 10 };
 enum { LY = 0, LCX = 1, LE = 4, NLAM = 5 };
 constexpr int NOBJ = 2, NPAR = 3;
 
+// per cell and objective: the cell's own sums (NOWN) and what its particles
+// add to the fields of the cells below and above (NNBR each)
+constexpr int NSUM = NOWN + 2 * NNBR;
+static_assert(NSUM <= 64, "a lane per sum");
+// workgroups that share a cell's particles in K2, each with its own sums
+constexpr int K2_PARTS = 2;
+
 struct AdjWsLayout {
-  size_t lam1, own, nbr, nbrc, cons, csum, lmom, gcell, map, total;
+  size_t lam1, cons, csum, gcell, done, total;
 };
 
 static AdjWsLayout adj_ws_layout(int64_t M, int64_t cap) {
@@ -80,14 +84,10 @@ static AdjWsLayout adj_ws_layout(int64_t M, int64_t cap) {
   size_t o = 0;
   auto take = [&](size_t bytes) { const size_t r = o; o = al256(o + bytes); return r; };
   w.lam1 = take((size_t)NOBJ * NLAM * cap * 8);
-  w.own = take((size_t)NOBJ * NOWN * cap * 8);
-  w.nbr = take((size_t)NOBJ * NNBR * cap * 8);
-  w.nbrc = take((size_t)cap * 4);
   w.cons = take((size_t)NOBJ * NCONS * M * 8);
-  w.csum = take((size_t)NOBJ * NOWN * M * 8);
-  w.lmom = take((size_t)NOBJ * NAMOM * M * 8);
+  w.csum = take((size_t)K2_PARTS * NOBJ * NSUM * M * 8);
   w.gcell = take((size_t)NOBJ * NPAR * M * 8);
-  w.map = take((size_t)cap * 4);
+  w.done = take(8);
   w.total = o;
   return w;
 }
@@ -139,28 +139,6 @@ __device__ __forceinline__ PartP<double> tape_parts(const TapeP& t, int64_t cap)
 }
 
 // ---- forward with tape ------------------------------------------------------
-__global__ void k_pid_map(const uint32_t* __restrict__ pid, const int64_t* __restrict__ count,
-                          int64_t cap, int32_t* __restrict__ map) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count[0]) return;
-  const uint32_t q = pid[i];
-  if ((int64_t)q < cap) map[q] = (int32_t)i;
-}
-
-__global__ void k_perm(const uint32_t* __restrict__ pid, const int64_t* __restrict__ count,
-                       int64_t cap, const int32_t* __restrict__ map, int32_t* __restrict__ perm) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= count[0]) return;
-  const uint32_t q = pid[j];
-  perm[j] = (int64_t)q < cap ? map[q] : -1;
-}
-
-// device-to-device copy on the stream; the first failure is kept in *e
-static void copy_d(void* dst, const void* src, size_t bytes, hipStream_t st, hipError_t* e) {
-  const hipError_t r = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, st);
-  if (*e == hipSuccess) *e = r;
-}
-
 // Several device-to-device copies in one launch (the tape copies of a
 // phase): blockIdx.y picks the copy; 8-byte words where both ends allow it,
 // bytes otherwise.
@@ -212,60 +190,39 @@ struct CopyBatch {
   }
 };
 
-// One full step of a 1D FP64 state through the separate phase kernels (the
-// bits of usp_step), keeping the tape.
+// One full step of a 1D FP64 state (the kernels of usp_step), keeping the
+// tape: the gathering bin records the permutation straight into it, the
+// particle phase writes the particle states as it passes them.
 static hipError_t step_taped(const GridP& g, const GasP& gas, const BcP& bc, double dt,
                              const PartP<double>& in, const PartP<double>& out, int64_t* offsets,
                              const int64_t* in_offsets, double* mom, double* cs, char* ws,
-                             const WsLayout& L, uint64_t seed,
-                             uint64_t step, char* tape, const TapeLayout& T, int32_t* map,
-                             int64_t* counters, hipStream_t st) {
-  const int64_t cap = out.capacity;
-  const int grid_p = (int)cdiv(cap, 256);
-  k_pid_map<<<grid_p, 256, 0, st>>>(in.pid, in.count, cap, map);
-  hipError_t e = launch_bin<double>(g, in, out, offsets, in_offsets, ws, L, counters, st);
+                             const WsLayout& L, uint64_t seed, uint64_t step, char* tape,
+                             const TapeLayout& T, int64_t* counters, hipStream_t st) {
+  uint32_t* perm = (uint32_t*)(tape + T.perm);
+  const TileIndex ti{(int32_t*)(ws + L.tiles),
+                     update_ntiles(UPDATE_STAGE_F64, out.capacity, g.M), UPDATE_STAGE_F64};
+  hipError_t e = launch_bin<double>(g, in, out, offsets, in_offsets, ws, L, counters, st, perm, ti);
   if (e != hipSuccess) return e;
-  k_perm<<<grid_p, 256, 0, st>>>(out.pid, out.count, cap, map, (int32_t*)(tape + T.perm));
-  hipError_t ce = hipSuccess;
-  const size_t d = (size_t)cap * 8;
-  CopyBatch cb;
-  cb.add(tape + T.y, out.y, d);
-  cb.add(tape + T.cx, out.cx, d);
-  cb.add(tape + T.cy, out.cy, d);
-  cb.add(tape + T.cz, out.cz, d);
-  cb.add(tape + T.erot, out.erot, d);
-  cb.add(tape + T.vib, out.vib, (size_t)cap);
-  cb.add(tape + T.cell, out.cell, (size_t)cap * 4);
-  cb.add(tape + T.pid, out.pid, (size_t)cap * 4);
-  cb.launch(st, &ce);
-  if ((e = launch_cells<double>(g, gas, out, offsets, mom, dt, nullptr, cs, counters, st)) !=
-      hipSuccess)
+  if ((e = launch_cells<double>(g, gas, in, offsets, mom, dt, nullptr, cs, counters, st, perm,
+                                !update_solo(g))) != hipSuccess)
     return e;
+  auto d = [&](size_t at) { return (double*)(tape + at); };
+  TapeOut to;
+  to.y = d(T.y); to.cx = d(T.cx); to.cy = d(T.cy); to.cz = d(T.cz); to.erot = d(T.erot);
+  to.vib = (uint8_t*)(tape + T.vib); to.cell = (int32_t*)(tape + T.cell);
+  to.pid = (uint32_t*)(tape + T.pid);
+  to.ccx = d(T.ccx); to.ccy = d(T.ccy); to.ccz = d(T.ccz); to.cerot = d(T.cerot);
+  to.kcx = d(T.kcx); to.kcy = d(T.kcy); to.kcz = d(T.kcz); to.kerot = d(T.kerot);
+  to.kvib = (uint8_t*)(tape + T.kvib);
+  to.fcy = d(T.fcy);
+  if ((e = launch_update_taped(g, gas, bc, dt, cs, offsets, out, seed, step, ws, L, counters, st, in,
+                               perm, to)) != hipSuccess)
+    return e;
+  CopyBatch cb;
   cb.add(tape + T.offsets, offsets, (size_t)(g.M + 1) * 8);
   cb.add(tape + T.cs, cs, cellstate_bytes(g.M));
-  cb.launch(st, &ce);
-  if ((e = launch_collide<double>(g, gas, cs, offsets, out, seed, step, counters, st)) != hipSuccess)
-    return e;
-  cb.add(tape + T.ccx, out.cx, d);
-  cb.add(tape + T.ccy, out.cy, d);
-  cb.add(tape + T.ccz, out.cz, d);
-  cb.add(tape + T.cerot, out.erot, d);
-  cb.launch(st, &ce);
-  if ((e = launch_conserve<double>(g, gas, cs, offsets, out, seed, step, counters, st)) != hipSuccess)
-    return e;
-  cb.add(tape + T.kcx, out.cx, d);
-  cb.add(tape + T.kcy, out.cy, d);
-  cb.add(tape + T.kcz, out.cz, d);
-  cb.add(tape + T.kerot, out.erot, d);
-  cb.add(tape + T.kvib, out.vib, (size_t)cap);
-  cb.launch(st, &ce);
-  if (ce != hipSuccess) return ce;
-  if ((e = launch_advect<double>(g, gas, bc, dt, out, seed, step, ws, L, counters, st)) != hipSuccess)
-    return e;
-  // the y velocity after the flight, for the hit-time derivative of the
-  // particles that met a wall (1D: no particle is created or removed)
-  copy_d(tape + T.fcy, out.cy, d, st, &ce);
-  return ce;
+  cb.launch(st, &e);
+  return e;
 }
 
 // ---- shared pieces of the reverse -------------------------------------------
@@ -305,6 +262,14 @@ __device__ __forceinline__ void trel_dual(double th, double Ttr, double Trot, do
   using D6 = Dual<6>;
   const D6 tt = D6::var(Ttr, 0), tr = D6::var(Trot, 1), tv = D6::var(Tvib, 2);
   const D6 aa = D6::var(a, 3), bb = D6::var(b, 4), om = D6::var(oma2, 5);
+  if (b < 1e-12) {
+    // the forward's gammas have no vibrational part here (particle_coef)
+    const D6 g1 = 3.0 * aa / (1.5 + aa);
+    const D6 X = g1 * (tt - tr);
+    *Ttr_rel = tt - X / (1.5 * om);
+    *Trot_rel = tr + X / om;
+    return;
+  }
   const D6 Tc = tcheck_dual<6>(th, tt, tr, tv, aa, bb);
   const D6 cb = cbar_R<D6>(D6(th), Tc, tv);
   const D6 D = 1.5 + aa + bb * cb;
@@ -330,33 +295,39 @@ __device__ __forceinline__ T prandtl_t(const GasP& g, T Ttr) {
 
 // The cell coefficients the particle update and conservation read (the
 // forward's cell_state, USP-FPM branch, constant collision numbers) as
-// functions of (T_tr, T_rot, T_vib, Z_rot, omega, mu_ref):
-// out = a, b, alpha, 1 - alpha^2, nu, e_rot target.
+// functions of (T_tr, T_rot, T_vib, Z_rot, omega, mu_ref), differentiated in
+// direction `dir` of the six (a lane takes one; all six on one lane were
+// 7 us a cell): out = a, b, alpha, 1 - alpha^2, nu, e_rot target.
 __device__ __forceinline__ void cell_coef_dual(const GasP& gas, double alpha_vss, double nd,
                                                double dtc, double Ttr, double Trot, double Tvib,
-                                               Dual<6> out[6]) {
-  using D6 = Dual<6>;
+                                               int dir, Dual<1> out[6]) {
+  using D1 = Dual<1>;
+  auto var = [&](double x, int k) {
+    D1 r(x);
+    r.d[0] = k == dir ? 1.0 : 0.0;
+    return r;
+  };
   const double R = gas.R, Th = gas.theta;
-  const D6 tt = D6::var(Ttr, 0), tr = D6::var(Trot, 1), tv = D6::var(Tvib, 2);
-  const D6 zr = D6::var(gas.Z_rot, 3), om = D6::var(gas.omega, 4), mr = D6::var(gas.mu_ref, 5);
-  const D6 K = alpha_vss * (5.0 - 2.0 * om) * (7.0 - 2.0 * om) /
+  const D1 tt = var(Ttr, 0), tr = var(Trot, 1), tv = var(Tvib, 2);
+  const D1 zr = var(gas.Z_rot, 3), om = var(gas.omega, 4), mr = var(gas.mu_ref, 5);
+  const D1 K = alpha_vss * (5.0 - 2.0 * om) * (7.0 - 2.0 * om) /
                (5.0 * (alpha_vss + 1.0) * (alpha_vss + 2.0));
-  const D6 mu = mr * pow(tt / gas.T_ref, om);
-  const D6 mup = mu / (nd * KB * tt);
-  const D6 tauc = K * mup;
-  const D6 Pr = prandtl_t<D6>(gas, tt);
-  const D6 A = 2.0 * mup;
-  const D6 r3 = (A - Pr * dtc) / (A + Pr * dtc);
-  const D6 r2 = (A - dtc) / (A + dtc);
-  const D6 al = cbrt(r3);
-  const D6 oma2 = (2.0 * Pr * dtc / (A + Pr * dtc)) * (1.0 + al) / (1.0 + al + al * al);
-  const D6 nu = (r2 - al * al) / oma2;
-  const D6 a = dtc / (dtc + 2.0 * zr * tauc);
-  const D6 b = dtc / (dtc + 2.0 * gas.Z_vib * tauc);
-  const D6 Tc = tcheck_dual<6>(Th, tt, tr, tv, a, b);
-  const D6 cb = cbar_R<D6>(D6(Th), Tc, tv);
-  const D6 D = 1.5 + a + b * cb;
-  const D6 g1 = 3.0 * a / D, g3 = 2.0 * a * b * cb / D;
+  const D1 mu = mr * pow(tt / gas.T_ref, om);
+  const D1 mup = mu / (nd * KB * tt);
+  const D1 tauc = K * mup;
+  const D1 Pr = prandtl_t<D1>(gas, tt);
+  const D1 A = 2.0 * mup;
+  const D1 r3 = (A - Pr * dtc) / (A + Pr * dtc);
+  const D1 r2 = (A - dtc) / (A + dtc);
+  const D1 al = cbrt(r3);
+  const D1 oma2 = (2.0 * Pr * dtc / (A + Pr * dtc)) * (1.0 + al) / (1.0 + al + al * al);
+  const D1 nu = (r2 - al * al) / oma2;
+  const D1 a = dtc / (dtc + 2.0 * zr * tauc);
+  const D1 b = dtc / (dtc + 2.0 * gas.Z_vib * tauc);
+  const D1 Tc = tcheck_dual<1>(Th, tt, tr, tv, a, b);
+  const D1 cb = cbar_R<D1>(D1(Th), Tc, tv);
+  const D1 D = 1.5 + a + b * cb;
+  const D1 g1 = 3.0 * a / D, g3 = 2.0 * a * b * cb / D;
   out[0] = a; out[1] = b; out[2] = al; out[3] = oma2; out[4] = nu;
   out[5] = R * tr + R * (g1 * (tt - tr) - g3 * (tr - tv));
 }
@@ -383,23 +354,45 @@ __device__ __forceinline__ double& lam_at(double* lam, int o, int f, int64_t cap
   return lam[((int64_t)o * NLAM + f) * cap + i];
 }
 
-// ---- K1: flight and conservation reversed, wave per cell ----------------------
-__global__ __launch_bounds__(256) void k_adj_flight_conserve(GridP g, GasP gas, BcP bc, double dt,
-                                                             TapeP T, int64_t cap,
-                                                             const double* __restrict__ lam_in,
-                                                             double* __restrict__ lam1,
-                                                             double* __restrict__ cons,
-                                                             double w_tau) {
-  const int lane = threadIdx.x & 63;
-  const int64_t c = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+// The reverse kernels take a workgroup per cell, a thread per particle: the
+// differentiable channel has a hundred cells of some hundred particles, and a
+// wave a cell left the chip idle (100 x 500: flight and conservation 40 us).
+constexpr int ADJ_BLOCK = 512;
+constexpr int ADJ_WAVES = ADJ_BLOCK / 64;
+
+// Sums of N values over the workgroup, in wave order; every thread gets them.
+template <int N>
+__device__ __forceinline__ void block_sums(double v[N], double (*red)[ADJ_WAVES]) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const double t = wave_sum(v[k]);
+    if (lane == 0) red[k][wid] = t;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    double t = red[k][0];
+#pragma unroll
+    for (int w = 1; w < ADJ_WAVES; ++w) t += red[k][w];
+    v[k] = t;
+  }
+  __syncthreads();
+}
+
+// ---- K1: flight and conservation reversed -------------------------------------
+__global__ __launch_bounds__(ADJ_BLOCK) void k_adj_flight_conserve(
+    GridP g, GasP gas, BcP bc, double dt, TapeP T, int64_t cap, const double* __restrict__ lam_in,
+    double* __restrict__ lam1, double* __restrict__ cons, double w_tau, unsigned int* done) {
+  __shared__ double red[10][ADJ_WAVES];
+  const int64_t c = blockIdx.x;
   const int64_t M = g.M;
-  if (c >= M) return;
+  if (c == 0 && threadIdx.x == 0) *done = 0u;  // counts the workgroups of K3
   const int64_t o0 = T.offsets[c], o1 = T.offsets[c + 1], N = o1 - o0;
-  for (int o = 0; o < NOBJ; ++o)
-    if (lane < NCONS) cons[((int64_t)o * NCONS + lane) * M + c] = 0.0;
-  if (N == 0) return;
   const double* cs = T.cs;
-  const bool coll = cs[CS_COLLIDE * M + c] != 0.0;
+  const bool coll = N > 0 && cs[CS_COLLIDE * M + c] != 0.0;
+  if (!coll && threadIdx.x < NOBJ * NCONS) cons[(int64_t)threadIdx.x * M + c] = 0.0;
+  if (N == 0) return;
   // adjoint of the post-conservation state (o, component) of particle i.
   // A particle whose flight meets a wall leaves with the re-emitted
   // velocity, energy and level (constants of the path); its position after
@@ -410,14 +403,13 @@ __global__ __launch_bounds__(256) void k_adj_flight_conserve(GridP g, GasP gas, 
   const double ylo = (double)g.y0, yhi = (double)edge<double>(g.y0, g.dy, g.ny);
   auto post = [&](int64_t i, int o, double lc[3], double* le, double* ly) {
     const double ck[3] = {T.kcx[i] + bc.g[0] * dt, T.kcy[i] + bc.g[1] * dt, T.kcz[i] + bc.g[2] * dt};
+    const double lyv = lam_at(const_cast<double*>(lam_in), o, LY, cap, i);
     if (flight_event_1d(g, T.y[i], ck[1], dt)) {
-      const double lyf = lam_at(const_cast<double*>(lam_in), o, LY, cap, i);
       const double r = T.fcy[i] / ck[1];
       const double t1 = ((ck[1] < 0.0 ? ylo : yhi) - T.y[i]) / ck[1];
-      lc[0] = o == 1 ? w_tau : 0.0; lc[1] = lyf * r * t1; lc[2] = 0.0; *le = 0.0; *ly = lyf * r;
+      lc[0] = o == 1 ? w_tau : 0.0; lc[1] = lyv * r * t1; lc[2] = 0.0; *le = 0.0; *ly = lyv * r;
       return;
     }
-    const double lyv = lam_at(const_cast<double*>(lam_in), o, LY, cap, i);
     lc[0] = lam_at(const_cast<double*>(lam_in), o, LCX, cap, i);
     lc[1] = lam_at(const_cast<double*>(lam_in), o, LCX + 1, cap, i) + dt * lyv;
     lc[2] = lam_at(const_cast<double*>(lam_in), o, LCX + 2, cap, i);
@@ -425,7 +417,7 @@ __global__ __launch_bounds__(256) void k_adj_flight_conserve(GridP g, GasP gas, 
     *ly = lyv;
   };
   if (!coll) {
-    for (int64_t i = o0 + lane; i < o1; i += 64)
+    for (int64_t i = o0 + threadIdx.x; i < o1; i += ADJ_BLOCK)
       for (int o = 0; o < NOBJ; ++o) {
         double lc[3], le, ly;
         post(i, o, lc, &le, &ly);
@@ -437,17 +429,15 @@ __global__ __launch_bounds__(256) void k_adj_flight_conserve(GridP g, GasP gas, 
   }
   // forward scalars of the conservation (the forward's own sums)
   const double Un[3] = {cs[CS_UX * M + c], cs[CS_UY * M + c], cs[CS_UZ * M + c]};
-  double s[5] = {0, 0, 0, 0, 0};
-  double SIp = 0.0;
-  for (int64_t i = o0 + lane; i < o1; i += 64) {
+  double s[6] = {0, 0, 0, 0, 0, 0};
+  for (int64_t i = o0 + threadIdx.x; i < o1; i += ADJ_BLOCK) {
     const double d0 = T.ccx[i] - Un[0], d1 = T.ccy[i] - Un[1], d2 = T.ccz[i] - Un[2];
     s[0] += d0; s[1] += d1; s[2] += d2;
     s[3] += d0 * d0 + d1 * d1 + d2 * d2;
     s[4] += T.cerot[i];
-    SIp += (double)T.kvib[i];
+    s[5] += (double)T.kvib[i];
   }
-  for (int k = 0; k < 5; ++k) s[k] = wave_sum(s[k]);
-  SIp = wave_sum(SIp);
+  block_sums<6>(s, red);
   const double Nd = (double)N;
   const double m1[3] = {s[0] / Nd, s[1] / Nd, s[2] / Nd};
   const double etr_s = 0.5 * (s[3] / Nd - (m1[0] * m1[0] + m1[1] * m1[1] + m1[2] * m1[2]));
@@ -456,39 +446,46 @@ __global__ __launch_bounds__(256) void k_adj_flight_conserve(GridP g, GasP gas, 
   const double frot = rot ? erot_t / erot_s : 1.0;
   const double erot_a = rot ? erot_t : erot_s;
   const double RTh = gas.R * gas.theta;
-  const double evib_a = SIp * RTh / Nd;
+  const double evib_a = s[5] * RTh / Nd;
   const double E0 = cs[CS_ETR * M + c] + cs[CS_EROT * M + c] + cs[CS_EVIB * M + c];
   const double s2 = (E0 - erot_a - evib_a) / etr_s;
   const bool vel = etr_s > 0.0 && s2 > 0.0;
   const double sc = vel ? sqrt(s2) : 0.0;
   const double Us[3] = {Un[0] + m1[0], Un[1] + m1[1], Un[2] + m1[2]};
-  for (int o = 0; o < NOBJ; ++o) {
-    // reverse sums over the cell
-    double r[5] = {0, 0, 0, 0, 0};  // Lambda_e, L_sc, sum lc (3)
-    for (int64_t i = o0 + lane; i < o1; i += 64) {
+  // reverse sums over the cell: Lambda_e, L_sc, sum lc (3) of each objective
+  double r[NOBJ * 5];
+#pragma unroll
+  for (int k = 0; k < NOBJ * 5; ++k) r[k] = 0.0;
+  for (int64_t i = o0 + threadIdx.x; i < o1; i += ADJ_BLOCK) {
+#pragma unroll
+    for (int o = 0; o < NOBJ; ++o) {
       double lc[3], le, ly;
       post(i, o, lc, &le, &ly);
-      r[0] += le * T.cerot[i];
-      r[1] += lc[0] * (T.ccx[i] - Us[0]) + lc[1] * (T.ccy[i] - Us[1]) + lc[2] * (T.ccz[i] - Us[2]);
-      r[2] += lc[0]; r[3] += lc[1]; r[4] += lc[2];
+      r[5 * o] += le * T.cerot[i];
+      r[5 * o + 1] += lc[0] * (T.ccx[i] - Us[0]) + lc[1] * (T.ccy[i] - Us[1]) + lc[2] * (T.ccz[i] - Us[2]);
+      r[5 * o + 2] += lc[0]; r[5 * o + 3] += lc[1]; r[5 * o + 4] += lc[2];
     }
-    for (int k = 0; k < 5; ++k) r[k] = wave_sum(r[k]);
+  }
+  block_sums<NOBJ * 5>(r, red);
+#pragma unroll
+  for (int o = 0; o < NOBJ; ++o) {
+    const double* ro = r + 5 * o;
     double l_erot_t = 0.0, l_erot_s = 0.0;
     if (rot) {
-      const double lfrot = r[0];
+      const double lfrot = ro[0];
       l_erot_t = lfrot / erot_s;
       l_erot_s = -lfrot * frot / erot_s;
     }
     double lE0 = 0.0, letr = 0.0, lUs[3] = {0, 0, 0}, lUn[3] = {0, 0, 0};
     if (vel) {
-      const double ls2 = r[1] / (2.0 * sc);
+      const double ls2 = ro[1] / (2.0 * sc);
       lE0 = ls2 / etr_s;
       const double lerot_a = -ls2 / etr_s;
       letr = -ls2 * s2 / etr_s;
-      for (int k = 0; k < 3; ++k) { lUs[k] = -sc * r[2 + k]; lUn[k] = r[2 + k]; }
+      for (int k = 0; k < 3; ++k) { lUs[k] = -sc * ro[2 + k]; lUn[k] = ro[2 + k]; }
       if (rot) l_erot_t += lerot_a; else l_erot_s += lerot_a;
     }
-    for (int64_t i = o0 + lane; i < o1; i += 64) {
+    for (int64_t i = o0 + threadIdx.x; i < o1; i += ADJ_BLOCK) {
       double lc[3], le, ly;
       post(i, o, lc, &le, &ly);
       const double cst[3] = {T.ccx[i], T.ccy[i], T.ccz[i]};
@@ -499,7 +496,7 @@ __global__ __launch_bounds__(256) void k_adj_flight_conserve(GridP g, GasP gas, 
       lam_at(lam1, o, LE, cap, i) = (rot ? frot * le : le) + l_erot_s / Nd;
       lam_at(lam1, o, LY, cap, i) = ly;
     }
-    if (lane == 0) {
+    if (threadIdx.x == 0) {
       double* cc = cons + (int64_t)o * NCONS * M;
       for (int k = 0; k < 3; ++k) cc[(CC_U + k) * M + c] = lUn[k];
       cc[CC_EROT_NEW * M + c] = l_erot_t;
@@ -508,272 +505,257 @@ __global__ __launch_bounds__(256) void k_adj_flight_conserve(GridP g, GasP gas, 
   }
 }
 
-// ---- K2: the particle update reversed, thread per particle --------------------
-__global__ __launch_bounds__(256) void k_adj_collide(GridP g, GasP gas, TapeP T, int64_t cap,
-                                                     uint64_t seed, uint32_t step,
-                                                     double* __restrict__ lam1,
-                                                     double* __restrict__ own,
-                                                     double* __restrict__ nbr,
-                                                     int32_t* __restrict__ nbrc) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t M = g.M;
-  if (i >= T.offsets[M]) return;
-  const int32_t c = T.cell[i];
-  const double* cs = T.cs;
-  for (int o = 0; o < NOBJ; ++o) {
-    for (int f = 0; f < NOWN; ++f) own[((int64_t)o * NOWN + f) * cap + i] = 0.0;
-    for (int f = 0; f < NNBR; ++f) nbr[((int64_t)o * NNBR + f) * cap + i] = 0.0;
-  }
-  nbrc[i] = -1;
-  if (cs[CS_COLLIDE * M + c] == 0.0) return;  // identity: lam1 already holds the adjoint
-  const PartP<double> p = tape_parts(T, cap);
-  const Stencil st = particle_stencil<double>(g, cell_records(cs, M)[c].stencil, c,
-                                              load_pos(p, i, g.dim));
-  double U[3], P[6], Tk[3];
-  fields_planes(cs, M, c, st, U, P, Tk);
-  bool floored[3];
-  for (int k = 0; k < 3; ++k) floored[k] = Tk[k] == 0.05 * cs[(CS_TTR + k) * M + c] &&
-                                           interp_planes(cs, M, CS_TTR + k, c, st) < Tk[k];
-  const CellCoef cc = coef_planes(cs, M, c, false);  // the adjoint takes the Prandtl-number rule
-  const PartCoef<double> pc = particle_coef<double>(gas.R, gas.theta, Tk[0], Tk[1], Tk[2], P, cc);
-  if (pc.fallback) {
-    // held fixed: no adjoint reaches the pre-collision values through it
-    for (int o = 0; o < NOBJ; ++o)
-      for (int k = 0; k < 4; ++k) lam_at(lam1, o, LCX + k, cap, i) = 0.0;
-    return;
-  }
-  const double R = gas.R;
-  Dual<6> Ttr_rel, Trot_rel;
-  trel_dual(gas.theta, Tk[0], Tk[1], Tk[2], cc.a, cc.b, cc.oma2, &Ttr_rel, &Trot_rel);
-  const bool rclamp = pc.clamp_rot;
-  // draws (the forward's)
-  const U4 w0 = philox(T.pid[i], step, TAG_COLLIDE, 0u, seed);
-  double G1, G2, G3, G4;
-  box_muller<double>(w0.w[0], w0.w[1], &G1, &G2);
-  box_muller<double>(w0.w[2], w0.w[3], &G3, &G4);
-  const double al = cc.al, oma2 = cc.oma2, nu = cc.nu, sq = sqrt(oma2);
-  const double* L = pc.L;
-  const double v[3] = {L[0] * G1, L[1] * G1 + L[2] * G2, L[3] * G1 + L[4] * G2 + L[5] * G3};
-  const double cin[3] = {T.cx[i], T.cy[i], T.cz[i]}, ein = T.erot[i];
-  const double Trr = pc.Trot_rel;
-  const double half = 0.5 * R * Trr * oma2;
-  const double se = sqrt(ein), sh = sqrt(half);
-  const double root = se * al + sh * G4;
-  const int ty = st.hy ? (int)(st.c01 - c) : 0;
-  if (st.hy) nbrc[i] = (int32_t)st.c01;
-  for (int o = 0; o < NOBJ; ++o) {
-    double lcp[3];
-    for (int k = 0; k < 3; ++k) lcp[k] = lam_at(lam1, o, LCX + k, cap, i);
-    const double lep = lam_at(lam1, o, LE, cap, i);
-    double lU[3], lc[3], lP[6] = {0, 0, 0, 0, 0, 0}, lT[3] = {0, 0, 0};
-    double lal = 0.0, lsq = 0.0;
-    double lL[6];
-    for (int k = 0; k < 3; ++k) {
-      lU[k] = (1.0 - al) * lcp[k];
-      lc[k] = al * lcp[k];
-      lal += lcp[k] * (cin[k] - U[k]);
-      lsq += lcp[k] * v[k];
-    }
-    const double lv0 = sq * lcp[0], lv1 = sq * lcp[1], lv2 = sq * lcp[2];
-    lL[0] = lv0 * G1; lL[1] = lv1 * G1; lL[2] = lv1 * G2;
-    lL[3] = lv2 * G1; lL[4] = lv2 * G2; lL[5] = lv2 * G3;
-    // rotational energy
-    double lhalf = lep;
-    const double lroot = 2.0 * root * lep;
-    const double le = se > 0.0 ? lroot * al / (2.0 * se) : 0.0;
-    lal += lroot * se;
-    if (sh > 0.0) lhalf += lroot * G4 / (2.0 * sh);
-    const double lTrr = rclamp ? 0.0 : lhalf * 0.5 * R * oma2;
-    double loma2 = lhalf * 0.5 * R * Trr + lsq / (2.0 * sq);
-    // Lambda = R T_tr^rel I + nu (Pi - R T_tr I), its Cholesky factor
-    double lS[6];
-    chol3_reverse(L, lL, lS);
-    const double lTtr_rel = R * (lS[0] + lS[1] + lS[2]);
-    double lnu = 0.0;
-    for (int k = 0; k < 3; ++k) lnu += lS[k] * (P[k] - R * Tk[0]);
-    for (int k = 3; k < 6; ++k) lnu += lS[k] * P[k];
-    for (int k = 0; k < 6; ++k) lP[k] += nu * lS[k];
-    lT[0] += -nu * R * (lS[0] + lS[1] + lS[2]);
-    // relaxation temperatures: inputs (T_tr, T_rot, T_vib, a, b, 1-alpha^2)
-    double lin6[6];
-    for (int k = 0; k < 6; ++k) lin6[k] = lTtr_rel * Ttr_rel.d[k] + lTrr * Trot_rel.d[k];
-    lT[0] += lin6[0]; lT[1] += lin6[1]; lT[2] += lin6[2];
-    const double la = lin6[3], lb = lin6[4];
-    loma2 += lin6[5];
-    // floors and the reconstruction (Sec. III.B, 1D: own cell and c01)
-    double* ow = own + (int64_t)o * NOWN * cap;
-    double* nb = nbr + (int64_t)o * NNBR * cap;
-    double lw = 0.0;
-    auto scatter = [&](int f, int plane, double lf) {
-      const double* F = cs + (int64_t)plane * M;
-      if (st.hy) {
-        ow[(int64_t)f * cap + i] += (1.0 - st.wy) * lf;
-        nb[(int64_t)f * cap + i] += st.wy * lf;
-        lw += (F[st.c01] - F[c]) * lf;
-      } else {
-        ow[(int64_t)f * cap + i] += lf;
-      }
-    };
-    for (int k = 0; k < 3; ++k) scatter(CF_U + k, CS_UX + k, lU[k]);
-    for (int k = 0; k < 6; ++k) scatter(CF_P + k, CS_PXX + k, lP[k]);
-    for (int k = 0; k < 3; ++k) {
-      if (floored[k]) ow[(int64_t)(CF_T + k) * cap + i] += 0.05 * lT[k];
-      else scatter(CF_T + k, CS_TTR + k, lT[k]);
-    }
-    ow[(int64_t)CF_A * cap + i] = la;
-    ow[(int64_t)CF_B * cap + i] = lb;
-    ow[(int64_t)CF_AL * cap + i] = lal;
-    ow[(int64_t)CF_OMA2 * cap + i] = loma2;
-    ow[(int64_t)CF_NU * cap + i] = lnu;
-    for (int k = 0; k < 3; ++k) lam_at(lam1, o, LCX + k, cap, i) = lc[k];
-    lam_at(lam1, o, LE, cap, i) = le;
-    if (ty != 0) lam_at(lam1, o, LY, cap, i) += lw / ((double)ty * g.dy);
-  }
-}
+// ---- K2: the particle update reversed ------------------------------------------
+// The contributions of a cell's particles to the fields they read (their own
+// cell's, and through the stencil those of the cell below or above) are
+// summed over the workgroup as they are formed, in a fixed order.  Two
+// workgroups of four waves a cell: the kernel holds 250 registers, and a
+// hundred cells would fill 100 of 256 CUs (100 x 500: 45 us for it and the
+// separate sums before, 38 now).
+constexpr int K2_BLOCK = ADJ_BLOCK / K2_PARTS;
+constexpr int K2_WAVES = K2_BLOCK / 64;
 
-// lane 0 of K3: the cell state reversed for objective o
-__device__ __forceinline__ void cell_reverse(const GasP& gas, int64_t c, int64_t M, int o,
-                                             const double lf[NOWN], const Dual<6> co[6],
-                                             const double* __restrict__ cons,
-                                             double* __restrict__ lmom,
-                                             double* __restrict__ gcell) {
-  {
-    const double R = gas.R;
-    const double* cc = cons + (int64_t)o * NCONS * M;
-    double lU[3], lP[6];
-    for (int k = 0; k < 3; ++k) lU[k] = lf[CF_U + k] + cc[(CC_U + k) * M + c];
-    for (int k = 0; k < 6; ++k) lP[k] = lf[CF_P + k];
-    const double lE0 = cc[CC_E0 * M + c];
-    // coefficients (a, b, alpha, 1-alpha^2, nu, e_rot target) of (T_tr,
-    // T_rot, T_vib, Z_rot, omega, mu_ref)
-    const double lout[6] = {lf[CF_A], lf[CF_B], lf[CF_AL], lf[CF_OMA2], lf[CF_NU],
-                            cc[CC_EROT_NEW * M + c]};
-    double lin[6] = {0, 0, 0, 0, 0, 0};
-    for (int q = 0; q < 6; ++q)
-      for (int k = 0; k < 6; ++k) lin[k] += lout[q] * co[q].d[k];
-    const double lTtr = lf[CF_T] + lin[0];
-    const double lTrot = lf[CF_T + 1] + lin[1];
-    // T_tr = tr(Pi)/(3R), T_rot = e_rot/R, E0 = tr(Pi)/2 + e_rot + I R theta
-    for (int k = 0; k < 3; ++k) lP[k] += lTtr / (3.0 * R) + 0.5 * lE0;
-    double* lm = lmom + (int64_t)o * NAMOM * M;
-    for (int k = 0; k < 3; ++k) lm[(AM_U + k) * M + c] = lU[k];
-    for (int k = 0; k < 6; ++k) lm[(AM_P + k) * M + c] = lP[k];
-    lm[AM_EROT * M + c] = lTrot / R + lE0;
-    for (int k = 0; k < NPAR; ++k) gcell[((int64_t)o * NPAR + k) * M + c] = lin[3 + k];
-  }
-}
-
-// ---- K3: cell adjoints, then the cell state reversed ---------------------------
-// K3a: one wave per (objective, field, cell): the cell's own particles'
-// contributions plus those of the neighbouring cells' particles whose
-// stencil reads it (1D: cells c-1 and c+1), in a fixed order.
-__global__ __launch_bounds__(256) void k_adj_cell_sums(int64_t M, TapeP T, int64_t cap,
-                                                       const double* __restrict__ own,
-                                                       const double* __restrict__ nbr,
-                                                       const int32_t* __restrict__ nbrc,
-                                                       double* __restrict__ csum) {
-  const int lane = threadIdx.x & 63;
-  const int64_t w = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (w >= (int64_t)NOBJ * NOWN * M) return;
-  const int64_t c = w % M, of = w / M;
-  const int o = (int)(of / NOWN), f = (int)(of % NOWN);
+__global__ __launch_bounds__(K2_BLOCK) void k_adj_collide(GridP g, GasP gas, TapeP T, int64_t cap,
+                                                           uint64_t seed, uint32_t step,
+                                                           double* __restrict__ lam1,
+                                                           double* __restrict__ csum) {
+  __shared__ double acc[K2_WAVES][NOBJ * NSUM];
+  const int64_t M = g.M, c = blockIdx.x / K2_PARTS;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, half = (int)(blockIdx.x % K2_PARTS);
+  for (int k = threadIdx.x; k < K2_WAVES * NOBJ * NSUM; k += K2_BLOCK) (&acc[0][0])[k] = 0.0;
+  __syncthreads();
   const int64_t o0 = T.offsets[c], o1 = T.offsets[c + 1];
+  const double* cs = T.cs;
+  const bool coll = cs[CS_COLLIDE * M + c] != 0.0;  // else identity: lam1 already holds the adjoint
+  const PartP<double> p = tape_parts(T, cap);
+  // every wave walks the same number of rounds (the sums need whole waves)
+  for (int64_t b = o0 + (half * K2_WAVES + wid) * 64; coll && b < o1; b += ADJ_BLOCK) {
+    const int64_t i = b + lane;
+    bool act = i < o1;
+    const int64_t iq = act ? i : o0;
+    const Stencil st = particle_stencil<double>(g, cell_records(cs, M)[c].stencil, (int32_t)c,
+                                                load_pos(p, iq, g.dim));
+    double U[3], P[6], Tk[3];
+    fields_planes(cs, M, c, st, U, P, Tk);
+    bool floored[3];
+    for (int k = 0; k < 3; ++k) floored[k] = Tk[k] == 0.05 * cs[(CS_TTR + k) * M + c] &&
+                                             interp_planes(cs, M, CS_TTR + k, c, st) < Tk[k];
+    const CellCoef cc = coef_planes(cs, M, c, false);  // the adjoint takes the Prandtl-number rule
+    const PartCoef<double> pc = particle_coef<double>(gas.R, gas.theta, Tk[0], Tk[1], Tk[2], P, cc);
+    if (pc.fallback) {
+      // held fixed: no adjoint reaches the pre-collision values through it
+      if (act)
+        for (int o = 0; o < NOBJ; ++o)
+          for (int k = 0; k < 4; ++k) lam_at(lam1, o, LCX + k, cap, i) = 0.0;
+      act = false;
+    }
+    const double R = gas.R;
+    Dual<6> Ttr_rel, Trot_rel;
+    trel_dual(gas.theta, Tk[0], Tk[1], Tk[2], cc.a, cc.b, cc.oma2, &Ttr_rel, &Trot_rel);
+    const bool rclamp = pc.clamp_rot;
+    // draws (the forward's)
+    const U4 w0 = philox(T.pid[iq], step, TAG_COLLIDE, 0u, seed);
+    double G1, G2, G3, G4;
+    box_muller<double>(w0.w[0], w0.w[1], &G1, &G2);
+    box_muller<double>(w0.w[2], w0.w[3], &G3, &G4);
+    const double al = cc.al, oma2 = cc.oma2, nu = cc.nu, sq = sqrt(oma2);
+    const double* L = pc.L;
+    const double cin[3] = {T.cx[iq], T.cy[iq], T.cz[iq]}, ein = T.erot[iq];
+    const double Trr = pc.Trot_rel;
+    const double half = 0.5 * R * Trr * oma2;
+    const double se = sqrt(ein), sh = sqrt(half);
+    const double root = se * al + sh * G4;
+    const int ty = st.hy ? (int)(st.c01 - c) : 0;
+    const double v[3] = {L[0] * G1, L[1] * G1 + L[2] * G2, L[3] * G1 + L[4] * G2 + L[5] * G3};
+#pragma unroll 1
+    for (int o = 0; o < NOBJ; ++o) {
+      // each sum over the wave goes to the lane of its slot (a particle that
+      // takes no part adds zero, whatever its own values are)
+      double mine = 0.0;
+      auto emit = [&](int slot, double x, bool on) {
+        const double t = wave_sum(on ? x : 0.0);
+        mine = lane == slot ? t : mine;
+      };
+      double lcp[3];
+      for (int k = 0; k < 3; ++k) lcp[k] = lam_at(lam1, o, LCX + k, cap, iq);
+      const double lep = lam_at(lam1, o, LE, cap, iq);
+      // floors and the reconstruction (Sec. III.B, 1D: own cell and c01)
+      double lw = 0.0;
+      auto scatter = [&](int f, int plane, double lf, bool held) {
+        const double* F = cs + (int64_t)plane * M;
+        const bool across = st.hy && !held;
+        emit(f, held ? 0.05 * lf : across ? (1.0 - st.wy) * lf : lf, act);
+        emit(NOWN + f, st.wy * lf, act && across && ty < 0);
+        emit(NOWN + NNBR + f, st.wy * lf, act && across && ty > 0);
+        if (across) lw += (F[st.c01] - F[c]) * lf;
+      };
+      double lal = 0.0, lsq = 0.0;
+      double lL[6];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        scatter(CF_U + k, CS_UX + k, (1.0 - al) * lcp[k], false);
+        lal += lcp[k] * (cin[k] - U[k]);
+        lsq += lcp[k] * v[k];
+      }
+      const double lv0 = sq * lcp[0], lv1 = sq * lcp[1], lv2 = sq * lcp[2];
+      lL[0] = lv0 * G1; lL[1] = lv1 * G1; lL[2] = lv1 * G2;
+      lL[3] = lv2 * G1; lL[4] = lv2 * G2; lL[5] = lv2 * G3;
+      // rotational energy
+      double lhalf = lep;
+      const double lroot = 2.0 * root * lep;
+      const double le = se > 0.0 ? lroot * al / (2.0 * se) : 0.0;
+      lal += lroot * se;
+      if (sh > 0.0) lhalf += lroot * G4 / (2.0 * sh);
+      const double lTrr = rclamp ? 0.0 : lhalf * 0.5 * R * oma2;
+      double loma2 = lhalf * 0.5 * R * Trr + lsq / (2.0 * sq);
+      // Lambda = R T_tr^rel I + nu (Pi - R T_tr I), its Cholesky factor
+      double lS[6];
+      chol3_reverse(L, lL, lS);
+      const double trS = lS[0] + lS[1] + lS[2], lTtr_rel = R * trS;
+      double lnu = 0.0;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        lnu += lS[k] * (k < 3 ? P[k] - R * Tk[0] : P[k]);
+        scatter(CF_P + k, CS_PXX + k, nu * lS[k], false);
+      }
+      // relaxation temperatures: inputs (T_tr, T_rot, T_vib, a, b, 1-alpha^2)
+      double lin6[6];
+      for (int k = 0; k < 6; ++k) lin6[k] = lTtr_rel * Ttr_rel.d[k] + lTrr * Trot_rel.d[k];
+      loma2 += lin6[5];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        scatter(CF_T + k, CS_TTR + k, k == 0 ? lin6[0] - nu * R * trS : lin6[k], floored[k]);
+      emit(CF_A, lin6[3], act);
+      emit(CF_B, lin6[4], act);
+      emit(CF_AL, lal, act);
+      emit(CF_OMA2, loma2, act);
+      emit(CF_NU, lnu, act);
+      if (act) {
+        for (int k = 0; k < 3; ++k) lam_at(lam1, o, LCX + k, cap, i) = al * lcp[k];
+        lam_at(lam1, o, LE, cap, i) = le;
+        if (ty != 0) lam_at(lam1, o, LY, cap, i) += lw / ((double)ty * g.dy);
+      }
+      if (lane < NSUM) acc[wid][o * NSUM + lane] += mine;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < NOBJ * NSUM) {
+    double t = acc[0][threadIdx.x];
+    for (int w = 1; w < K2_WAVES; ++w) t += acc[w][threadIdx.x];
+    csum[((int64_t)half * NOBJ * NSUM + threadIdx.x) * M + c] = t;
+  }
+}
+
+// ---- K3: cell state, moments and bin reversed, mass-flow source -----------------
+// The first wave of a cell's workgroup reverses its cell state (a lane per
+// objective and direction of the coefficients' Jacobian); then a thread per
+// particle takes the moments' adjoints on and undoes the bin.  The workgroup
+// that finishes last adds the cells' parameter partials to grad, in a fixed
+// order.
+__global__ __launch_bounds__(ADJ_BLOCK) void k_adj_moments(
+    GridP g, GasP gas, double alpha_vss, TapeP T, int64_t cap, const double* __restrict__ lam1,
+    const double* __restrict__ csum, const double* __restrict__ cons, double* __restrict__ lam_out,
+    double w_mdot, double* gcell, double* __restrict__ grad, unsigned int* done) {
+  __shared__ double lm[NOBJ][NAMOM], lf[NOBJ][NOWN], lin[NOBJ][6];
+  __shared__ bool last;
+  const int64_t M = g.M, c = blockIdx.x;
+  const double* cs = T.cs;
+  const int64_t o0 = T.offsets[c], o1 = T.offsets[c + 1];
+  // a thread's particle; the first one's loads run beside the cell's chain
+  int64_t i = o0 + threadIdx.x;
+  double cx = 0.0, cy = 0.0, cz = 0.0, l1[NOBJ][NLAM];
+  int32_t j = -1;
+  auto fetch = [&](int64_t k) {
+    if (k >= o1) return;
+    cx = T.cx[k]; cy = T.cy[k]; cz = T.cz[k]; j = T.perm[k];
+#pragma unroll
+    for (int o = 0; o < NOBJ; ++o)
+#pragma unroll
+      for (int f = 0; f < NLAM; ++f) l1[o][f] = lam_at(const_cast<double*>(lam1), o, f, cap, k);
+  };
+  fetch(i);
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    const bool coll = cs[CS_COLLIDE * M + c] != 0.0;
+    // adjoints of the cell's fields and coefficients: its own particles'
+    // sums and those of the cells below and above
+    if (lane < NOBJ * NOWN) {
+      const int o = lane / NOWN, f = lane % NOWN;
+      double t = 0.0;
+      for (int h = 0; h < K2_PARTS; ++h) {
+        const double* q = csum + (int64_t)(h * NOBJ + o) * NSUM * M;
+        t += q[f * M + c];
+        if (f < NNBR) {
+          if (c > 0) t += q[(NOWN + NNBR + f) * M + c - 1];
+          if (c + 1 < M) t += q[(NOWN + f) * M + c + 1];
+        }
+      }
+      lf[o][f] = t;
+    }
+    wave_sync_lds();
+    if (lane < NOBJ * 6) {
+      const int o = lane / 6, k = lane % 6;
+      double t = 0.0;
+      if (coll) {
+        Dual<1> co[6];
+        cell_coef_dual(gas, alpha_vss, cs[CS_NDENS * M + c], cs[CS_DT * M + c], cs[CS_TTR * M + c],
+                       cs[CS_TROT * M + c], cs[CS_TVIB * M + c], k, co);
+        const double lout[6] = {lf[o][CF_A], lf[o][CF_B], lf[o][CF_AL], lf[o][CF_OMA2], lf[o][CF_NU],
+                                cons[((int64_t)o * NCONS + CC_EROT_NEW) * M + c]};
+        for (int q = 0; q < 6; ++q) t += lout[q] * co[q].d[0];
+      }
+      lin[o][k] = t;
+      if (k >= 3) gcell[((int64_t)o * NPAR + k - 3) * M + c] = t;
+    }
+    wave_sync_lds();
+    if (lane < NOBJ) {
+      const int o = lane;
+      const double* cc = cons + (int64_t)o * NCONS * M;
+      const double lE0 = cc[CC_E0 * M + c];
+      const double lTtr = lf[o][CF_T] + lin[o][0], lTrot = lf[o][CF_T + 1] + lin[o][1];
+      for (int k = 0; k < 3; ++k) lm[o][AM_U + k] = coll ? lf[o][CF_U + k] + cc[(CC_U + k) * M + c] : 0.0;
+      // T_tr = tr(Pi)/(3R), T_rot = e_rot/R, E0 = tr(Pi)/2 + e_rot + I R theta
+      for (int k = 0; k < 6; ++k)
+        lm[o][AM_P + k] =
+            coll ? lf[o][CF_P + k] + (k < 3 ? lTtr / (3.0 * gas.R) + 0.5 * lE0 : 0.0) : 0.0;
+      lm[o][AM_EROT] = coll ? lTrot / gas.R + lE0 : 0.0;
+    }
+    __threadfence();
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) last = atomicAdd(done, 1u) == (unsigned int)M - 1u;
+  const double N = (double)(o1 - o0);
+  for (; i < o1; i += ADJ_BLOCK, fetch(i)) {
+    const double d[3] = {cx - cs[CS_UX * M + c], cy - cs[CS_UY * M + c], cz - cs[CS_UZ * M + c]};
+    if (j < 0) continue;
+#pragma unroll
+    for (int o = 0; o < NOBJ; ++o) {
+      const double* lP = lm[o] + AM_P;
+      // Pi = <C C>: xx yy zz xy xz yz
+      const double gP[3] = {2.0 * d[0] * lP[0] + d[1] * lP[3] + d[2] * lP[4],
+                            2.0 * d[1] * lP[1] + d[0] * lP[3] + d[2] * lP[5],
+                            2.0 * d[2] * lP[2] + d[0] * lP[4] + d[1] * lP[5]};
+      for (int k = 0; k < 3; ++k) {
+        double v = l1[o][LCX + k] + (lm[o][AM_U + k] + gP[k]) / N;
+        if (o == 0 && k == 0) v += w_mdot;
+        lam_at(lam_out, o, LCX + k, cap, j) = v;
+      }
+      lam_at(lam_out, o, LE, cap, j) = l1[o][LE] + lm[o][AM_EROT] / N;
+      lam_at(lam_out, o, LY, cap, j) = l1[o][LY];
+    }
+  }
+  __syncthreads();
+  if (!last) return;
+  // wave q: parameter partial q of all cells, lanes striding over them
+  __threadfence();
+  const int q = threadIdx.x >> 6;
+  if (q >= NOBJ * NPAR) return;
   double s = 0.0;
-  if (T.cs[CS_COLLIDE * M + c] != 0.0) {
-    const double* ow = own + ((int64_t)o * NOWN + f) * cap;
-    for (int64_t i = o0 + lane; i < o1; i += 64) s += ow[i];
-    if (f < NNBR) {
-      const double* nb = nbr + ((int64_t)o * NNBR + f) * cap;
-      const int64_t lo_n = c > 0 ? T.offsets[c - 1] : o0;
-      const int64_t hi_n = c + 1 < M ? T.offsets[c + 2] : o1;
-      for (int64_t i = lo_n + lane; i < o0; i += 64)
-        if (nbrc[i] == c) s += nb[i];
-      for (int64_t i = o1 + lane; i < hi_n; i += 64)
-        if (nbrc[i] == c) s += nb[i];
-    }
-  }
+  for (int64_t k = threadIdx.x & 63; k < M; k += 64) s += gcell[(int64_t)q * M + k];
   s = wave_sum(s);
-  if (lane == 0) csum[of * M + c] = s;
+  if ((threadIdx.x & 63) == 0) grad[q] += s;
 }
-
-// K3b: thread per cell: the cell state reversed (Dual<6> Jacobian of the
-// coefficients), giving moment adjoints and per-cell parameter partials.
-__global__ __launch_bounds__(64) void k_adj_cellstate(GridP g, GasP gas, double alpha_vss,
-                                                      TapeP T, const double* __restrict__ csum,
-                                                      const double* __restrict__ cons,
-                                                      double* __restrict__ lmom,
-                                                      double* __restrict__ gcell) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t M = g.M;
-  if (c >= M) return;
-  const double* cs = T.cs;
-  for (int o = 0; o < NOBJ; ++o) {
-    for (int k = 0; k < NAMOM; ++k) lmom[((int64_t)o * NAMOM + k) * M + c] = 0.0;
-    for (int k = 0; k < NPAR; ++k) gcell[((int64_t)o * NPAR + k) * M + c] = 0.0;
-  }
-  if (cs[CS_COLLIDE * M + c] == 0.0) return;
-  Dual<6> co[6];
-  cell_coef_dual(gas, alpha_vss, cs[CS_NDENS * M + c], cs[CS_DT * M + c], cs[CS_TTR * M + c],
-                 cs[CS_TROT * M + c], cs[CS_TVIB * M + c], co);
-  for (int o = 0; o < NOBJ; ++o) {
-    double lf[NOWN];
-    for (int f = 0; f < NOWN; ++f) lf[f] = csum[((int64_t)o * NOWN + f) * M + c];
-    cell_reverse(gas, c, M, o, lf, co, cons, lmom, gcell);
-  }
-}
-
-// ---- K4: moments reversed, mass-flow source, bin undone -----------------------
-__global__ __launch_bounds__(256) void k_adj_moments(GridP g, TapeP T, int64_t cap,
-                                                     const double* __restrict__ lam1,
-                                                     const double* __restrict__ lmom,
-                                                     double* __restrict__ lam_out, double w_mdot) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t M = g.M;
-  if (i >= T.offsets[M]) return;
-  const int32_t c = T.cell[i];
-  const double* cs = T.cs;
-  const double N = (double)(T.offsets[c + 1] - T.offsets[c]);
-  const double d[3] = {T.cx[i] - cs[CS_UX * M + c], T.cy[i] - cs[CS_UY * M + c],
-                       T.cz[i] - cs[CS_UZ * M + c]};
-  const int32_t j = T.perm[i];
-  if (j < 0) return;
-  for (int o = 0; o < NOBJ; ++o) {
-    const double* lm = lmom + (int64_t)o * NAMOM * M;
-    double lP[6];
-    for (int k = 0; k < 6; ++k) lP[k] = lm[(AM_P + k) * M + c];
-    // Pi = <C C>: xx yy zz xy xz yz
-    const double gP[3] = {2.0 * d[0] * lP[0] + d[1] * lP[3] + d[2] * lP[4],
-                          2.0 * d[1] * lP[1] + d[0] * lP[3] + d[2] * lP[5],
-                          2.0 * d[2] * lP[2] + d[0] * lP[4] + d[1] * lP[5]};
-    for (int k = 0; k < 3; ++k) {
-      double v = lam_at(const_cast<double*>(lam1), o, LCX + k, cap, i) +
-                 (lm[(AM_U + k) * M + c] + gP[k]) / N;
-      if (o == 0 && k == 0) v += w_mdot;
-      lam_at(lam_out, o, LCX + k, cap, j) = v;
-    }
-    lam_at(lam_out, o, LE, cap, j) =
-        lam_at(const_cast<double*>(lam1), o, LE, cap, i) + lm[AM_EROT * M + c] / N;
-    lam_at(lam_out, o, LY, cap, j) = lam_at(const_cast<double*>(lam1), o, LY, cap, i);
-  }
-}
-
-// ---- K5: parameter partials summed in a fixed order -------------------------
-__global__ __launch_bounds__(256) void k_adj_grad(int64_t M, const double* __restrict__ gcell,
-                                                  double* __restrict__ grad) {
-  __shared__ double red[256];
-  for (int q = 0; q < NOBJ * NPAR; ++q) {
-    double s = 0.0;
-    for (int64_t c = threadIdx.x; c < M; c += 256) s += gcell[(int64_t)q * M + c];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) grad[q] += red[0];
-    __syncthreads();
-  }
-}
+static_assert(NOBJ * NPAR <= ADJ_WAVES, "a wave per parameter partial");
 
 static hipError_t adjoint_step(const GridP& g, const GasP& gas, const BcP& bc, double alpha_vss,
                                double dt, const TapeP& T, int64_t cap, uint64_t seed,
@@ -781,22 +763,16 @@ static hipError_t adjoint_step(const GridP& g, const GasP& gas, const BcP& bc, d
                                double w_mdot, double w_tau, double* grad, char* aws,
                                const AdjWsLayout& W, hipStream_t st) {
   double* lam1 = (double*)(aws + W.lam1);
-  double* own = (double*)(aws + W.own);
-  double* nbr = (double*)(aws + W.nbr);
-  int32_t* nbrc = (int32_t*)(aws + W.nbrc);
   double* cons = (double*)(aws + W.cons);
-  double* lmom = (double*)(aws + W.lmom);
-  double* gcell = (double*)(aws + W.gcell);
-  const int cells = (int)cdiv(g.M, 4);
-  const int parts = (int)cdiv(cap, 256);
-  k_adj_flight_conserve<<<cells, 256, 0, st>>>(g, gas, bc, dt, T, cap, lam_in, lam1, cons, w_tau);
-  k_adj_collide<<<parts, 256, 0, st>>>(g, gas, T, cap, seed, (uint32_t)step, lam1, own, nbr, nbrc);
   double* csum = (double*)(aws + W.csum);
-  k_adj_cell_sums<<<(int)cdiv((int64_t)NOBJ * NOWN * g.M, 4), 256, 0, st>>>(g.M, T, cap, own, nbr,
-                                                                            nbrc, csum);
-  k_adj_cellstate<<<(int)cdiv(g.M, 64), 64, 0, st>>>(g, gas, alpha_vss, T, csum, cons, lmom, gcell);
-  k_adj_moments<<<parts, 256, 0, st>>>(g, T, cap, lam1, lmom, lam_out, w_mdot);
-  k_adj_grad<<<1, 256, 0, st>>>(g.M, gcell, grad);
+  double* gcell = (double*)(aws + W.gcell);
+  unsigned int* done = (unsigned int*)(aws + W.done);
+  const int cells = (int)g.M;
+  k_adj_flight_conserve<<<cells, ADJ_BLOCK, 0, st>>>(g, gas, bc, dt, T, cap, lam_in, lam1, cons,
+                                                     w_tau, done);
+  k_adj_collide<<<K2_PARTS * cells, K2_BLOCK, 0, st>>>(g, gas, T, cap, seed, (uint32_t)step, lam1, csum);
+  k_adj_moments<<<cells, ADJ_BLOCK, 0, st>>>(g, gas, alpha_vss, T, cap, lam1, csum, cons, lam_out,
+                                             w_mdot, gcell, grad, done);
   return hipGetLastError();
 }
 
@@ -850,13 +826,12 @@ usp_status usp_step_taped(const usp_grid* grid, const usp_gas* gas, const usp_bc
     return USP_EINVAL;
   const GridP g = make_grid(grid);
   const TapeLayout T = tape_layout(g.M, cap);
-  const AdjWsLayout W = adj_ws_layout(g.M, cap);
   const WsLayout L = ws_layout(g.M, cap, n_faces(g));
   hipStream_t st = (hipStream_t)stream;
   const hipError_t e = step_taped(g, make_gas(gas), make_bc(bc), dt, make_parts<double>(p),
                                   make_parts<double>(p_alt), offsets, in_offsets, mom, cs,
                                   (char*)ws, L, seed,
-                                  step, (char*)tape, T, (int32_t*)((char*)aws + W.map), counters, st);
+                                  step, (char*)tape, T, counters, st);
   if (e != hipSuccess) return USP_EDEVICE;
   const usp_particles tmp = *p;
   *p = *p_alt;

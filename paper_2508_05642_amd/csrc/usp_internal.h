@@ -260,6 +260,25 @@ template <typename S>
 hipError_t launch_inject(const GridP& g, const GasP& gas, const BcP& bc, double dt,
                          const PartP<S>& p, uint64_t seed, uint64_t step, char* ws,
                          const WsLayout& L, int64_t* counters, hipStream_t st);
+// Where the particle phase of a taped step (FP64) keeps, per slot, the binned
+// state, the velocity and rotational energy after the collision, the state
+// after the conservation and the y velocity after the flight.
+struct TapeOut {
+  double *y, *cx, *cy, *cz, *erot;
+  uint8_t* vib;
+  int32_t* cell;
+  uint32_t* pid;
+  double *ccx, *ccy, *ccz, *cerot;
+  double *kcx, *kcy, *kcz, *kerot;
+  uint8_t* kvib;
+  double* fcy;
+};
+// launch_update (in_step, gathering, USP-FPM per particle) that fills a tape.
+hipError_t launch_update_taped(const GridP& g, const GasP& gas, const BcP& bc, double dt,
+                               const double* cs, const int64_t* offsets, const PartP<double>& p,
+                               uint64_t seed, uint64_t step, char* ws, const WsLayout& L,
+                               int64_t* counters, hipStream_t st, const PartP<double>& src,
+                               const uint32_t* gather_perm, const TapeOut& tape);
 // Grids whose particle phase takes one cell a workgroup (at most one on a
 // CU).
 inline bool update_solo(const GridP& g) { return g.M <= 256; }

@@ -17,6 +17,8 @@
 // place in global memory.  The arithmetic is that of the separate phase
 // kernels (shared device functions), in the same order, so the result is
 // bit-identical to running them one after the other.
+#include <type_traits>
+
 #include "usp_tile.h"
 
 namespace usp {
@@ -164,6 +166,9 @@ __device__ __forceinline__ void tile_gather(const GridP& g, const PartP<S>& src,
   __syncthreads();
 }
 
+// The particle phase that keeps no tape.
+struct NoTape {};
+
 // The three phases of one tile; st = LDS stage or the particle arrays.
 // With G the stage (or, for a tile past the stage, the arrays of p) was
 // filled by the gather prologue, so phase A updates it in place; with POS
@@ -178,7 +183,7 @@ __device__ __forceinline__ void tile_gather(const GridP& g, const PartP<S>& src,
 // (200 cells of 1000: 13.5 -> 7.7 thousand cycles for B).  In the many-cell
 // kernel the pass in place is even, and reading scalars back cost 0.6 to 2%.
 template <typename S, bool STAGED, int CAP, int MODE, bool G, bool POS, int BLOCK,
-          bool ALONE>
+          bool ALONE, typename TP>
 __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const BcP& bc,
                                           double dt, const double* __restrict__ cs,
                                           const int64_t* __restrict__ offsets, const PartP<S>& p,
@@ -186,7 +191,8 @@ __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const
                                           const Stage<S>& st, const PosStage<S>& ps,
                                           ConsScalars* cons, uint16_t* esc_list, int* nesc,
                                           uint64_t seed, uint32_t step, bool advect,
-                                          int64_t* counters, WgCounters wc) {
+                                          int64_t* counters, WgCounters wc, const TP& tape) {
+  constexpr bool TAPE = !std::is_same<TP, NoTape>::value;
   // A: inputs from the stage the gather filled, or from the arrays of p
   // (in place when the tile is past the stage)
   constexpr bool SAME = !STAGED || G;
@@ -212,6 +218,14 @@ __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const
       if (c >= 0) {
         const PartPos<S> q = POS ? ps.load(i) : load_pos(p, i, g.dim);
         o = update_first<MODE>(gl, gas, csl, q, c, in, seed, step, &ev, &esc);
+      }
+      if constexpr (TAPE) {
+        const PartPos<S> q = POS ? ps.load(i) : load_pos(p, i, g.dim);
+        tape.y[i] = q.y; tape.pid[i] = q.pid; tape.cell[i] = c;
+        tape.cx[i] = in.cx; tape.cy[i] = in.cy; tape.cz[i] = in.cz; tape.erot[i] = in.erot;
+        tape.vib[i] = (uint8_t)in.vib;
+        const PartNew<S> w = o.changed ? o : in;
+        tape.ccx[i] = w.cx; tape.ccy[i] = w.cy; tape.ccz[i] = w.cz; tape.cerot[i] = w.erot;
       }
       if (esc) esc_list[atomicAdd(nesc, 1)] = (uint16_t)(i - cb);
       else if (o.changed) st.store(i, o);
@@ -261,6 +275,10 @@ __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const
     if constexpr (SOLO) {
       if (c >= 0) cons_apply<S, S>(*cons, 0, &v.cx, &v.cy, &v.cz, &v.erot);
     }
+    if constexpr (TAPE) {
+      tape.kcx[i] = v.cx; tape.kcy[i] = v.cy; tape.kcz[i] = v.cz; tape.kerot[i] = v.erot;
+      tape.kvib[i] = (uint8_t)v.vib;
+    }
     if (advect && c >= 0) {
       const PartPos<S> q = POS ? ps.load(i) : load_pos(p, i, g.dim);
       advect_one<S, POS>(g, gas, bc, dt, p, i, q, v.cx, v.cy, v.cz, v.erot, v.vib, seed, step,
@@ -274,10 +292,11 @@ __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const
         p.pid[i] = q.pid;
       }
     }
+    if constexpr (TAPE) tape.fcy[i] = p.cy[i];  // this thread's own store
   }
 }
 
-template <typename S, int MODE, bool G, int BLOCK, bool ALONE>
+template <typename S, int MODE, bool G, int BLOCK, bool ALONE, bool WALL, typename TP>
 __global__ __launch_bounds__(BLOCK, 4) void k_update(GridP g, GasP gas, BcP bc, double dt,
                                                      const double* __restrict__ cs,
                                                      const int64_t* __restrict__ offsets,
@@ -285,7 +304,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_update(GridP g, GasP gas, BcP bc, 
                                                      PartP<S> p, uint64_t seed, uint32_t step,
                                                      int advect, int64_t* counters, PartP<S> src,
                                                      const uint32_t* __restrict__ perm,
-                                                     double* stencils) {
+                                                     double* stencils, TP tape) {
   constexpr int CAP = UpdCfg<S>::STAGE;
   constexpr int PCAP = G ? CAP : 1;
   __shared__ S scx[CAP], scy[CAP], scz[CAP], ser[CAP];
@@ -305,6 +324,16 @@ __global__ __launch_bounds__(BLOCK, 4) void k_update(GridP g, GasP gas, BcP bc, 
     // reader is this workgroup, past the first barrier of the gather or of A)
     if (stencils && threadIdx.x == 0) stencil_cell(g, stencils, c0);
   }
+  // WALL: the wall sums of a channel cell.  Every hit of the launch would add
+  // its nine quantities to the same two elements in memory; the workgroup's
+  // hits meet in LDS first (integer sums: the same totals).  (A variant of
+  // its own: redirecting the pointer at run time cost the channel 10%.)
+  __shared__ unsigned long long wall[WALL ? 2 * USP_SURF_NQ : 1];
+  unsigned long long* const surf = bc.surf;
+  if constexpr (WALL) {
+    if (threadIdx.x < 2 * USP_SURF_NQ) wall[threadIdx.x] = 0ull;  // barriers ahead of the flight
+    bc.surf = wall;
+  }
   const int64_t i0 = offsets[c0], i1 = offsets[c1];
   wg_counters_init(wcnt);  // ordered before use by the first barrier of A
   const WgCounters wc{counters ? wcnt : nullptr};
@@ -315,21 +344,25 @@ __global__ __launch_bounds__(BLOCK, 4) void k_update(GridP g, GasP gas, BcP bc, 
     st.cx = scx; st.cy = scy; st.cz = scz; st.erot = ser; st.vib = svb; st.base = i0;
     if constexpr (G) {
       tile_gather<S, true, BLOCK>(g, src, perm, p, i0, i1, st, ps);
-      tile_pass<S, true, CAP, MODE, G, true, BLOCK, ALONE>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st, ps,
+      tile_pass<S, true, CAP, MODE, G, true, BLOCK, ALONE, TP>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st, ps,
                                             &cons, esc_list, &nesc, seed, step, advect != 0, counters,
-                                            wc);
+                                            wc, tape);
     } else {
-      tile_pass<S, true, CAP, MODE, G, false, BLOCK, ALONE>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st,
+      tile_pass<S, true, CAP, MODE, G, false, BLOCK, ALONE, TP>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1, st,
                                              ps, &cons, esc_list, &nesc, seed, step, advect != 0,
-                                             counters, wc);
+                                             counters, wc, tape);
     }
   } else {
     if constexpr (G) tile_gather<S, false, BLOCK>(g, src, perm, p, i0, i1, global_stage(p), ps);
-    tile_pass<S, false, CAP, MODE, G, false, BLOCK, ALONE>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1,
+    tile_pass<S, false, CAP, MODE, G, false, BLOCK, ALONE, TP>(g, gas, bc, dt, cs, offsets, p, c0, c1, i0, i1,
                                             global_stage(p), ps, &cons, esc_list, &nesc, seed, step,
-                                            advect != 0, counters, wc);
+                                            advect != 0, counters, wc, tape);
   }
   __syncthreads();
+  if constexpr (WALL) {
+    if (threadIdx.x < 2 * USP_SURF_NQ && wall[threadIdx.x])
+      atomicAdd(surf + threadIdx.x, wall[threadIdx.x]);
+  }
   wg_counters_flush(wcnt, counters);
 }
 
@@ -344,6 +377,41 @@ hipError_t launch_tiles(const int64_t* offsets, int64_t M, int64_t T, int64_t nt
   return hipGetLastError();
 }
 
+// The launch of the particle phase itself (variants by workgroup shape).
+template <typename S, int MODE, bool G, typename TP>
+static void update_kernel(const GridP& g, const GasP& gas, const BcP& bc, double dt,
+                          const double* cs, const int64_t* offsets, const int32_t* first,
+                          int64_t ntiles, const PartP<S>& p, uint64_t seed, uint64_t step,
+                          int64_t* counters, hipStream_t st, const PartP<S>& src,
+                          const uint32_t* perm, double* stencils, const TP& tape) {
+  const uint32_t s32 = (uint32_t)step;
+  const int adv = g.dim != 0 ? 1 : 0;
+#define USP_K_LAUNCH(BLOCK, ALONE, WALL, NB)                                                       \
+  k_update<S, MODE, G, BLOCK, ALONE, WALL, TP><<<NB, BLOCK, 0, st>>>(                               \
+      g, gas, bc, dt, cs, offsets, first, p, seed, s32, adv, counters, src, perm, stencils, tape)
+  if (!update_solo(g)) {
+    USP_K_LAUNCH(KU_BLOCK, false, false, ntiles);
+    return;
+  }
+  const bool wide = p.capacity > KU_BLOCK * g.M;
+  if constexpr (MODE == MODE_USP && G && std::is_same<TP, NoTape>::value) {
+    if (g.dim == 1 && bc.surf) {
+      if (wide) USP_K_LAUNCH(KU_WIDE, true, true, g.M);
+      else USP_K_LAUNCH(KU_BLOCK, true, true, g.M);
+      return;
+    }
+  }
+  if (wide) USP_K_LAUNCH(KU_WIDE, true, false, g.M);
+  else USP_K_LAUNCH(KU_BLOCK, true, false, g.M);
+#undef USP_K_LAUNCH
+}
+
+// (the cell state is an input; the stencil words of an update_solo grid are
+// finished in place)
+static double* own_stencils(const GridP& g, const double* cs, bool in_step) {
+  return in_step && update_solo(g) && g.dim != 0 ? const_cast<double*>(cs) : nullptr;
+}
+
 template <typename S>
 hipError_t launch_update(const GridP& g, const GasP& gas, const BcP& bc, double dt,
                          const double* cs, const int64_t* offsets, const PartP<S>& p,
@@ -356,41 +424,43 @@ hipError_t launch_update(const GridP& g, const GasP& gas, const BcP& bc, double 
   const int64_t T = update_tile(UpdCfg<S>::STAGE, p.capacity, g.M);
   const int64_t ntiles = update_ntiles(UpdCfg<S>::STAGE, p.capacity, g.M);
   int32_t* first = (int32_t*)(ws + L.tiles);
-  const bool solo = update_solo(g), wide = p.capacity > KU_BLOCK * g.M;
-  // (the cell state is an input; its stencil words are finished in place)
-  double* stencils = in_step && solo && g.dim != 0 ? const_cast<double*>(cs) : nullptr;
-  if (!in_step && !solo && launch_tiles(offsets, g.M, T, ntiles, first, st, UpdCfg<S>::STAGE) != hipSuccess)
+  if (!in_step && !update_solo(g) &&
+      launch_tiles(offsets, g.M, T, ntiles, first, st, UpdCfg<S>::STAGE) != hipSuccess)
     return hipGetLastError();
-  const uint32_t s32 = (uint32_t)step;
-  const int adv = g.dim != 0 ? 1 : 0;
   const int mode = update_mode(gas);
   const PartP<S> sp = src ? *src : p;
+  double* stencils = own_stencils(g, cs, in_step);
   if (ev_begin && hipEventRecord(ev_begin, st) != hipSuccess) return hipGetLastError();
-#define USP_K_LAUNCH(MODE, G, PERM, BLOCK, ALONE, NB)                                              \
-  k_update<S, MODE, G, BLOCK, ALONE><<<NB, BLOCK, 0, st>>>(g, gas, bc, dt, cs, offsets, first, p,  \
-                                                           seed, s32, adv, counters, sp, PERM,     \
-                                                           stencils)
-#define USP_K_UPDATE(MODE, G, PERM)                                                                \
-  do {                                                                                             \
-    if (solo && wide) USP_K_LAUNCH(MODE, G, PERM, KU_WIDE, true, g.M);                             \
-    else if (solo) USP_K_LAUNCH(MODE, G, PERM, KU_BLOCK, true, g.M);                               \
-    else USP_K_LAUNCH(MODE, G, PERM, KU_BLOCK, false, ntiles);                                     \
-  } while (0)
+#define USP_K_UPDATE(MODE, G)                                                                   \
+  update_kernel<S, MODE, G>(g, gas, bc, dt, cs, offsets, first, ntiles, p, seed, step, counters, \
+                            st, sp, gather_perm, stencils, NoTape{})
   if (gather_perm) {
-    if (mode == MODE_FPM) USP_K_UPDATE(MODE_FPM, true, gather_perm);
-    else if (mode == MODE_CELL) USP_K_UPDATE(MODE_CELL, true, gather_perm);
-    else USP_K_UPDATE(MODE_USP, true, gather_perm);
+    if (mode == MODE_FPM) USP_K_UPDATE(MODE_FPM, true);
+    else if (mode == MODE_CELL) USP_K_UPDATE(MODE_CELL, true);
+    else USP_K_UPDATE(MODE_USP, true);
   } else {
-    if (mode == MODE_FPM) USP_K_UPDATE(MODE_FPM, false, nullptr);
-    else if (mode == MODE_CELL) USP_K_UPDATE(MODE_CELL, false, nullptr);
-    else USP_K_UPDATE(MODE_USP, false, nullptr);
+    if (mode == MODE_FPM) USP_K_UPDATE(MODE_FPM, false);
+    else if (mode == MODE_CELL) USP_K_UPDATE(MODE_CELL, false);
+    else USP_K_UPDATE(MODE_USP, false);
   }
 #undef USP_K_UPDATE
-#undef USP_K_LAUNCH
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && ev_end) e = hipEventRecord(ev_end, st);
   if (e != hipSuccess || g.dim == 0) return e;
   return launch_inject<S>(g, gas, bc, dt, p, seed, step, ws, L, counters, st);
+}
+
+hipError_t launch_update_taped(const GridP& g, const GasP& gas, const BcP& bc, double dt,
+                               const double* cs, const int64_t* offsets, const PartP<double>& p,
+                               uint64_t seed, uint64_t step, char* ws, const WsLayout& L,
+                               int64_t* counters, hipStream_t st, const PartP<double>& src,
+                               const uint32_t* gather_perm, const TapeOut& tape) {
+  update_kernel<double, MODE_USP, true>(g, gas, bc, dt, cs, offsets,
+                                        (const int32_t*)(ws + L.tiles),
+                                        update_ntiles(UPDATE_STAGE_F64, p.capacity, g.M), p, seed,
+                                        step, counters, st, src, gather_perm,
+                                        own_stencils(g, cs, true), tape);
+  return hipGetLastError();
 }
 
 template hipError_t launch_update<float>(const GridP&, const GasP&, const BcP&, double,
