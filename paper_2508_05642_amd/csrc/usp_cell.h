@@ -31,18 +31,34 @@ __device__ __forceinline__ MomIn<PS> mom_load(const PS* cx, const PS* cy, const 
   return MomIn<PS>{cx[i], cy[i], cz[i], er[i], (uint32_t)vb[i]};
 }
 
+// (Every product of the sums and of the moments is fused explicitly: the
+// kernels that form a cell's moments in one order then agree bit for bit,
+// whatever the compiler would contract around them.)
+__device__ __forceinline__ double mom_sq(double d0, double d1, double d2) {
+#pragma clang fp contract(off)
+  return __builtin_fma(d2, d2, __builtin_fma(d0, d0, d1 * d1));
+}
+
 template <typename PS>
 __device__ __forceinline__ void mom_add(const MomIn<PS>& a, double r0, double r1, double r2,
                                         double* s) {
-  const double d0 = (double)a.c0 - r0, d1 = (double)a.c1 - r1, d2 = (double)a.c2 - r2;
+#pragma clang fp contract(off)
+  const double d[3] = {(double)a.c0 - r0, (double)a.c1 - r1, (double)a.c2 - r2};
   const double e = (double)a.e, I = (double)a.I;
-  const double q = d0 * d0 + d1 * d1 + d2 * d2;
-  s[0] += d0; s[1] += d1; s[2] += d2;
-  s[3] += d0 * d0; s[4] += d1 * d1; s[5] += d2 * d2;
-  s[6] += d0 * d1; s[7] += d0 * d2; s[8] += d1 * d2;
-  s[9] += q * d0; s[10] += q * d1; s[11] += q * d2;
-  s[12] += e; s[13] += d0 * e; s[14] += d1 * e; s[15] += d2 * e;
-  s[16] += I; s[17] += d0 * I; s[18] += d1 * I; s[19] += d2 * I;
+  const double q = mom_sq(d[0], d[1], d[2]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    s[k] += d[k];
+    s[3 + k] = __builtin_fma(d[k], d[k], s[3 + k]);
+    s[9 + k] = __builtin_fma(q, d[k], s[9 + k]);
+    s[13 + k] = __builtin_fma(d[k], e, s[13 + k]);
+    s[17 + k] = __builtin_fma(d[k], I, s[17 + k]);
+  }
+  s[6] = __builtin_fma(d[0], d[1], s[6]);
+  s[7] = __builtin_fma(d[0], d[2], s[7]);
+  s[8] = __builtin_fma(d[1], d[2], s[8]);
+  s[12] += e;
+  s[16] += I;
 }
 
 constexpr int MOM_LANES = 16;
@@ -91,37 +107,108 @@ __device__ __forceinline__ void row_moments(const PS* cx, const PS* cy, const PS
   moments_from_sums(s, N, r0, r1, r2, v);
 }
 
+// The same 20 sums of a cell by a whole workgroup, for grids too small to
+// fill the chip with a row of 16 lanes a cell: thread
+// (k, sub) = (t / 16, t % 16), t < 320, forms the sum k over the row's
+// particles sub, sub + 16, ... in row_moments' order, so the bits are the
+// same.  The particles' shifted velocities (and |d|^2, e, I) pass through LDS,
+// SC at a time (SC a multiple of 16).  sums[20] (LDS) holds the result for
+// every thread on return.
+template <int SC>
+struct MomStage {
+  double v[6][SC];  // d0, d1, d2, |d|^2, e, I
+  double sums[20];
+};
+constexpr int MOM_THREADS = 20 * MOM_LANES;
+
+template <typename PS, bool G, int BLOCK, int SC>
+__device__ __forceinline__ void block_row_sums(const PS* cx, const PS* cy, const PS* cz,
+                                               const PS* er, const uint8_t* vb, int64_t o0,
+                                               int64_t o1, double r0, double r1, double r2,
+                                               MomStage<SC>* st, const uint32_t* perm = nullptr) {
+#pragma clang fp contract(off)
+  static_assert(BLOCK >= MOM_THREADS && SC % MOM_LANES == 0, "shape of the sums");
+  // factors of sum k: v[xi] times v[yi] (6: one)
+  const int k = threadIdx.x / MOM_LANES, sub = threadIdx.x & (MOM_LANES - 1);
+  int xi, yi;
+  if (k < 3) { xi = k; yi = 6; }
+  else if (k < 6) { xi = k - 3; yi = k - 3; }
+  else if (k < 9) { xi = k == 8 ? 1 : 0; yi = k == 6 ? 1 : 2; }
+  else if (k < 12) { xi = k - 9; yi = 3; }
+  else if (k < 16) { xi = k == 12 ? 4 : k - 13; yi = k == 12 ? 6 : 4; }
+  else { xi = k == 16 ? 5 : k - 17; yi = k == 16 ? 6 : 5; }
+  const double* x = st->v[xi < 6 ? xi : 0];
+  const double* y = st->v[yi < 6 ? yi : 0];
+  double s = 0.0;
+  for (int64_t base = o0; base < o1; base += SC) {
+    const int n = (int)(o1 - base < SC ? o1 - base : SC);
+    for (int j = threadIdx.x; j < n; j += BLOCK) {
+      int64_t i = base + j;
+      if constexpr (G) i = (int64_t)perm[i];
+      const MomIn<PS> a = mom_load<PS>(cx, cy, cz, er, vb, i);
+      const double d0 = (double)a.c0 - r0, d1 = (double)a.c1 - r1, d2 = (double)a.c2 - r2;
+      st->v[0][j] = d0; st->v[1][j] = d1; st->v[2][j] = d2;
+      st->v[3][j] = mom_sq(d0, d1, d2);
+      st->v[4][j] = (double)a.e; st->v[5][j] = (double)a.I;
+    }
+    __syncthreads();
+    if (threadIdx.x < MOM_THREADS) {
+      int j = sub;
+      for (; j + 7 * MOM_LANES < n; j += 8 * MOM_LANES) {
+        double a[8], b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          a[u] = x[j + u * MOM_LANES];
+          b[u] = yi < 6 ? y[j + u * MOM_LANES] : 1.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s = __builtin_fma(a[u], b[u], s);
+      }
+      for (; j < n; j += MOM_LANES) s = __builtin_fma(x[j], yi < 6 ? y[j] : 1.0, s);
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x < MOM_THREADS) {
+    s = row16_sum(s);
+    if (sub == 0) st->sums[k] = s;
+  }
+  __syncthreads();
+}
+
 // The NMOM moments of N particles from their 20 sums shifted by (r0, r1,
 // r2) (the first particle's velocity): the sums of d, d_i d_j, |d|^2 d_i,
 // e, d_i e, I, d_i I of mom_add.
 __device__ __forceinline__ void moments_from_sums(const double s[20], int64_t N, double r0,
                                                   double r1, double r2, double v[NMOM]) {
+#pragma clang fp contract(off)
   if (N == 0) {
 #pragma unroll
     for (int k = 0; k < NMOM; ++k) v[k] = 0.0;
     return;
   }
+  auto fma = [](double a, double b, double c) { return __builtin_fma(a, b, c); };
   const double Nd = (double)N, invN = 1.0 / Nd;
   const double m[3] = {s[0] * invN, s[1] * invN, s[2] * invN};
-  const double Sm[3] = {s[3] * m[0] + s[6] * m[1] + s[7] * m[2],
-                        s[6] * m[0] + s[4] * m[1] + s[8] * m[2],
-                        s[7] * m[0] + s[8] * m[1] + s[5] * m[2]};
-  const double tr = s[3] + s[4] + s[5], mm = m[0] * m[0] + m[1] * m[1] + m[2] * m[2];
+  const double Sm[3] = {fma(s[7], m[2], fma(s[3], m[0], s[6] * m[1])),
+                        fma(s[8], m[2], fma(s[4], m[1], s[6] * m[0])),
+                        fma(s[5], m[2], fma(s[7], m[0], s[8] * m[1]))};
+  const double tr = s[3] + s[4] + s[5], mm = fma(m[2], m[2], fma(m[0], m[0], m[1] * m[1]));
+  const double n2 = 2.0 * Nd * mm;
   v[M_N] = Nd;
-  v[M_UX] = r0 + m[0]; v[M_UY] = r1 + m[1]; v[M_UZ] = r2 + m[2];
-  v[M_PXX] = s[3] * invN - m[0] * m[0];
-  v[M_PYY] = s[4] * invN - m[1] * m[1];
-  v[M_PZZ] = s[5] * invN - m[2] * m[2];
-  v[M_PXY] = s[6] * invN - m[0] * m[1];
-  v[M_PXZ] = s[7] * invN - m[0] * m[2];
-  v[M_PYZ] = s[8] * invN - m[1] * m[2];
+  v[M_UX] = fma(invN, s[0], r0); v[M_UY] = fma(invN, s[1], r1); v[M_UZ] = fma(invN, s[2], r2);
+  v[M_PXX] = fma(s[3], invN, -(m[0] * m[0]));
+  v[M_PYY] = fma(s[4], invN, -(m[1] * m[1]));
+  v[M_PZZ] = fma(s[5], invN, -(m[2] * m[2]));
+  v[M_PXY] = fma(s[6], invN, -(m[0] * m[1]));
+  v[M_PXZ] = fma(s[7], invN, -(m[0] * m[2]));
+  v[M_PYZ] = fma(s[8], invN, -(m[1] * m[2]));
   v[M_EROT] = s[12] * invN;
   v[M_IBAR] = s[16] * invN;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    v[M_QTRX + k] = 0.5 * (s[9 + k] - m[k] * tr - 2.0 * Sm[k] + 2.0 * Nd * mm * m[k]) * invN;
-    v[M_QROTX + k] = (s[13 + k] - m[k] * s[12]) * invN;
-    v[M_QIX + k] = (s[17 + k] - m[k] * s[16]) * invN;
+    v[M_QTRX + k] = 0.5 * fma(m[k], n2, fma(-2.0, Sm[k], fma(-m[k], tr, s[9 + k]))) * invN;
+    v[M_QROTX + k] = fma(-m[k], s[12], s[13 + k]) * invN;
+    v[M_QIX + k] = fma(-m[k], s[16], s[17 + k]) * invN;
   }
 }
 
@@ -283,6 +370,18 @@ __device__ __forceinline__ void store_cell_state(double* cs, int64_t M, int64_t 
   r.collide = v[CS_COLLIDE] != 0.0 ? 1 : 0;
   r.pad = 0;
   cell_records(cs, M)[c] = r;
+}
+
+// Per-cell state of cell c.
+__device__ __forceinline__ void reconstruct_cell(const GridP& g, const GasP& gas, const double* mom,
+                                                 double dt, const double* dt_cell, double* cs,
+                                                 int64_t* counters, int64_t c) {
+  const int64_t M = g.M;
+  double m[NMOM], v[NCS];
+#pragma unroll
+  for (int k = 0; k < NMOM; ++k) m[k] = mom[k * M + c];
+  cell_state(g, gas, m, c, dt_cell ? dt_cell[c] : dt, v, counters);
+  store_cell_state(cs, M, c, v);
 }
 
 }  // namespace usp

@@ -20,72 +20,36 @@ __global__ __launch_bounds__(CELL_BLOCK) void k_moments(GridP g, PartP<S> p, con
   if (valid) store_moments(mom, M, c, sub, v);
 }
 
-// On grids of few cells 16 lanes a cell leave the chip idle: a workgroup of
-// WAVES waves takes a cell (lane i of it the particles i, i + 64 WAVES, ...),
-// the waves' sums are added in wave order, and with `state` one lane goes on
-// to the cell state (a serial chain of some 8 us, for all cells at once),
-// which saves its launch.  200 cells of 1000 particles: 22 + 10 us for the
-// two kernels before, 12 together; 0.7M FP64 particles in 1800 cells: the
-// moments 38 -> 18 us.
-template <typename S, bool G, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void k_moments_wide(GridP g, GasP gas, PartP<S> p,
-                                                             const int64_t* __restrict__ offsets,
-                                                             double* mom,
-                                                             const uint32_t* __restrict__ perm,
-                                                             double dt, const double* dt_cell,
-                                                             double* cs, int64_t* counters,
-                                                             int state) {
-  __shared__ double part[WAVES][20];
+// On grids of few cells 16 lanes a cell leave the chip idle: a workgroup takes
+// a cell (block_row_sums: the bits of k_moments), and with `state` one lane
+// goes on to the cell state (a serial chain of some 4 us, for all cells at
+// once), which saves its launch.  200 cells of 1000 particles: 22 + 10 us for
+// the two kernels before, 14 together; 0.7M FP64 particles in 1800 cells: the
+// moments 38 -> 18 us. (Each lane its own particles in all 20 sums took 12:
+// other bits, which a FP32 state carries on.)
+template <typename S, bool G, int BLOCK, int SC>
+__global__ __launch_bounds__(BLOCK) void k_moments_wide(GridP g, GasP gas, PartP<S> p,
+                                                        const int64_t* __restrict__ offsets,
+                                                        double* mom,
+                                                        const uint32_t* __restrict__ perm,
+                                                        double dt, const double* dt_cell,
+                                                        double* cs, int64_t* counters, int state) {
+  __shared__ MomStage<SC> st;
   const int64_t M = g.M, c = blockIdx.x;
-  const int64_t o0 = offsets[c], o1 = offsets[c + 1], N = o1 - o0;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  auto at = [&](int64_t i) -> int64_t {
-    if constexpr (G) return (int64_t)perm[i];
-    else return i;
-  };
+  const int64_t o0 = offsets[c], o1 = offsets[c + 1];
   double r0 = 0.0, r1 = 0.0, r2 = 0.0;
-  if (N > 0) {
-    const int64_t j = at(o0);
+  if (o1 > o0) {
+    int64_t j = o0;
+    if constexpr (G) j = (int64_t)perm[o0];
     r0 = (double)p.cx[j]; r1 = (double)p.cy[j]; r2 = (double)p.cz[j];
   }
-  double s[20];
+  block_row_sums<S, G, BLOCK, SC>(p.cx, p.cy, p.cz, p.erot, p.vib, o0, o1, r0, r1, r2, &st, perm);
+  if (threadIdx.x >= 64) return;
+  double s[20], v[NMOM];
 #pragma unroll
-  for (int k = 0; k < 20; ++k) s[k] = 0.0;
-  constexpr int STEP = 64 * WAVES;
-  for (int64_t b = o0 + threadIdx.x; b < o1; b += 4 * STEP) {
-    // four slots' loads in flight (a slot past the cell reads the first)
-    int64_t j[4];
-    MomIn<S> a[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) j[u] = at(b + u * STEP < o1 ? b + u * STEP : o0);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) a[u] = mom_load<S>(p.cx, p.cy, p.cz, p.erot, p.vib, j[u]);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (b + u * STEP < o1) mom_add(a[u], r0, r1, r2, s);
-  }
-#pragma unroll
-  for (int k = 0; k < 20; ++k) s[k] = wave_sum(s[k]);
-  if constexpr (WAVES > 1) {
-    if (lane < 20) {
-      double w = 0.0;
-#pragma unroll
-      for (int k = 0; k < 20; ++k)
-        if (k == lane) w = s[k];
-      part[wid][lane] = w;
-    }
-    __syncthreads();
-    if (wid != 0) return;
-#pragma unroll
-    for (int k = 0; k < 20; ++k) {
-      double t = part[0][k];
-#pragma unroll
-      for (int w = 1; w < WAVES; ++w) t += part[w][k];
-      s[k] = t;
-    }
-  }
-  double v[NMOM];
-  moments_from_sums(s, N, r0, r1, r2, v);
+  for (int k = 0; k < 20; ++k) s[k] = st.sums[k];
+  moments_from_sums(s, o1 - o0, r0, r1, r2, v);
+  const int lane = threadIdx.x;
   if (lane < MOM_LANES) store_moments(mom, M, c, lane, v);
   if (state && lane == 0) {
     double w[NCS];
@@ -94,38 +58,26 @@ __global__ __launch_bounds__(64 * WAVES) void k_moments_wide(GridP g, GasP gas, 
   }
 }
 
-// Waves a cell: 0 the 16-lane kernel, which also keeps the 0D grids (the
-// batched solve sums its cells in that order).  The rule looks at the grid
-// alone, so that a state gives the same bits from buffers of any capacity.
-static int moment_waves(const GridP& g) {
-  return g.dim == 0 || g.M > 4096 ? 0 : g.M <= 512 ? 4 : 1;
+// 0: the 16-lane kernel; 1 and 2: a workgroup a cell, of 5 waves, or on the
+// smallest grids of 8 (0D grids keep their two kernels: the cell state of
+// thousands of cells is spread over threads).
+static int moments_shape(const GridP& g) {
+  return g.dim == 0 || g.M > 4096 ? 0 : g.M <= 512 ? 2 : 1;
 }
 
-template <typename S, int WAVES>
+template <typename S, int BLOCK, int SC>
 static hipError_t moments_wide(const GridP& g, const GasP& gas, const PartP<S>& p,
                                const int64_t* offsets, double* mom, double dt,
                                const double* dt_cell, double* cs, int64_t* counters,
                                hipStream_t st, const uint32_t* perm, int state) {
   const int nb = (int)g.M;
   if (perm)
-    k_moments_wide<S, true, WAVES><<<nb, 64 * WAVES, 0, st>>>(g, gas, p, offsets, mom, perm, dt,
-                                                              dt_cell, cs, counters, state);
+    k_moments_wide<S, true, BLOCK, SC><<<nb, BLOCK, 0, st>>>(g, gas, p, offsets, mom, perm, dt,
+                                                             dt_cell, cs, counters, state);
   else
-    k_moments_wide<S, false, WAVES><<<nb, 64 * WAVES, 0, st>>>(g, gas, p, offsets, mom, perm, dt,
-                                                               dt_cell, cs, counters, state);
+    k_moments_wide<S, false, BLOCK, SC><<<nb, BLOCK, 0, st>>>(g, gas, p, offsets, mom, perm, dt,
+                                                              dt_cell, cs, counters, state);
   return hipGetLastError();
-}
-
-// Per-cell state of cell c.
-__device__ __forceinline__ void reconstruct_cell(const GridP& g, const GasP& gas, const double* mom,
-                                                 double dt, const double* dt_cell, double* cs,
-                                                 int64_t* counters, int64_t c) {
-  const int64_t M = g.M;
-  double m[NMOM], v[NCS];
-#pragma unroll
-  for (int k = 0; k < NMOM; ++k) m[k] = mom[k * M + c];
-  cell_state(g, gas, m, c, dt_cell ? dt_cell[c] : dt, v, counters);
-  store_cell_state(cs, M, c, v);
 }
 
 // Per-cell state, one thread per cell.
@@ -204,10 +156,10 @@ hipError_t launch_sample_fields(const GridP& g, const double* mom, double* acc, 
 template <typename S>
 hipError_t launch_moments(const GridP& g, const PartP<S>& p, const int64_t* offsets, double* mom,
                           hipStream_t st, const uint32_t* gather_perm) {
-  const int waves = moment_waves(g);
-  if (waves) {
+  const int shape = moments_shape(g);
+  if (shape) {
     const GasP none{};
-    return (waves == 4 ? moments_wide<S, 4> : moments_wide<S, 1>)(
+    return (shape == 2 ? moments_wide<S, 512, 512> : moments_wide<S, MOM_THREADS, 256>)(
         g, none, p, offsets, mom, 0.0, nullptr, nullptr, nullptr, st, gather_perm, 0);
   }
   const int64_t nb = cdiv(g.M * MOM_LANES, CELL_BLOCK);
@@ -244,12 +196,12 @@ hipError_t launch_cells(const GridP& g, const GasP& gas, const PartP<S>& p, cons
                         double* mom, double dt, const double* dt_cell, double* cs,
                         int64_t* counters, hipStream_t st, const uint32_t* gather_perm,
                         bool stencils) {
-  const int waves = moment_waves(g);
-  if (!waves) {
+  const int shape = moments_shape(g);
+  if (!shape) {
     const hipError_t e = launch_moments<S>(g, p, offsets, mom, st, gather_perm);
     return e != hipSuccess ? e : launch_reconstruct(g, gas, mom, dt, dt_cell, cs, counters, st);
   }
-  const hipError_t e = (waves == 4 ? moments_wide<S, 4> : moments_wide<S, 1>)(
+  const hipError_t e = (shape == 2 ? moments_wide<S, 512, 512> : moments_wide<S, MOM_THREADS, 256>)(
       g, gas, p, offsets, mom, dt, dt_cell, cs, counters, st, gather_perm, 1);
   if (e != hipSuccess) return e;
   return stencils ? launch_stencil(g, gas, cs, st) : launch_cell_coef(g, gas, cs, st);

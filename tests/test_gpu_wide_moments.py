@@ -83,3 +83,22 @@ def test_moments_of_few_cells(M, f32):
     # stencil words of the packed records (byte 60 of 128)
     ra, rb = sa[rec].view(M, 128)[:, 60:64], sb[rec].view(M, 128)[:, 60:64]
     assert torch.equal(ra, rb)
+
+
+@pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("M", [500, 4000])
+def test_wide_sums_keep_the_order_of_rows(M, f32):
+    """A workgroup per cell and a row of 16 lanes per cell add a cell's
+    particles in one order: the same cells in a grid past the rule's line
+    (empty cells appended) give the same bits."""
+    from paper_2508_05642_amd import usp
+    out = []
+    for cells in (M, 4200):
+        prob, parts, cell = _channel(M, f32, 5)
+        prob.grid = W.Grid(dim=1, nx=1, ny=cells, dy=1.0, fnum=1e15, volume=np.ones(cells),
+                           flags=np.zeros(cells, np.uint8))
+        st = usp.DeviceState(prob, parts, capacity=parts["n"] + 64)
+        st.bin()
+        st.do_moments()
+        out.append(st.moments()[:, :M])
+    assert np.array_equal(*out)
