@@ -3,11 +3,21 @@
 //
 // In 0D no particle changes cell and no cell reads a neighbour, so a
 // workgroup that owns a tile of whole cells can run step after step without
-// any grid-wide synchronisation: per step the moments and cell state of its
-// cells (16 lanes per cell), the particle update (thread per particle) and
-// the conservation (wave per cell), all on an LDS stage that holds the
-// tile's velocities, rotational energies and levels from the first step to
-// the last.  Tiles larger than the stage run in place in global memory.
+// any grid-wide synchronisation: per step the moments of its cells (16 lanes
+// or a wave each), their cell state (a thread each), the particle update
+// (thread per particle) and the conservation (wave per cell), all on an LDS
+// stage that holds the tile's velocities, rotational energies and levels
+// from the first step to the last.
+//
+// Bound by the tiles of one or two large cells, in which the update is close
+// to its instruction rate and the sums and the conservation leave waves idle.
+// So the stage takes a cell of 4096 FP32 particles (a cell past the stage
+// runs in place in global memory), 8 waves work on it, a wave shares a large
+// cell's 20 sums out over its lanes, and a tile whose last cell does not fit
+// beside the others runs that cell after them.  Cycles of a step for tiles of
+// 4046 particles: cells 103 -> 68 thousand, update 245 -> 148, conservation
+// 252 -> 47 (4 waves and half the stage before, such tiles in global memory).
+// 4096 cells of 16 to 4096 FP32 particles, 20 steps: 5.29 -> 4.26 ms.
 // Every phase calls the device functions of the step kernels in the same
 // order, so the result is bit-identical to usp_step on the same state.
 #include "usp_tile.h"
@@ -20,8 +30,9 @@ __device__ __forceinline__ void batch_tile(const GridP& g, const GasP& gas, doub
                                            const int64_t* __restrict__ offsets,
                                            const PartP<S>& p, int64_t c0, int64_t c1,
                                            int64_t i0, int64_t i1, const Stage<S>& st,
-                                           uint16_t* esc_list, int* nesc, uint64_t seed,
-                                           uint64_t step0, int nsteps, int64_t* counters,
+                                           uint16_t* esc_list, int* nesc,
+                                           uint64_t seed, uint64_t step0, int nsteps,
+                                           int64_t* counters,
                                            unsigned long long* wcnt) {
   // per-particle events of the update go to the workgroup's counts, which
   // are added to the global counters after every step
@@ -53,112 +64,98 @@ __device__ __forceinline__ void batch_tile(const GridP& g, const GasP& gas, doub
   }
 }
 
-// CAP = stage size (twice the tile window); WPE = waves per SIMD the
-// register budget is held to (what the stage's LDS allows).
-template <typename S, int CAP, int WPE, int MODE>
-__global__ __launch_bounds__(UPD_BLOCK, WPE) void k_batch(GridP g, GasP gas, double dt,
-                                                          const double* dt_cell, double* mom,
-                                                          double* cs,
-                                                          const int64_t* __restrict__ offsets,
-                                                          const int32_t* __restrict__ first,
-                                                          const int32_t* __restrict__ order,
-                                                          PartP<S> p, uint64_t seed,
-                                                          uint64_t step0, int nsteps,
-                                                          int64_t* counters) {
+// Stage sizes (two workgroups' LDS on a CU), and the particles of one round of
+// the update (the FP32 first pass lists its escalations for the second).
+template <typename S> struct BatchCfg;
+template <> struct BatchCfg<float> { static constexpr int STAGE = 4352, ROUND = 2048, ESC = 2048; };
+template <> struct BatchCfg<double> { static constexpr int STAGE = 2304, ROUND = 2304, ESC = 1; };
+
+template <typename S, int MODE>
+__global__ __launch_bounds__(UPD_BLOCK, 4) void k_batch(GridP g, GasP gas, double dt,
+                                                        const double* dt_cell, double* mom,
+                                                        double* cs,
+                                                        const int64_t* __restrict__ offsets,
+                                                        const int32_t* __restrict__ first,
+                                                        const int32_t* __restrict__ order,
+                                                        PartP<S> p, uint64_t seed, uint64_t step0,
+                                                        int nsteps, int64_t* counters) {
+  constexpr int CAP = BatchCfg<S>::STAGE, ROUND = BatchCfg<S>::ROUND;
   __shared__ S scx[CAP], scy[CAP], scz[CAP], ser[CAP];
   __shared__ uint8_t svb[CAP];
-  __shared__ uint16_t esc_list[CAP];
+  __shared__ uint16_t esc_list[BatchCfg<S>::ESC];
   __shared__ int nesc;
   __shared__ unsigned long long wcnt[USP_NCOUNTERS];
   const int64_t t = order[blockIdx.x];
   const int64_t c0 = first[t], c1 = first[t + 1];
   if (c0 >= c1) return;
-  const int64_t i0 = offsets[c0], i1 = offsets[c1];
   wg_counters_init(wcnt);  // ordered before use by the barriers ahead of the first update
-  if (i1 - i0 <= CAP) {
-    Stage<S> st;
-    st.cx = scx; st.cy = scy; st.cz = scz; st.erot = ser; st.vib = svb; st.base = i0;
-    batch_tile<S, true, CAP, MODE>(g, gas, dt, dt_cell, mom, cs, offsets, p, c0, c1, i0, i1, st,
-                             esc_list, &nesc, seed, step0, nsteps, counters, wcnt);
-  } else {
-    batch_tile<S, false, CAP, MODE>(g, gas, dt, dt_cell, mom, cs, offsets, p, c0, c1, i0, i1,
-                              global_stage(p), esc_list, &nesc, seed, step0, nsteps, counters, wcnt);
+  // the cells before the last one start and end within the window, which the
+  // stage holds; the last cell alone may reach past it
+  const int64_t span = offsets[c1] - offsets[c0];
+  const int64_t cut = span <= CAP ? c1 : c1 - 1;
+  for (int64_t a = c0; a < c1;) {
+    const int64_t b = a < cut ? cut : c1;
+    const int64_t i0 = offsets[a], i1 = offsets[b];
+    if (i1 - i0 <= CAP) {
+      Stage<S> st;
+      st.cx = scx; st.cy = scy; st.cz = scz; st.erot = ser; st.vib = svb; st.base = i0;
+      batch_tile<S, true, ROUND, MODE>(g, gas, dt, dt_cell, mom, cs, offsets, p, a, b, i0, i1, st,
+                                       esc_list, &nesc, seed, step0, nsteps, counters, wcnt);
+    } else {
+      batch_tile<S, false, ROUND, MODE>(g, gas, dt, dt_cell, mom, cs, offsets, p, a, b, i0, i1,
+                                        global_stage(p), esc_list, &nesc, seed, step0, nsteps,
+                                        counters, wcnt);
+    }
+    __syncthreads();  // the stage and the counts are free again
+    a = b;
   }
 }
 
 // Dispatch order of a batched launch: the tiles by descending particle
-// count (ties by index), so that the heaviest tiles start first and the
-// launch, in which every workgroup keeps its tile for all its steps, does
-// not end on a heavy tile started late.  One block, a bitonic sort of
-// (count, index) keys in LDS; more than ORDER_MAX tiles keep launch order.
-constexpr int ORDER_MAX = 8192;
+// count, so that the heaviest start first and the launch, in which every
+// workgroup keeps its tile for all its steps, does not end on a heavy tile
+// started late.  Counts are binned (ORDER_BINS bins up to the largest), the
+// order inside a bin is left open (no result depends on it).  One block;
+// a full sort of 3000 tiles took 55 us of a call.
+constexpr int ORDER_BINS = 1024;
 
 __global__ __launch_bounds__(1024) void k_tile_order(const int64_t* __restrict__ offsets,
                                                      const int32_t* __restrict__ first,
                                                      int64_t ntiles, int32_t* order) {
-  __shared__ unsigned long long key[ORDER_MAX];
-  const int n = (int)ntiles;
-  if (ntiles > ORDER_MAX) {
-    for (int64_t t = threadIdx.x; t < ntiles; t += blockDim.x) order[t] = (int32_t)t;
-    return;
-  }
-  int P = 1;
-  while (P < n) P <<= 1;
-  for (int t = threadIdx.x; t < P; t += blockDim.x) {
-    unsigned long long k = ~0ull;  // padding sorts last
-    if (t < n) {
-      const int64_t w = offsets[first[t + 1]] - offsets[first[t]];
-      const uint32_t wc = w > 0xFFFFFFF0LL ? 0xFFFFFFF0u : (uint32_t)w;
-      k = ((unsigned long long)(0xFFFFFFFFu - wc) << 32) | (uint32_t)t;
-    }
-    key[t] = k;
-  }
+  __shared__ unsigned int hist[ORDER_BINS], wsum[16], most;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if (threadIdx.x == 0) most = 0u;
+  hist[threadIdx.x] = 0u;
   __syncthreads();
-  for (int k = 2; k <= P; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int t = threadIdx.x; t < P; t += blockDim.x) {
-        const int u = t ^ j;
-        if (u > t) {
-          const unsigned long long a = key[t], b = key[u];
-          if ((a > b) == ((t & k) == 0)) {
-            key[t] = b;
-            key[u] = a;
-          }
-        }
-      }
-      __syncthreads();
-    }
+  auto count = [&](int64_t t) -> unsigned int {
+    const int64_t w = offsets[first[t + 1]] - offsets[first[t]];
+    return w > 0xFFFFFFFFLL ? 0xFFFFFFFFu : (unsigned int)w;
+  };
+  unsigned int m = 0u;
+  for (int64_t t = threadIdx.x; t < ntiles; t += 1024) {
+    const unsigned int w = count(t);
+    m = w > m ? w : m;
   }
-  for (int t = threadIdx.x; t < n; t += blockDim.x) order[t] = (int32_t)(key[t] & 0xFFFFFFFFull);
-}
-
-template <typename S, int TILE, int WPE>
-static hipError_t batch_launches(const GridP& g, const GasP& gas, double dt,
-                                 const double* dt_cell, double* mom, double* cs,
-                                 const int64_t* offsets, const PartP<S>& p, int spl,
-                                 uint64_t seed, uint64_t step, int nsteps, int32_t* first,
-                                 int64_t* counters, hipStream_t st) {
-  const int64_t ntiles = cdiv(p.capacity, TILE);
-  hipError_t e = launch_tiles(offsets, g.M, TILE, ntiles, first, st);
-  // the order follows first[] in the workspace (sized for 128-slot windows)
-  int32_t* order = first + ntiles + 1;
-  if (e == hipSuccess) {
-    k_tile_order<<<1, 1024, 0, st>>>(offsets, first, ntiles, order);
-    e = hipGetLastError();
+  atomicMax(&most, m);
+  __syncthreads();
+  const unsigned int width = most / ORDER_BINS + 1u;
+  auto bin = [&](int64_t t) { return ORDER_BINS - 1 - (int)(count(t) / width); };
+  for (int64_t t = threadIdx.x; t < ntiles; t += 1024) atomicAdd(&hist[bin(t)], 1u);
+  __syncthreads();
+  // exclusive scan of the bins, a thread each
+  const unsigned int v = hist[threadIdx.x];
+  unsigned int x = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
   }
-  for (int s = 0; s < nsteps && e == hipSuccess; s += spl) {
-    const int k = nsteps - s < spl ? nsteps - s : spl;
-    const int mode = update_mode(gas);
-#define USP_K_BATCH(MODE)                                                                     \
-  k_batch<S, 2 * TILE, WPE, MODE><<<ntiles, UPD_BLOCK, 0, st>>>(                               \
-      g, gas, dt, dt_cell, mom, cs, offsets, first, order, p, seed, step + (uint64_t)s, k, counters)
-    if (mode == MODE_FPM) USP_K_BATCH(MODE_FPM);
-    else if (mode == MODE_CELL) USP_K_BATCH(MODE_CELL);
-    else USP_K_BATCH(MODE_USP);
-#undef USP_K_BATCH
-    e = hipGetLastError();
-  }
-  return e;
+  if (lane == 63) wsum[wid] = x;
+  __syncthreads();
+  unsigned int base = 0u;
+  for (int w = 0; w < wid; ++w) base += wsum[w];
+  hist[threadIdx.x] = base + x - v;
+  __syncthreads();
+  for (int64_t t = threadIdx.x; t < ntiles; t += 1024) order[atomicAdd(&hist[bin(t)], 1u)] = (int32_t)t;
 }
 
 template <typename S>
@@ -167,22 +164,36 @@ hipError_t launch_batch(const GridP& g, const GasP& gas, double dt, const double
                         int tile, int steps_per_launch, uint64_t seed, uint64_t step,
                         int nsteps, char* ws, const WsLayout& L, int64_t* counters,
                         hipStream_t st) {
-  int32_t* first = (int32_t*)(ws + L.tiles);
-  const int spl = steps_per_launch > 0 ? steps_per_launch : (nsteps > 0 ? nsteps : 1);
   if (nsteps <= 0) return hipSuccess;
-  if constexpr (sizeof(S) == 4) {
-    if (tile == 512)
-      return batch_launches<S, 512, 4>(g, gas, dt, dt_cell, mom, cs, offsets, p, spl, seed, step,
-                                       nsteps, first, counters, st);
-    if (tile == 2048)
-      return batch_launches<S, 2048, 2>(g, gas, dt, dt_cell, mom, cs, offsets, p, spl, seed, step,
-                                        nsteps, first, counters, st);
-    return batch_launches<S, 1024, 4>(g, gas, dt, dt_cell, mom, cs, offsets, p, spl, seed, step,
-                                      nsteps, first, counters, st);
-  } else {
-    return batch_launches<S, 512, 4>(g, gas, dt, dt_cell, mom, cs, offsets, p, spl, seed, step,
-                                     nsteps, first, counters, st);
+  int32_t* first = (int32_t*)(ws + L.tiles);
+  const int spl = steps_per_launch > 0 ? steps_per_launch : nsteps;
+  // The window (at most half the stage, so that the cells before a tile's
+  // last one always fit it).  4096 cells of up to 4096 FP32 particles: 512
+  // slots 4.81 ms, 1024 4.48, 1536 4.26, 2048 4.33, 4096 4.74 (short tiles
+  // leave waves idle in the per-cell phases, long ones end in a cell run by
+  // itself).
+  const int64_t window = sizeof(S) == 4 ? (tile > 0 ? tile : 1536) : 512;
+  const int64_t ntiles = cdiv(p.capacity, window);
+  hipError_t e = launch_tiles(offsets, g.M, window, ntiles, first, st);
+  // the order follows first[] in the workspace (sized for 128-slot windows)
+  int32_t* order = first + ntiles + 1;
+  if (e == hipSuccess) {
+    k_tile_order<<<1, 1024, 0, st>>>(offsets, first, ntiles, order);
+    e = hipGetLastError();
   }
+  const int mode = update_mode(gas);
+  for (int s = 0; s < nsteps && e == hipSuccess; s += spl) {
+    const int k = nsteps - s < spl ? nsteps - s : spl;
+#define USP_K_BATCH(MODE)                                                                       \
+  k_batch<S, MODE><<<ntiles, UPD_BLOCK, 0, st>>>(g, gas, dt, dt_cell, mom, cs, offsets, first,    \
+                                                 order, p, seed, step + (uint64_t)s, k, counters)
+    if (mode == MODE_FPM) USP_K_BATCH(MODE_FPM);
+    else if (mode == MODE_CELL) USP_K_BATCH(MODE_CELL);
+    else USP_K_BATCH(MODE_USP);
+#undef USP_K_BATCH
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 template hipError_t launch_batch<float>(const GridP&, const GasP&, double, const double*, double*,

@@ -10,7 +10,7 @@
 
 namespace usp {
 
-constexpr int UPD_BLOCK = 256;
+constexpr int UPD_BLOCK = 512;  // workgroup of a batched tile
 constexpr int UPD_WAVES = UPD_BLOCK / 64;
 
 // Where a tile's velocities, rotational energies and levels live: an LDS
@@ -151,27 +151,86 @@ __device__ __forceinline__ void tile_conserve(const GasP& gas, const double* __r
   }
 }
 
-// Moments and cell state of the cells [c0, c1) from st, 16 lanes per cell
-// (each row of 16 lanes takes every 16th cell); the planes and records go
-// to mom and cs.
+// The 20 sums of a cell by a wave, in row_moments' order: group k < 3 of 16
+// lanes forms the sums that hold d_k (s[k], s[3+k], s[9+k], s[13+k],
+// s[17+k]), group 3 the others (s[6], s[7], s[8], s[12], s[16]), lane sub of
+// each over the particles sub, sub + 16, ....
+template <typename S>
+__device__ __forceinline__ void wave_row_sums(const Stage<S>& st, int64_t o0, int64_t o1, double r0,
+                                              double r1, double r2, double s[20]) {
+#pragma clang fp contract(off)
+  const int lane = threadIdx.x & 63, sub = lane & (MOM_LANES - 1), k = lane / MOM_LANES;
+  const bool own = k < 3;
+  double t[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  auto add = [&](const MomIn<S>& a) {
+    const double d0 = (double)a.c0 - r0, d1 = (double)a.c1 - r1, d2 = (double)a.c2 - r2;
+    const double e = (double)a.e, I = (double)a.I, q = mom_sq(d0, d1, d2);
+    const double A = k == 1 ? d1 : k == 2 ? d2 : d0, D = own ? A : 1.0, B = own ? A : d2;
+    t[0] = __builtin_fma(A, own ? 1.0 : d1, t[0]);
+    t[1] = __builtin_fma(A, B, t[1]);
+    t[2] = __builtin_fma(own ? q : d1, B, t[2]);
+    t[3] = __builtin_fma(D, e, t[3]);
+    t[4] = __builtin_fma(D, I, t[4]);
+  };
+  constexpr int AHEAD = 4;
+  int64_t i = o0 + sub;
+  for (; i + (AHEAD - 1) * MOM_LANES < o1; i += AHEAD * MOM_LANES) {
+    MomIn<S> a[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+      a[u] = mom_load<S>(st.cx, st.cy, st.cz, st.erot, st.vib, i + u * MOM_LANES);
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) add(a[u]);
+  }
+  for (; i < o1; i += MOM_LANES) add(mom_load<S>(st.cx, st.cy, st.cz, st.erot, st.vib, i));
+#pragma unroll
+  for (int j = 0; j < 5; ++j) t[j] = row16_sum(t[j]);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    s[c] = __shfl(t[0], c * MOM_LANES);
+    s[3 + c] = __shfl(t[1], c * MOM_LANES);
+    s[9 + c] = __shfl(t[2], c * MOM_LANES);
+    s[13 + c] = __shfl(t[3], c * MOM_LANES);
+    s[17 + c] = __shfl(t[4], c * MOM_LANES);
+  }
+  s[6] = __shfl(t[0], 48); s[7] = __shfl(t[1], 48); s[8] = __shfl(t[2], 48);
+  s[12] = __shfl(t[3], 48); s[16] = __shfl(t[4], 48);
+}
+
+// Moments and cell state of the cells [c0, c1) from st; the planes and
+// records go to mom and cs.  A row of 16 lanes takes a cell of up to
+// TILE_ROW_MAX particles, a wave a larger one (the same sums in the same
+// order); the cell state follows for all cells at once, a thread each.
+constexpr int TILE_ROW_MAX = 128;
+
 template <typename S>
 __device__ __forceinline__ void tile_cells(const GridP& g, const GasP& gas, double dt,
                                            const double* dt_cell, double* mom, double* cs,
                                            const int64_t* __restrict__ offsets, int64_t c0,
                                            int64_t c1, const Stage<S>& st, int64_t* counters) {
   const int row = threadIdx.x / MOM_LANES, sub = threadIdx.x & (MOM_LANES - 1);
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t M = g.M;
+  int nth = 0;  // the larger cells go to the waves in turn
+  for (int64_t c = c0; c < c1; ++c) {
+    const int64_t o0 = offsets[c] - st.base, o1 = offsets[c + 1] - st.base;
+    if (o1 - o0 <= TILE_ROW_MAX || nth++ % UPD_WAVES != wid) continue;
+    const double r0 = (double)st.cx[o0], r1 = (double)st.cy[o0], r2 = (double)st.cz[o0];
+    double s[20], v[NMOM];
+    wave_row_sums<S>(st, o0, o1, r0, r1, r2, s);
+    moments_from_sums(s, o1 - o0, r0, r1, r2, v);
+    if (lane < MOM_LANES) store_moments(mom, M, c, lane, v);
+  }
   for (int64_t c = c0 + row; c < c1; c += UPD_BLOCK / MOM_LANES) {
     const int64_t o0 = offsets[c] - st.base, o1 = offsets[c + 1] - st.base;
+    if (o1 - o0 > TILE_ROW_MAX) continue;
     double v[NMOM];
     row_moments<S>(st.cx, st.cy, st.cz, st.erot, st.vib, o0, o1, sub, v);
     store_moments(mom, M, c, sub, v);
-    if (sub == 0) {
-      double w[NCS];
-      cell_state(g, gas, v, c, dt_cell ? dt_cell[c] : dt, w, counters);
-      store_cell_state(cs, M, c, w);
-    }
   }
+  __syncthreads();
+  for (int64_t c = c0 + threadIdx.x; c < c1; c += UPD_BLOCK)
+    reconstruct_cell(g, gas, mom, dt, dt_cell, cs, counters, c);
 }
 
 }  // namespace usp
