@@ -166,7 +166,7 @@ struct SortPlan {
 };
 SortPlan sort_plan(int64_t M, int64_t capacity);
 // Which route the bin takes.  An input without segments is sorted (its
-// order is unknown; 3.0M particles in random order: 1.0 ms against 2.2 ms
+// order is unknown; 4.6M particles in random order: 0.46 ms against 2.2 ms
 // through the appended-particle path).  A binned input is sorted on grids of
 // at most SORT_BUCKETS cells (one pass, two launches: 19 against 73 us at
 // 1e5 to 1e6 particles, and moves over any number of cells cost the same)

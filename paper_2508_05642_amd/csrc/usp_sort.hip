@@ -10,7 +10,9 @@
 // of equal digit found by ballots): no atomics on memory, nothing to clear
 // beforehand, and the result does not depend on the launch.  k_sort_place
 // writes the final order, or (buckets) the list of (index, cell) pairs in
-// bucket order, which k_sort_fine orders by cell, a workgroup per bucket.
+// bucket order, which k_sort_fine orders by cell, a workgroup per bucket
+// (moving the particles, recording the order, or, for a large unordered
+// input, recording it for k_sort_fetch).
 #include "usp_binkey.h"
 
 namespace usp {
@@ -490,6 +492,117 @@ __global__ __launch_bounds__(FINE_BLOCK) void k_sort_fine(GridP g, PartP<S> in, 
   }
 }
 
+// An unordered input of many particles in two steps: the buckets only record
+// the order (k_sort_fine<S, true>), then every slot fetches its particle.  A
+// bucket of a shock layer holds seven times the mean, and a workgroup that
+// also fetches its bucket's particles ends long after the others.  The fetch
+// is bound by lines of memory: a word in an array of its own costs a line as
+// much as 16 bytes side by side do, so the words are first laid in packs of
+// the pairs' 16 bytes a particle (free by then), one pack after the other.
+// 4.6M FP32 particles of a shocked cylinder in random order: 1030 us by
+// buckets, 645 fetching one 16-byte pack and four words, 456 in two packs (FP64, four
+// packs: 1157 -> 693).
+constexpr int FETCH_BLOCK = 256;
+constexpr int FETCH_U = 4;
+
+struct alignas(16) SortPack {
+  uint32_t w[4];
+};
+
+// Pack K of a particle: FP32 (cx, cy, cz, erot), (x, y, pid, level); FP64
+// (cx, cy), (cz, erot), (x, y), (pid, level).
+template <typename S>
+constexpr int SORT_PACKS = sizeof(S) == 4 ? 2 : 4;
+
+template <typename S>
+__device__ __forceinline__ void pack_words(SortPack* a, int at, S v) {
+  __builtin_memcpy(&a->w[at * (int)(sizeof(S) / 4)], &v, sizeof(S));
+}
+template <typename S>
+__device__ __forceinline__ S unpack_words(const SortPack& a, int at) {
+  S v;
+  __builtin_memcpy(&v, &a.w[at * (int)(sizeof(S) / 4)], sizeof(S));
+  return v;
+}
+
+template <typename S, int K>
+__global__ __launch_bounds__(FETCH_BLOCK) void k_sort_pack(PartP<S> in, SortPack* pack, bool has_x,
+                                                           bool has_y) {
+  constexpr bool WIDE = sizeof(S) == 8;
+  const int64_t i = (int64_t)blockIdx.x * FETCH_BLOCK + threadIdx.x;
+  if (i >= in.count[0]) return;
+  SortPack a = {};
+  if constexpr (K == 0) {
+    pack_words<S>(&a, 0, in.cx[i]);
+    pack_words<S>(&a, 1, in.cy[i]);
+  }
+  if constexpr (K == (WIDE ? 1 : 0)) {
+    pack_words<S>(&a, WIDE ? 0 : 2, in.cz[i]);
+    pack_words<S>(&a, WIDE ? 1 : 3, in.erot[i]);
+  }
+  if constexpr (K == (WIDE ? 2 : 1)) {
+    if (has_x) pack_words<S>(&a, 0, in.x[i]);
+    if (has_y) pack_words<S>(&a, 1, in.y[i]);
+  }
+  if constexpr (K == SORT_PACKS<S> - 1) {
+    a.w[2] = in.pid[i];
+    a.w[3] = in.vib[i];
+  }
+  pack[i] = a;
+}
+
+template <typename S, int K>
+__global__ __launch_bounds__(FETCH_BLOCK) void k_sort_fetch(PartP<S> out,
+                                                            const SortPack* __restrict__ pack,
+                                                            const uint32_t* __restrict__ perm,
+                                                            bool has_x, bool has_y) {
+  constexpr bool WIDE = sizeof(S) == 8;
+  const int64_t n = out.count[0];
+  const int64_t p0 = (int64_t)blockIdx.x * (FETCH_BLOCK * FETCH_U) + threadIdx.x;
+  if (p0 >= n) return;
+  uint32_t i[FETCH_U];
+  SortPack a[FETCH_U];
+#pragma unroll
+  for (int u = 0; u < FETCH_U; ++u) {
+    const int64_t p = p0 + u * FETCH_BLOCK;
+    i[u] = perm[p < n ? p : p0];
+  }
+#pragma unroll
+  for (int u = 0; u < FETCH_U; ++u) a[u] = pack[i[u]];
+#pragma unroll
+  for (int u = 0; u < FETCH_U; ++u) {
+    const int64_t p = p0 + u * FETCH_BLOCK;
+    if (p >= n) continue;
+    if constexpr (K == 0) {
+      out.cx[p] = unpack_words<S>(a[u], 0);
+      out.cy[p] = unpack_words<S>(a[u], 1);
+    }
+    if constexpr (K == (WIDE ? 1 : 0)) {
+      out.cz[p] = unpack_words<S>(a[u], WIDE ? 0 : 2);
+      out.erot[p] = unpack_words<S>(a[u], WIDE ? 1 : 3);
+    }
+    if constexpr (K == (WIDE ? 2 : 1)) {
+      if (has_x) out.x[p] = unpack_words<S>(a[u], 0);
+      if (has_y) out.y[p] = unpack_words<S>(a[u], 1);
+    }
+    if constexpr (K == SORT_PACKS<S> - 1) {
+      out.pid[p] = a[u].w[2];
+      out.vib[p] = (uint8_t)a[u].w[3];
+    }
+  }
+}
+
+template <typename S, int K = 0>
+static void fetch_packs(const PartP<S>& in, const PartP<S>& out, SortPack* pack,
+                        const uint32_t* perm, bool hx, bool hy, hipStream_t st) {
+  if (!(sizeof(S) == 8 && K == 2 && !hy)) {  // a pack of positions alone
+    k_sort_pack<S, K><<<(int)cdiv(in.capacity, FETCH_BLOCK), FETCH_BLOCK, 0, st>>>(in, pack, hx, hy);
+    k_sort_fetch<S, K><<<(int)cdiv(out.capacity, FETCH_BLOCK * FETCH_U), FETCH_BLOCK, 0, st>>>(
+        out, pack, perm, hx, hy);
+  }
+  if constexpr (K + 1 < SORT_PACKS<S>) fetch_packs<S, K + 1>(in, out, pack, perm, hx, hy, st);
+}
+
 SortPlan sort_plan(int64_t M, int64_t capacity) {
   SortPlan sp;
   sp.shift = 0;
@@ -504,6 +617,14 @@ SortPlan sort_plan(int64_t M, int64_t capacity) {
   sp.self_scan = sp.nchunks * sp.ld <= SORT_SELF_SCAN ? 1 : 0;
   return sp;
 }
+
+// Capacity from which an unordered input is fetched in packs (its 3 or 7 more
+// launches cost 10 to 25 us).  Buckets against packs, capacity 1.6 times the
+// particles: FP32 0.23M particles 50 / 58 us, 0.36M 67 / 71, 0.47M (shocked)
+// 101 / 74, 0.73M 134 / 96; FP64 0.23M 56 / 80, 0.47M 111 / 108, 0.73M 147 /
+// 145, 4.6M 1157 / 693.
+template <typename S>
+constexpr int64_t SORT_FETCH_CAP = sizeof(S) == 4 ? 5 << 17 : 1 << 20;
 
 template <typename S, bool G>
 hipError_t sort_launches(const GridP& g, const PartP<S>& in, const PartP<S>& out, int64_t* offsets,
@@ -528,6 +649,16 @@ hipError_t sort_launches(const GridP& g, const PartP<S>& in, const PartP<S>& out
     k_sort_place<S, G, true><<<nk + 1, SORT_BLOCK, 0, st>>>(g, in, out, key, T, tot, sp, ns, offsets,
                                                         perm, pair_i, pair_c, bucket_off, ti);
     const size_t lds = sizeof(uint32_t) * (size_t)(FINE_WAVES + 1) << sp.shift;
+    if constexpr (!G) {
+      if (!in_offsets && in.capacity >= SORT_FETCH_CAP<S>) {
+        perm = (uint32_t*)(ws + L.perm);
+        k_sort_fine<S, true><<<sp.nb, FINE_BLOCK, lds, st>>>(g, in, out, sp, offsets, perm, pair_i,
+                                                             pair_c, bucket_off, ti);
+        // (the pairs have been read)
+        fetch_packs<S>(in, out, (SortPack*)(ws + L.far), perm, g.dim == 2, g.dim >= 1, st);
+        return hipGetLastError();
+      }
+    }
     k_sort_fine<S, G><<<sp.nb, FINE_BLOCK, lds, st>>>(g, in, out, sp, offsets, perm, pair_i, pair_c,
                                                     bucket_off, ti);
   }

@@ -119,3 +119,44 @@ def test_routes_give_the_same_state(kind, f32, gather):
     assert np.array_equal(oa, ob) and np.array_equal(ma, mb)
     for k in a:
         assert np.array_equal(a[k], b[k]), k
+
+
+# from these capacities an unordered input is fetched in packs of words
+@pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("M,n", [(1025, 0), (1025, 1), (1500, 1023), (1500, 1025), (70001, 90001),
+                                 (1025, 700000)])
+def test_large_unordered_input_is_fetched_in_packs(M, n, f32):
+    cap = max(n, 5 << 17 if f32 else 1 << 20)
+    print(f"[sort bin, packs] M={M} n={n} f32={f32} cap={cap}", flush=True)
+    st, parts = _cells_state(M, n, f32, seed=M + n, cap=cap)
+    cell = parts["cell"]
+    st.bin()
+    _check(st, parts, np.nonzero(cell >= 0)[0], cell)
+
+
+@pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("nx,ny,dim", [(50, 41, 2), (1, 2050, 1)])
+def test_packs_carry_positions(nx, ny, dim, f32):
+    rng = np.random.default_rng(3)
+    n, M = 30011, nx * ny
+    grid = W.Grid(dim=dim, nx=nx, ny=ny, dx=1.0, dy=1.0, fnum=1.0, volume=np.ones(M),
+                  flags=np.zeros(M, np.uint8))
+    prob = W.Problem("cells", W.Gas(), grid, W.BC(kind=(W.BC_PERIODIC,) * 4), dt=1e-8, seed=1, f32=f32)
+    dt = np.float32 if f32 else np.float64
+    ix, iy = rng.integers(0, nx, n), rng.integers(0, ny, n)
+    cell = iy * nx + ix
+    v = {k: rng.standard_normal(n).astype(dt) for k in ("cx", "cy", "cz", "erot")}
+    x = (ix + 0.1 + 0.8 * rng.random(n)).astype(dt) if dim == 2 else None
+    y = (iy + 0.1 + 0.8 * rng.random(n)).astype(dt)
+    cap = 5 << 17 if f32 else 1 << 20
+    parts = dict(n=n, cap=n, x=x, y=y, vib=rng.integers(0, 200, n), cell=cell,
+                 pid=rng.permutation(n).astype(np.uint32), next_pid=n, **v)
+    print(f"[sort bin, packs] dim={dim} f32={f32}", flush=True)
+    st = _usp().DeviceState(prob, parts, capacity=cap)
+    st.bin()
+    _check(st, parts, np.arange(n), cell)
+    order = np.argsort(cell, kind="stable")
+    got = st.state()
+    for k, a in (("x", x), ("y", y)):
+        if a is not None:
+            assert np.array_equal(got[k], a[order].astype(np.float64)), k
