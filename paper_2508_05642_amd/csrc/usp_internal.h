@@ -134,7 +134,7 @@ template <typename S> PartP<S> make_parts(const usp_particles* p);
 
 // workspace layout (byte offsets into the caller's scratch buffer)
 struct WsLayout {
-  size_t key, perm, blocksums, t9, cell_i32, old_off, far_off, far, face_cnt, face_off, misc,
+  size_t key, perm, blocksums, t9, cell_i32, old_off, far_off, far, face_off, misc,
       tiles, chunk_off, chunk_part, cons_scal, sort_t, sort_tot, total;
 };
 // Cells split into chunks for the per-cell reductions (grids whose cells

@@ -46,7 +46,7 @@ size_t noalloc_layout(const GridP& g, int64_t capacity, WsLayout* L) {
   const int nf = n_faces(g);
   size_t o = 0;
   *L = WsLayout{};
-  L->face_cnt = o; o = align256(o + sizeof(int32_t) * (size_t)(nf + 1));
+  o = align256(sizeof(int32_t) * (size_t)(nf + 1));  // unused; keeps the documented limits
   L->face_off = o; o = align256(o + sizeof(int64_t) * (size_t)(nf + 1));
   L->misc = o; o = align256(o + sizeof(int64_t) * 8);
   L->tiles = o; o = align256(o + sizeof(int32_t) * (size_t)(ntiles + 2));
