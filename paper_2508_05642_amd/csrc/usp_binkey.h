@@ -81,14 +81,16 @@ __device__ __forceinline__ void mark_tiles(const TileIndex& ti, uint32_t W, int6
                                            uint32_t o1) {
   if (c == 0) ti.first[0] = 0;
   int64_t hi = o1 / W;
-  if (hi > ti.ntiles) hi = ti.ntiles;
+  if (hi >= ti.ntiles) hi = ti.ntiles - 1;
   for (int64_t t = (int64_t)(o / W) + 1; t <= hi; ++t) ti.first[t] = (int32_t)(c + 1);
 }
 
-// The tiles past the last particle begin at cell M (by `stride` threads).
+// The tiles past the last particle begin at cell M, and so does entry ntiles
+// (by `stride` threads).
 __device__ __forceinline__ void mark_last_tiles(const TileIndex& ti, int64_t W, int64_t M,
                                                 int64_t total, int64_t thread, int64_t stride) {
-  for (int64_t t = total / W + 1 + thread; t <= ti.ntiles; t += stride) ti.first[t] = (int32_t)M;
+  const int64_t past = total / W < ti.ntiles ? total / W + 1 : ti.ntiles;
+  for (int64_t t = past + thread; t <= ti.ntiles; t += stride) ti.first[t] = (int32_t)M;
 }
 
 // U particles i[u] of a lane to the slots p[u] (c[u] < 0: none).  Copied

@@ -34,7 +34,9 @@ __global__ void k_fill_first(int32_t* first, int64_t n, int32_t v) {
 
 // first[t] = the smallest cell c with offsets[c] >= t * T (tiles past the
 // last particle keep the prefilled M): cell c owns the tiles t with
-// offsets[c-1] < t T <= offsets[c].
+// offsets[c-1] < t T <= offsets[c].  first[ntiles] stays M also where the
+// last particle ends the last window: the empty cells behind it are the last
+// tile's.
 __device__ __forceinline__ int64_t tile_window(const int64_t* __restrict__ offsets, int64_t M,
                                                int64_t T, int stage) {
   return stage > 0 ? update_tile(stage, offsets[M], M) : T;
@@ -44,7 +46,7 @@ __device__ __forceinline__ void tile_first(const int64_t* __restrict__ offsets, 
                                            int64_t ntiles, int32_t* first, int64_t c) {
   const int64_t lo = c == 0 ? 0 : offsets[c - 1] / T + 1;
   int64_t hi = offsets[c] / T;
-  if (hi > ntiles) hi = ntiles;
+  if (hi >= ntiles) hi = ntiles - 1;
   for (int64_t t = lo; t <= hi; ++t) first[t] = (int32_t)c;
 }
 

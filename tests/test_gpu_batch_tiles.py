@@ -37,3 +37,28 @@ def test_tiles_equal_step(f32, tile, shift):
     assert a.cnt() == b.cnt()
     assert np.array_equal(a.moments(), b.moments())
     assert np.array_equal(a.cellstate(), b.cellstate())
+
+
+@pytest.mark.parametrize("f32,tile,n", [(True, 0, 1536), (True, 0, 3072), (True, 512, 1024),
+                                        (True, 1024, 2048), (True, 2048, 2048), (False, 0, 1024)])
+def test_empty_cells_past_the_last_window(f32, tile, n):
+    """A full state whose particles end on a window's edge, with empty cells
+    behind them: those cells' averages are written and their skips counted."""
+    from paper_2508_05642_amd import usp
+    counts = np.array([n - 300, 300, 0, 0, 0])
+    prob, parts = W.batch0d(np.maximum(counts, 1), T_tr=[9000.0] * 5, T_rot=[300.0] * 5,
+                            T_vib=[300.0] * 5, dens=np.full(5, 1e23), dt=2e-8, f32=f32)
+    parts = {k: v[:n] if isinstance(v, np.ndarray) else v for k, v in parts.items()}
+    parts["n"] = n
+    print(f"[batch tiles, empty end] f32={f32} tile={tile} n={n}", flush=True)
+    a, b = (usp.DeviceState(prob, parts, capacity=n) for _ in range(2))
+    for st in (a, b):
+        st.bin()
+        st.mom.fill_(-7.0)
+        st.cs.fill_(-7.0)
+    a.step(0, 3)
+    b.batch(0, 3, tile, 2)
+    torch.cuda.synchronize()
+    assert np.array_equal(a.moments(), b.moments())
+    assert np.array_equal(a.cellstate(), b.cellstate())
+    assert a.cnt() == b.cnt()
