@@ -400,7 +400,7 @@ usp_status usp_update(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc
 /* For callers that cannot allocate device memory (code under HIP graph
    capture, tight serving loops, harnesses that forbid allocation): the
    fused particle phase of usp_update with its scratch (the tile index and
-   the injection's face counts, offsets and totals) in a fixed device array
+   the injection's face offsets and totals) in a fixed device array
    of USP_NOALLOC_SCRATCH_BYTES inside the library instead of a caller
    workspace.  Same arguments, results (the same kernels: bit-identical to
    usp_update) and errors as usp_update, less ws and ws_bytes; the call
@@ -410,10 +410,10 @@ usp_status usp_update(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc
    may overlap on one GPU (different streams, or one stream from several
    host threads without ordering) race and must not be issued.  Nothing in
    the array needs to start at zero (every call writes what it reads).
-   Returns USP_ESCRATCH when the grid's faces and the capacity's tile index
-   need more than the array holds (about 2.6e5 tiles: e.g. 4.0e8 particle
-   slots for the cylinder's cells, whose launch bound is a 1527-slot
-   window), USP_EDEVICE when the array's
+   Returns USP_ESCRATCH when the grid's faces (12 bytes each) and the
+   capacity's tile index (4 bytes a tile) need more than the array holds
+   (about 2.6e5 tiles: e.g. 4.0e8 particle slots for the cylinder's cells,
+   whose launch bound is a 1527-slot window), USP_EDEVICE when the array's
    address cannot be found. */
 #define USP_NOALLOC_SCRATCH_BYTES (1 << 20)
 usp_status usp_update_noalloc(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc,

@@ -326,12 +326,16 @@ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // workgroups on each of 256 CUs, one round): the particle phase of 960
 // particles in 16 cells took 21 us as one tile and takes 15 as eight.
 constexpr int64_t UPDATE_TILES = 512;
-__host__ __device__ inline int64_t update_tile(int stage, int64_t n, int64_t M) {
+__host__ __device__ inline int64_t stage_window(int stage, int64_t n, int64_t M) {
   const int64_t ppc = M > 0 ? (n + M - 1) / M : stage;
   int64_t t = stage - ppc - ppc / 2 - ppc / 8;
   const int64_t lo = stage / 8, hi = stage - stage / 8;
   if (t < lo) t = lo;
   if (t > hi) t = hi;
+  return t < UPDATE_TILE_MIN ? UPDATE_TILE_MIN : t;
+}
+__host__ __device__ inline int64_t update_tile(int stage, int64_t n, int64_t M) {
+  int64_t t = stage_window(stage, n, M);
   const int64_t even = (n + UPDATE_TILES - 1) / UPDATE_TILES;
   if (t > even) t = even;
   return t < UPDATE_TILE_MIN ? UPDATE_TILE_MIN : t;

@@ -1,6 +1,6 @@
 // usp_noalloc.hip -- usp_update_noalloc: the fused particle phase of
 // usp_update with its scratch (the tile index and the injection's face
-// counts, offsets and totals) in a fixed device array instead of a caller
+// offsets and totals) in a fixed device array instead of a caller
 // workspace, for callers that cannot allocate device memory.
 #include <mutex>
 
@@ -36,22 +36,29 @@ char* scratch_ptr() {
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // The parts of the workspace layout the fused particle phase uses, packed
-// for this grid and capacity: face counts, face offsets, injection totals,
-// and the tile index of the window update_tile gives.  Returns the bytes
-// needed.
+// for this grid and capacity: face offsets, injection totals and the tile
+// index.  Whether they fit is decided by the documented need, which does not
+// change with the windows in use: 12 bytes a face (a count and an offset),
+// the totals, and the tile index of stage_window's windows.  The arrays never
+// take more than that where it is near the limit: an evenly cut state has at
+// most UPDATE_TILES tiles, 2 KB, and a grid whose faces come near the limit
+// leaves its 4 bytes a face for them.
 template <typename S>
-size_t noalloc_layout(const GridP& g, int64_t capacity, WsLayout* L) {
+bool noalloc_layout(const GridP& g, int64_t capacity, WsLayout* L) {
   const int stage = sizeof(S) == 4 ? UPDATE_STAGE_F32 : UPDATE_STAGE_F64;
-  const int64_t ntiles = update_ntiles(stage, capacity, g.M);
-  const int nf = n_faces(g);
-  size_t o = 0;
+  const size_t nf = (size_t)n_faces(g);
+  const size_t counts = align256(sizeof(int32_t) * (nf + 1));
+  const size_t offs = align256(sizeof(int64_t) * (nf + 1)), misc = align256(sizeof(int64_t) * 8);
+  auto index = [](int64_t ntiles) { return align256(sizeof(int32_t) * (size_t)(ntiles + 2)); };
   *L = WsLayout{};
-  o = align256(sizeof(int32_t) * (size_t)(nf + 1));  // unused; keeps the documented limits
-  L->face_off = o; o = align256(o + sizeof(int64_t) * (size_t)(nf + 1));
-  L->misc = o; o = align256(o + sizeof(int64_t) * 8);
-  L->tiles = o; o = align256(o + sizeof(int32_t) * (size_t)(ntiles + 2));
-  L->total = o;
-  return o;
+  L->face_off = 0;
+  L->misc = offs;
+  L->tiles = offs + misc;
+  L->total = L->tiles + index(update_ntiles(stage, capacity, g.M));
+  const size_t need =
+      counts + offs + misc + index(cdiv(capacity, stage_window(stage, capacity, g.M)));
+  return need <= (size_t)USP_NOALLOC_SCRATCH_BYTES &&
+         L->total <= (size_t)USP_NOALLOC_SCRATCH_BYTES;
 }
 
 template <typename S>
@@ -60,8 +67,7 @@ usp_status noalloc_update(const usp_grid* grid, const usp_gas* gas, const usp_bc
                           uint64_t seed, uint64_t step, int64_t* counters, hipStream_t st) {
   const GridP g = make_grid(grid);
   WsLayout L;
-  if (noalloc_layout<S>(g, p->capacity, &L) > (size_t)USP_NOALLOC_SCRATCH_BYTES)
-    return USP_ESCRATCH;
+  if (!noalloc_layout<S>(g, p->capacity, &L)) return USP_ESCRATCH;
   char* ws = scratch_ptr();
   if (!ws) return USP_EDEVICE;
   const hipError_t e = launch_update<S>(g, make_gas(gas), make_bc(bc), dt, cs, offsets,

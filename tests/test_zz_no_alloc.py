@@ -100,6 +100,24 @@ def test_noalloc_update_fp64_channel():
     _case(prob, parts, 3)
 
 
+@pytest.mark.gpu
+def test_noalloc_takes_the_faces_its_array_holds():
+    """A strip of 43,650 cells: its faces (12 bytes each, as documented) and
+    the tile index of its windows end exactly on the array's last byte."""
+    nx, n = 43650, 20000
+    rng = np.random.default_rng(1)
+    grid = W.Grid(dim=2, nx=nx, ny=1, dx=1.0, dy=1.0, fnum=1e15, volume=np.ones(nx),
+                  flags=np.zeros(nx, np.uint8))
+    prob = W.Problem("strip", W.Gas(), grid, W.BC(kind=(W.BC_PERIODIC,) * 4), dt=1e-4, seed=3, f32=True)
+    x = nx * rng.random(n)
+    v = {k: 300.0 * rng.standard_normal(n) for k in ("cx", "cy", "cz")}
+    parts = dict(n=n, cap=n, x=x, y=rng.random(n), erot=rng.exponential(1e5, n),
+                 vib=rng.integers(0, 3, n), cell=np.floor(x).astype(np.int32),
+                 pid=np.arange(n, dtype=np.uint32), next_pid=n, **v)
+    _say(f"[noalloc] strip of {nx} cells, n={n}")
+    assert _case(prob, parts, 4) == n
+
+
 def test_noalloc_rejects_capacity_beyond_scratch():
     """A capacity whose tile index does not fit the fixed array is rejected
     with USP_ESCRATCH in the host-side checks (the struct's arrays are
