@@ -234,7 +234,7 @@ usp_status do_step(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, d
           hipSuccess)
         return USP_EDEVICE;
       if ((e = launch_update<S>(g, gp, bp, dt, cs, offsets, out, seed, sn, w, L, counters, st, &in,
-                                gperm, nullptr, nullptr, true)) != hipSuccess)
+                                gperm, nullptr, nullptr, cs)) != hipSuccess)
         return USP_EDEVICE;
       const usp_particles tmp = *p;
       *p = *p_alt;
@@ -246,7 +246,7 @@ usp_status do_step(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, d
       return USP_EDEVICE;
     // the first step's tile index stands: nothing has moved
     if ((e = launch_update<S>(g, gp, bp, dt, cs, offsets, q, seed, sn, w, L, counters, st, nullptr,
-                              nullptr, nullptr, nullptr, true)) != hipSuccess)
+                              nullptr, nullptr, nullptr, cs)) != hipSuccess)
       return USP_EDEVICE;
   }
   return USP_OK;

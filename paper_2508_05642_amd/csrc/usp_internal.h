@@ -273,27 +273,28 @@ struct TapeOut {
   uint8_t* kvib;
   double* fcy;
 };
-// launch_update (in_step, gathering, USP-FPM per particle) that fills a tape.
+// launch_update (in a step, gathering, USP-FPM per particle) that fills a
+// tape.
 hipError_t launch_update_taped(const GridP& g, const GasP& gas, const BcP& bc, double dt,
-                               const double* cs, const int64_t* offsets, const PartP<double>& p,
+                               double* cs, const int64_t* offsets, const PartP<double>& p,
                                uint64_t seed, uint64_t step, char* ws, const WsLayout& L,
                                int64_t* counters, hipStream_t st, const PartP<double>& src,
                                const uint32_t* gather_perm, const TapeOut& tape);
 // Grids whose particle phase takes one cell a workgroup (at most one on a
 // CU).
 inline bool update_solo(const GridP& g) { return g.M <= 256; }
-// The fused particle phase (in_step: the tile index is made already, and on
-// update_solo grids the stencils are not) on p (binned), or, with gather_perm, on the
+// The fused particle phase on p (binned), or, with gather_perm, on the
 // particles of `src` in the order gather_perm gives (slot j holds
 // src[gather_perm[j]]), the results written to p (whose cells the
-// gathering bin has set).
+// gathering bin has set).  In a step, step_cs is cs: the tile index is made
+// already, and on update_solo grids the stencil words are still to be.
 template <typename S>
 hipError_t launch_update(const GridP& g, const GasP& gas, const BcP& bc, double dt,
                          const double* cs, const int64_t* offsets, const PartP<S>& p,
                          uint64_t seed, uint64_t step, char* ws, const WsLayout& L,
                          int64_t* counters, hipStream_t st, const PartP<S>* src = nullptr,
                          const uint32_t* gather_perm = nullptr, hipEvent_t ev_begin = nullptr,
-                         hipEvent_t ev_end = nullptr, bool in_step = false);
+                         hipEvent_t ev_end = nullptr, double* step_cs = nullptr);
 // Adds to *found the number of NaN or infinite values among the live
 // particles' floating arrays and, when given, the moment and FP64
 // cell-state planes of the occupied cells.

@@ -171,6 +171,12 @@ __device__ __forceinline__ void tile_gather(const GridP& g, const PartP<S>& src,
 // The particle phase that keeps no tape.
 struct NoTape {};
 
+// The cell state as the particle phase reads it.  A kernel that writes its
+// cell's stencil word there (OWN) must not promise that nothing does: its
+// loads could move over that store.
+template <bool OWN> struct CellIn { using type = const double* __restrict__; };
+template <> struct CellIn<true> { using type = const double*; };
+
 // The three phases of one tile; st = LDS stage or the particle arrays.
 // With G the stage (or, for a tile past the stage, the arrays of p) was
 // filled by the gather prologue, so phase A updates it in place; with POS
@@ -187,7 +193,7 @@ struct NoTape {};
 template <typename S, bool STAGED, int CAP, int MODE, bool G, bool POS, int BLOCK,
           bool ALONE, typename TP>
 __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const BcP& bc,
-                                          double dt, const double* __restrict__ cs,
+                                          double dt, typename CellIn<ALONE>::type cs,
                                           const int64_t* __restrict__ offsets, const PartP<S>& p,
                                           int64_t c0, int64_t c1, int64_t i0, int64_t i1,
                                           const Stage<S>& st, const PosStage<S>& ps,
@@ -300,7 +306,7 @@ __device__ __forceinline__ void tile_pass(const GridP& g, const GasP& gas, const
 
 template <typename S, int MODE, bool G, int BLOCK, bool ALONE, bool WALL, typename TP>
 __global__ __launch_bounds__(BLOCK, 4) void k_update(GridP g, GasP gas, BcP bc, double dt,
-                                                     const double* __restrict__ cs,
+                                                     typename CellIn<ALONE>::type cs,
                                                      const int64_t* __restrict__ offsets,
                                                      const int32_t* __restrict__ first,
                                                      PartP<S> p, uint64_t seed, uint32_t step,
@@ -408,10 +414,10 @@ static void update_kernel(const GridP& g, const GasP& gas, const BcP& bc, double
 #undef USP_K_LAUNCH
 }
 
-// (the cell state is an input; the stencil words of an update_solo grid are
-// finished in place)
-static double* own_stencils(const GridP& g, const double* cs, bool in_step) {
-  return in_step && update_solo(g) && g.dim != 0 ? const_cast<double*>(cs) : nullptr;
+// Where the particle phase of a step finishes the stencil words (update_solo
+// grids).
+static double* own_stencils(const GridP& g, double* step_cs) {
+  return update_solo(g) && g.dim != 0 ? step_cs : nullptr;
 }
 
 template <typename S>
@@ -420,18 +426,18 @@ hipError_t launch_update(const GridP& g, const GasP& gas, const BcP& bc, double 
                          uint64_t seed, uint64_t step, char* ws, const WsLayout& L,
                          int64_t* counters, hipStream_t st, const PartP<S>* src,
                          const uint32_t* gather_perm, hipEvent_t ev_begin, hipEvent_t ev_end,
-                         bool in_step) {
+                         double* step_cs) {
   // the launch covers a full state; the window itself comes from the
   // binned count on the device
   const int64_t T = update_tile(UpdCfg<S>::STAGE, p.capacity, g.M);
   const int64_t ntiles = update_ntiles(UpdCfg<S>::STAGE, p.capacity, g.M);
   int32_t* first = (int32_t*)(ws + L.tiles);
-  if (!in_step && !update_solo(g) &&
+  if (!step_cs && !update_solo(g) &&
       launch_tiles(offsets, g.M, T, ntiles, first, st, UpdCfg<S>::STAGE) != hipSuccess)
     return hipGetLastError();
   const int mode = update_mode(gas);
   const PartP<S> sp = src ? *src : p;
-  double* stencils = own_stencils(g, cs, in_step);
+  double* stencils = own_stencils(g, step_cs);
   if (ev_begin && hipEventRecord(ev_begin, st) != hipSuccess) return hipGetLastError();
 #define USP_K_UPDATE(MODE, G)                                                                   \
   update_kernel<S, MODE, G>(g, gas, bc, dt, cs, offsets, first, ntiles, p, seed, step, counters, \
@@ -453,7 +459,7 @@ hipError_t launch_update(const GridP& g, const GasP& gas, const BcP& bc, double 
 }
 
 hipError_t launch_update_taped(const GridP& g, const GasP& gas, const BcP& bc, double dt,
-                               const double* cs, const int64_t* offsets, const PartP<double>& p,
+                               double* cs, const int64_t* offsets, const PartP<double>& p,
                                uint64_t seed, uint64_t step, char* ws, const WsLayout& L,
                                int64_t* counters, hipStream_t st, const PartP<double>& src,
                                const uint32_t* gather_perm, const TapeOut& tape) {
@@ -461,7 +467,7 @@ hipError_t launch_update_taped(const GridP& g, const GasP& gas, const BcP& bc, d
                                         (const int32_t*)(ws + L.tiles),
                                         update_ntiles(UPDATE_STAGE_F64, p.capacity, g.M), p, seed,
                                         step, counters, st, src, gather_perm,
-                                        own_stencils(g, cs, true), tape);
+                                        own_stencils(g, cs), tape);
   return hipGetLastError();
 }
 
@@ -469,11 +475,11 @@ template hipError_t launch_update<float>(const GridP&, const GasP&, const BcP&, 
                                          const double*, const int64_t*, const PartP<float>&,
                                          uint64_t, uint64_t, char*, const WsLayout&, int64_t*,
                                          hipStream_t, const PartP<float>*, const uint32_t*,
-                                         hipEvent_t, hipEvent_t, bool);
+                                         hipEvent_t, hipEvent_t, double*);
 template hipError_t launch_update<double>(const GridP&, const GasP&, const BcP&, double,
                                           const double*, const int64_t*, const PartP<double>&,
                                           uint64_t, uint64_t, char*, const WsLayout&, int64_t*,
                                           hipStream_t, const PartP<double>*, const uint32_t*,
-                                          hipEvent_t, hipEvent_t, bool);
+                                          hipEvent_t, hipEvent_t, double*);
 
 }  // namespace usp

@@ -1,0 +1,58 @@
+"""usp_step on the routes of its bin and particle phase that the grid, the
+buffer or wall sampling selects, against the other routes."""
+import numpy as np
+import pytest
+
+import usp_workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+def _usp():
+    from paper_2508_05642_amd import usp
+    return usp
+
+
+@pytest.mark.parametrize("f32", [True, False])
+def test_step_reads_this_steps_stencils(f32):
+    """On a grid of at most 256 cells the particle phase makes its cell's
+    stencil word itself.  Half the cells empty out and fill again from step to
+    step, and the records hold other words on entry: the particles are those
+    of the single phases."""
+    usp = _usp()
+    cells = 40
+    rng = np.random.default_rng(4)
+    prob = W.poiseuille(kn=0.05, cells=cells, ppc=30, f32=f32)
+    parts = W.particles_for(prob)
+    n = parts["n"]
+    # clusters of three cells that drift by about a cell a step
+    home = rng.integers(0, cells // 5, n) * 5 + rng.integers(0, 3, n)
+    parts["y"][:n] = (home + 0.05 + 0.9 * rng.random(n)) * prob.grid.dy
+    parts["cy"][:n] = parts["cy"][:n] * 0.2 + prob.grid.dy / prob.dt
+    print(f"[step stencils] f32={f32} n={n}", flush=True)
+    a, b = (usp.DeviceState(prob, parts) for _ in range(2))
+    for k in range(4):
+        for st in (a, b):
+            st.cs.view(torch.uint8).fill_(0x5A)
+        a.step(k)
+        b.bin()
+        b.do_moments()
+        b.do_reconstruct()
+        words = b.cs.view(torch.uint8)[usp.NCS * 8 * cells:].view(-1)[: 128 * cells].view(cells, 128)
+        got = a.cs.view(torch.uint8)[usp.NCS * 8 * cells:].view(-1)[: 128 * cells].view(cells, 128)
+        assert torch.equal(got[:, 60:64], words[:, 60:64])
+        assert len(torch.unique(words[:, 60:64].contiguous().view(torch.int32))) > 1
+        b.collide(k)
+        b.conserve(k)
+        b.advect(k)
+        sa, sb = a.state(), b.state()
+        assert np.array_equal(sa["pid"], sb["pid"]) and np.array_equal(sa["vib"], sb["vib"])
+        v = np.sqrt(prob.gas.R * 300.0)
+        for q in ("cx", "cy", "cz"):
+            assert np.abs(sa[q] - sb[q]).max() <= (1e-5 if f32 else 1e-9) * v, q
+        # go on from one state, so that the steps compare the stencils alone
+        for q in usp.DeviceState.FIELDS:
+            if b.bufs[b.cur][q] is not None:
+                b.bufs[b.cur][q].copy_(a.bufs[a.cur][q])
+        b.bufs[b.cur]["cell"].copy_(a.bufs[a.cur]["cell"])
