@@ -102,3 +102,24 @@ def test_wide_sums_keep_the_order_of_rows(M, f32):
         st.do_moments()
         out.append(st.moments()[:, :M])
     assert np.array_equal(*out)
+
+
+@pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("M", [1, 12, 512, 513, 4096, 4097])
+def test_every_moment_of_few_cells_against_numpy(M, f32):
+    """Each plane by itself against FP64 numpy sums of the stored values: a
+    cell's sums have at most 1300 terms of some ten times the plane's scale,
+    each off by a few 1e-16 of it (1e-12 of the scale in all)."""
+    from paper_2508_05642_amd import usp
+    prob, parts, cell = _channel(M, f32, M + 1)
+    print(f"[wide moments, planes] M={M} n={parts['n']} f32={f32}", flush=True)
+    st = usp.DeviceState(prob, parts, capacity=parts["n"] + 64)
+    st.bin()
+    st.do_moments()
+    m, ref = st.moments(), _numpy_moments(parts, cell, M)
+    assert np.array_equal(m[0], ref[0])
+    c = np.sqrt(prob.gas.R * 3000.0) + 900.0
+    e = c * c
+    scale = np.array([c] * 3 + [e] * 6 + [e, 9.0] + [e * c] * 6 + [9.0 * c] * 3)
+    err = np.abs(m - ref).max(axis=1)[1:]
+    assert np.all(err <= 1e-10 * scale), (err / scale).tolist()
