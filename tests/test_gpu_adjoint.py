@@ -192,3 +192,33 @@ def test_adjoint_equals_central_differences_full_size():
         rel = np.abs(G[:, p] - fd) / np.abs(fd)
         _say(f"  d/d{('Z_rot', 'omega', 'mu_ref')[p]}: adjoint {G[:, p]}, FD {fd}, rel {rel}")
         assert np.all(rel <= 1e-3), (p, G[:, p], fd)
+
+
+@pytest.mark.parametrize("cells,ppc", [(257, 90), (300, 90), (1100, 90), (6, 1300)])
+def test_adjoint_of_every_particle_phase(cells, ppc):
+    """The taped particle phase over tiles (more than 256 cells), with its
+    order from buckets of cells (more than 1024) and in cells past the FP64
+    stage of 1024 slots: the step it makes is usp_step's (the large cells
+    aside, whose step adds its sums by chunks), and the gradient the
+    oracle's.  (No particle's Cholesky test fails on these paths: the oracle's
+    autograd has no value where one does.)"""
+    from paper_2508_05642_amd import usp
+    from paper_2508_05642_amd.adjoint import PathwiseAdjoint
+    prob, parts = _channel(cells=cells, ppc=ppc, seed=13)
+    _say(f"[adjoint, phases] cells={cells} n={parts['n']}")
+    K = 3
+    adj = PathwiseAdjoint(prob, parts, K, 2)
+    if ppc <= 1024:
+        a, b = (usp.DeviceState(prob, parts) for _ in range(2))
+        for k in range(K):
+            a.step(20 + k)
+            b.step_taped(20 + k, adj.tapes[0], adj.aws)
+        sa, sb = a.state(), b.state()
+        for k in sa:
+            if isinstance(sa[k], np.ndarray):
+                assert np.array_equal(sa[k], sb[k]), k
+        assert torch.equal(a.offsets, b.offsets) and a.cnt() == b.cnt()
+    Jo, Go = A.Path(A.Record(prob, parts, 20, K)).gradient()
+    J = adj.forward(20).cpu().numpy()
+    G = adj.backward().cpu().numpy()
+    _compare(J, G, Jo, Go, f"{cells} cells of {ppc}")
