@@ -9,9 +9,41 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+BIG = 9 << 20  # a capacity past the sorted bin's on grids of more than 1024 cells
+
+
 def _usp():
     from paper_2508_05642_amd import usp
     return usp
+
+
+def _same(a, b):
+    sa, sb = a.state(), b.state()
+    assert sa["n"] == sb["n"] and sa["next_pid"] == sb["next_pid"]
+    for k in sa:
+        if isinstance(sa[k], np.ndarray):
+            assert np.array_equal(sa[k], sb[k]), k
+    assert torch.equal(a.offsets, b.offsets) and a.cnt() == b.cnt()
+
+
+@pytest.mark.parametrize("scale,ppc,f32", [(0.2, 30.0, True), (0.2, 220.0, True), (0.26, 90.0, False)])
+def test_step_takes_its_tiles_from_either_bin(scale, ppc, f32):
+    """Four steps whose tile index comes from the neighbour-group bin's scan
+    against four whose tile index comes from the sorted bin: a small state cut
+    evenly (30 a cell) and windows by the mean cell.  (The larger buffer's mean
+    slots per cell stay below the stage, past which cells are split.)"""
+    usp = _usp()
+    prob = W.cylinder(scale=scale, f32=f32, ppc=ppc)
+    parts = W.particles_for(prob)
+    print(f"[step routes] scale={scale} ppc={ppc} f32={f32} n={parts['n']}", flush=True)
+    assert -(-BIG // prob.grid.ncells) <= (2048 if f32 else 1024)
+    a = usp.DeviceState(prob, parts, capacity=int(1.6 * parts["n"]))
+    b = usp.DeviceState(prob, parts, capacity=BIG)
+    for st in (a, b):
+        st.step(0, 1)
+        st.step(1, 3)
+    _same(a, b)
+    assert np.array_equal(a.moments(), b.moments())
 
 
 @pytest.mark.parametrize("f32", [True, False])
