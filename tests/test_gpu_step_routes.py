@@ -47,6 +47,38 @@ def test_step_takes_its_tiles_from_either_bin(scale, ppc, f32):
 
 
 @pytest.mark.parametrize("f32", [True, False])
+def test_unordered_input_of_more_cells_than_the_sort_takes(f32):
+    """2^20 + 3 cells, no segments passed: every particle goes through the
+    claimed slots of the neighbour-group route, a few cells with more than a
+    wave's sort holds among them."""
+    usp = _usp()
+    M, n = (1 << 20) + 3, 60000
+    rng = np.random.default_rng(8)
+    grid = W.Grid(dim=0, nx=M, ny=1, fnum=1.0, volume=np.ones(M), flags=np.zeros(M, np.uint8))
+    prob = W.Problem("cells", W.Gas(), grid, W.BC(), dt=1e-8, seed=1, f32=f32)
+    cell = rng.integers(0, M, n)
+    cell[: n // 2] = rng.integers(0, 3, n // 2) * (M - 1) // 2
+    cell = rng.permutation(cell)
+    cell[rng.random(n) < 0.05] = -1
+    dt = np.float32 if f32 else np.float64
+    v = {k: rng.standard_normal(n).astype(dt) for k in ("cx", "cy", "cz", "erot")}
+    parts = dict(n=n, cap=n, x=None, y=None, vib=rng.integers(0, 200, n), cell=cell,
+                 pid=rng.permutation(n).astype(np.uint32), next_pid=n, **v)
+    print(f"[step routes] cells={M} f32={f32}", flush=True)
+    st = usp.DeviceState(prob, parts)
+    st.bin()
+    got, keep = st.state(), np.nonzero(cell >= 0)[0]
+    order = keep[np.argsort(cell[keep], kind="stable")]
+    assert np.array_equal(got["cell"], cell[order])
+    for k in ("cx", "cy", "cz", "erot"):
+        assert np.array_equal(got[k], parts[k][order].astype(np.float64)), k
+    assert np.array_equal(got["pid"], parts["pid"][order])
+    assert np.array_equal(got["vib"], parts["vib"][order])
+    off = np.concatenate([[0], np.cumsum(np.bincount(cell[keep], minlength=M))])
+    assert np.array_equal(st.offsets.cpu().numpy(), off)
+
+
+@pytest.mark.parametrize("f32", [True, False])
 def test_step_reads_this_steps_stencils(f32):
     """On a grid of at most 256 cells the particle phase makes its cell's
     stencil word itself.  Half the cells empty out and fill again from step to
