@@ -79,6 +79,52 @@ def test_unordered_input_of_more_cells_than_the_sort_takes(f32):
 
 
 @pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("cells,ppc", [(16, 60), (5, 700), (256, 30)])
+def test_wall_sums_of_a_channel(cells, ppc, f32):
+    """A workgroup per cell adds its wall hits up in LDS first (8 or 16
+    waves): the same integers as the flight kernel's own additions, after
+    each of three steps."""
+    usp = _usp()
+    prob = W.poiseuille(kn=0.05, cells=cells, ppc=ppc, f32=f32)
+    parts = W.particles_for(prob)
+    n = parts["n"]
+    parts["cx"][:n] += 250.0
+    print(f"[wall sums] cells={cells} ppc={ppc} f32={f32}", flush=True)
+    a, b, c = (usp.DeviceState(prob, parts) for _ in range(3))
+    for st in (a, b, c):
+        st.enable_sampling(0)
+    for k in range(3):
+        for st in (a, b):
+            st.bin(gather=st is a)
+            st.do_moments()
+            st.do_reconstruct()
+        a.update(k)
+        b.collide(k)
+        b.conserve(k)
+        b.advect(k)
+        c.step(k)
+        sa, sb = a.surface_sums(), b.surface_sums()
+        assert np.array_equal(sa, sb)
+        hits = sb[:, usp.SURF_HITS].sum()
+        assert hits > 0 and np.count_nonzero(sb) == np.count_nonzero(sb[:2])
+        if k == 0:
+            # the step forms the cell state in a kernel of its own: a few
+            # units of the last place of the stored velocities and, a hit,
+            # one of the sums' 2^-16 m/s or 1/16 J/kg steps
+            sc = c.surface_sums()
+            assert np.array_equal(sc[:, usp.SURF_HITS], sb[:, usp.SURF_HITS])
+            assert np.array_equal(sc[:, usp.SURF_QVIB], sb[:, usp.SURF_QVIB])
+            v = 6.0 * np.sqrt(prob.gas.R * 300.0) + 500.0
+            ulp = 4 * (2.0 ** -23 if f32 else 2.0 ** -50)
+            for q in (usp.SURF_PX, usp.SURF_PY, usp.SURF_PZ, usp.SURF_PN, usp.SURF_PT):
+                tol = hits * (1 + ulp * v * usp.SURF_P_SCALE)
+                assert np.abs(sc[:, q] - sb[:, q]).max() <= tol, q
+            for q in (usp.SURF_ETR, usp.SURF_EROT):
+                tol = hits * (1 + ulp * 3 * v * v * usp.SURF_E_SCALE)
+                assert np.abs(sc[:, q] - sb[:, q]).max() <= tol, q
+
+
+@pytest.mark.parametrize("f32", [True, False])
 def test_step_reads_this_steps_stencils(f32):
     """On a grid of at most 256 cells the particle phase makes its cell's
     stencil word itself.  Half the cells empty out and fill again from step to
