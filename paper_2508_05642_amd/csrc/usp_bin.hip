@@ -29,6 +29,10 @@ constexpr int SCAN_ITEMS = 4;
 constexpr int SCAN_TILE = BIN_BLOCK * SCAN_ITEMS;
 constexpr int SORT_LDS = 4096;
 constexpr int BIN_U = 4;  // chunks of 64 particles per load batch of the grouped bin
+// Grids of at most this many cells launch independent bin kernels together
+// (they come here with buffers past the sorted bin's limit; 1200 cells of 20
+// particles in 9.4M slots: 73 us apart, 56 together).
+constexpr int64_t BIN_MERGE_MAX = 4096;
 
 __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -320,6 +324,27 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_tail_key(GridP g, PartP<S> in, co
               gridDim.x);
 }
 
+// On small grids, where the step is launch-bound, the two run side by side
+// in one launch (they touch disjoint arrays): the first ngroup blocks group
+// the binned prefix, the rest key the tail.  (On large grids the separate
+// launches are faster.)
+template <typename S>
+__global__ __launch_bounds__(BIN_BLOCK) void k_bin_group_tail(GridP g, Nbr nb, PartP<S> in,
+                                                              const int64_t* old_off, int32_t* key,
+                                                              int32_t* T9, int32_t* far_cnt,
+                                                              int32_t* far_c, int32_t* far_i,
+                                                              int32_t* far_total, int32_t* tail_cnt,
+                                                              int32_t* tail_cells,
+                                                              int32_t* n_tail_cells,
+                                                              int64_t* counters, int64_t ngroup) {
+  const int64_t blk = blockIdx.x;
+  if (blk < ngroup)
+    bin_group<S>(g, nb, in, old_off, key, T9, far_cnt, far_c, far_i, far_total, counters, blk);
+  else
+    tail_key<S>(g, in, old_off, key, tail_cnt, tail_cells, n_tail_cells, counters, blk - ngroup,
+                (int64_t)gridDim.x - ngroup);
+}
+
 // Far moves into per-cell lists (the order inside a list is fixed later).
 __global__ __launch_bounds__(BIN_BLOCK) void k_far_place(const int32_t* far_total,
                                                          const int32_t* far_c, const int32_t* far_i,
@@ -534,6 +559,29 @@ __global__ __launch_bounds__(BIN_BLOCK) void k_tail_claim(int64_t M, const int64
   tail_claim(M, old_off, count, key, offsets, nontail, cursor, perm, blockIdx.x, gridDim.x);
 }
 
+// Far moves and tail claims side by side in one launch on small grids
+// (disjoint slots): the first nfar blocks place the far moves, the rest
+// claim the tail's slots.
+template <typename S, bool G>
+__global__ __launch_bounds__(BIN_BLOCK) void k_far_tail(GridP g, PartP<S> in, PartP<S> out,
+                                                        uint32_t* gperm, const int32_t* far_total,
+                                                        const int32_t* far_c, const int32_t* far_i,
+                                                        const int64_t* far_off,
+                                                        const int32_t* far_list,
+                                                        const int32_t* far_base,
+                                                        const int64_t* old_off, const int32_t* key,
+                                                        const int64_t* offsets,
+                                                        const int32_t* nontail, int32_t* cursor,
+                                                        uint32_t* perm, int nfar) {
+  const int blk = blockIdx.x;
+  if (blk < nfar)
+    far_scatter<S, G>(g, in, out, gperm, far_total, far_c, far_i, far_off, far_list, far_base,
+                      offsets, blk, nfar);
+  else
+    tail_claim(g.M, old_off, in.count, key, offsets, nontail, cursor, perm, blk - nfar,
+               (int64_t)gridDim.x - nfar);
+}
+
 // One wave sorts one cell's tail slot list (distinct input indices) by rank
 // counting and copies each particle to its rank's slot: each lane holds K
 // entries; an entry's rank is the number of entries below it, counted
@@ -673,10 +721,17 @@ static hipError_t bin_launches(const GridP& g, const PartP<S>& in, const PartP<S
   k_bin_init<<<cdiv(M + 1, 256), 256, 0, st>>>(in_offsets, old_off, M, tail_cnt, cursor, far_cnt,
                                                 far_cur, far_total, n_tail_cells);
   const int64_t ngroup = cdiv(M, BIN_BLOCK / 64);
-  k_bin_group<S><<<ngroup, BIN_BLOCK, 0, st>>>(g, nb, in, old_off, key, T9, far_cnt, far_c, far_i,
-                                               far_total, counters);
-  k_tail_key<S><<<TAIL_GRID, BIN_BLOCK, 0, st>>>(g, in, old_off, key, tail_cnt, tail_cells,
-                                                 n_tail_cells, counters);
+  const bool merged = M <= BIN_MERGE_MAX;
+  if (merged) {
+    k_bin_group_tail<S><<<ngroup + TAIL_GRID, BIN_BLOCK, 0, st>>>(
+        g, nb, in, old_off, key, T9, far_cnt, far_c, far_i, far_total, tail_cnt, tail_cells,
+        n_tail_cells, counters, ngroup);
+  } else {
+    k_bin_group<S><<<ngroup, BIN_BLOCK, 0, st>>>(g, nb, in, old_off, key, T9, far_cnt, far_c, far_i,
+                                                 far_total, counters);
+    k_tail_key<S><<<TAIL_GRID, BIN_BLOCK, 0, st>>>(g, in, old_off, key, tail_cnt, tail_cells,
+                                                   n_tail_cells, counters);
+  }
   launch_scan(far_cnt, M, far_off, blocksums, nullptr, nullptr, st);
   k_far_place<<<64, BIN_BLOCK, 0, st>>>(far_total, far_c, far_i, far_off, far_cur, far_list);
   const int far_cpw = M >= 64 * 1024 ? 64 : 1;
@@ -689,10 +744,16 @@ static hipError_t bin_launches(const GridP& g, const PartP<S>& in, const PartP<S
   k_bin_scatter<S, G><<<cdiv(M, BIN_BLOCK / 64), BIN_BLOCK, 0, st>>>(g, nb, in, out, perm, old_off, key, T9,
                                                                    offsets);
   const int FAR_GRID = 64;
-  k_far_scatter<S, G><<<FAR_GRID, BIN_BLOCK, 0, st>>>(g, in, out, perm, far_total, far_c, far_i,
-                                                     far_off, far_list, far_base, offsets);
-  k_tail_claim<<<TAIL_GRID, BIN_BLOCK, 0, st>>>(M, old_off, in.count, key, offsets, nontail,
-                                                cursor, perm);
+  if (merged) {
+    k_far_tail<S, G><<<FAR_GRID + TAIL_GRID, BIN_BLOCK, 0, st>>>(
+        g, in, out, perm, far_total, far_c, far_i, far_off, far_list, far_base, old_off, key,
+        offsets, nontail, cursor, perm, FAR_GRID);
+  } else {
+    k_far_scatter<S, G><<<FAR_GRID, BIN_BLOCK, 0, st>>>(g, in, out, perm, far_total, far_c, far_i,
+                                                       far_off, far_list, far_base, offsets);
+    k_tail_claim<<<TAIL_GRID, BIN_BLOCK, 0, st>>>(M, old_off, in.count, key, offsets, nontail,
+                                                  cursor, perm);
+  }
   k_tail_sort_copy<S, G><<<TAIL_GRID, BIN_BLOCK, 0, st>>>(g, in, out, offsets, nontail, perm,
                                                        tail_cells, n_tail_cells);
   k_tail_sort_copy_big<S, G><<<TAIL_GRID, BIN_BLOCK, 0, st>>>(g, in, out, offsets, nontail, perm,
