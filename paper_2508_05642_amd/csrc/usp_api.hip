@@ -86,7 +86,6 @@ WsLayout ws_layout(int64_t M, int64_t capacity, int nfaces) {
   L.chunk_off = o; o = align256(o + sizeof(int64_t) * (size_t)(M + 1));
   L.chunk_part = o; o = align256(o + sizeof(double) * BIG_PARTS * (size_t)chunks_max(capacity, M));
   L.cons_scal = o; o = align256(o + CONS_SCALAR_BYTES * (size_t)M);
-  // a smaller state of the same grid may have more (smaller) chunks
   const int64_t chunks = std::min(cdiv(capacity, SORT_CHUNK_MIN), SORT_CHUNKS);
   L.sort_t = o; o = align256(o + sizeof(uint32_t) * (size_t)(chunks * std::min<int64_t>((M + 3) / 4 * 4, SORT_BUCKETS)));
   L.sort_tot = o; o = align256(o + sizeof(uint32_t) * (size_t)(2 * SORT_BUCKETS + 1));

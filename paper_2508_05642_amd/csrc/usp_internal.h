@@ -155,14 +155,14 @@ constexpr int UPDATE_TILE_MIN = 128;
 WsLayout ws_layout(int64_t M, int64_t capacity, int nfaces);
 
 // The bin as a counting sort of input chunks (usp_sort.hip): nb digits (the
-// cell, or a bucket of 2^shift cells), nchunks chunks of `chunk` slots.
+// cell, or a bucket of 2^shift cells), at most nchunks chunks.
 constexpr int SORT_BUCKETS = 1024;
 constexpr int64_t SORT_CHUNKS = 1024;
 constexpr int64_t SORT_CHUNK_MIN = 2048;
 constexpr int64_t SORT_SELF_SCAN = 32768;
 struct SortPlan {
   int shift, nb, ld, bits, self_scan;  // ld: row stride of the digit counts
-  int64_t chunk, nchunks;
+  int64_t nchunks;
 };
 SortPlan sort_plan(int64_t M, int64_t capacity);
 // Which route the bin takes.  An input without segments is sorted (its
