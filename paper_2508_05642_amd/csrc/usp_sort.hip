@@ -515,6 +515,9 @@ __global__ __launch_bounds__(FINE_BLOCK) void k_sort_fine(GridP g, PartP<S> in, 
 // packs: 1157 -> 693).
 constexpr int FETCH_BLOCK = 256;
 constexpr int FETCH_U = 4;
+// Workgroups at most (eight on each CU, four rounds); each goes on to the next
+// slots while any are left.
+constexpr int64_t FETCH_BLOCKS = 8192;
 
 struct alignas(16) SortPack {
   uint32_t w[4];
@@ -540,26 +543,28 @@ template <typename S, int K>
 __global__ __launch_bounds__(FETCH_BLOCK) void k_sort_pack(PartP<S> in, SortPack* pack, bool has_x,
                                                            bool has_y) {
   constexpr bool WIDE = sizeof(S) == 8;
-  const int64_t i = (int64_t)blockIdx.x * FETCH_BLOCK + threadIdx.x;
-  if (i >= in.count[0]) return;
-  SortPack a = {};
-  if constexpr (K == 0) {
-    pack_words<S>(&a, 0, in.cx[i]);
-    pack_words<S>(&a, 1, in.cy[i]);
+  const int64_t n = in.count[0];
+  for (int64_t i = (int64_t)blockIdx.x * FETCH_BLOCK + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * FETCH_BLOCK) {
+    SortPack a = {};
+    if constexpr (K == 0) {
+      pack_words<S>(&a, 0, in.cx[i]);
+      pack_words<S>(&a, 1, in.cy[i]);
+    }
+    if constexpr (K == (WIDE ? 1 : 0)) {
+      pack_words<S>(&a, WIDE ? 0 : 2, in.cz[i]);
+      pack_words<S>(&a, WIDE ? 1 : 3, in.erot[i]);
+    }
+    if constexpr (K == (WIDE ? 2 : 1)) {
+      if (has_x) pack_words<S>(&a, 0, in.x[i]);
+      if (has_y) pack_words<S>(&a, 1, in.y[i]);
+    }
+    if constexpr (K == SORT_PACKS<S> - 1) {
+      a.w[2] = in.pid[i];
+      a.w[3] = in.vib[i];
+    }
+    pack[i] = a;
   }
-  if constexpr (K == (WIDE ? 1 : 0)) {
-    pack_words<S>(&a, WIDE ? 0 : 2, in.cz[i]);
-    pack_words<S>(&a, WIDE ? 1 : 3, in.erot[i]);
-  }
-  if constexpr (K == (WIDE ? 2 : 1)) {
-    if (has_x) pack_words<S>(&a, 0, in.x[i]);
-    if (has_y) pack_words<S>(&a, 1, in.y[i]);
-  }
-  if constexpr (K == SORT_PACKS<S> - 1) {
-    a.w[2] = in.pid[i];
-    a.w[3] = in.vib[i];
-  }
-  pack[i] = a;
 }
 
 template <typename S, int K>
@@ -569,36 +574,37 @@ __global__ __launch_bounds__(FETCH_BLOCK) void k_sort_fetch(PartP<S> out,
                                                             bool has_x, bool has_y) {
   constexpr bool WIDE = sizeof(S) == 8;
   const int64_t n = out.count[0];
-  const int64_t p0 = (int64_t)blockIdx.x * (FETCH_BLOCK * FETCH_U) + threadIdx.x;
-  if (p0 >= n) return;
-  uint32_t i[FETCH_U];
-  SortPack a[FETCH_U];
+  for (int64_t p0 = (int64_t)blockIdx.x * (FETCH_BLOCK * FETCH_U) + threadIdx.x; p0 < n;
+       p0 += (int64_t)gridDim.x * (FETCH_BLOCK * FETCH_U)) {
+    uint32_t i[FETCH_U];
+    SortPack a[FETCH_U];
 #pragma unroll
-  for (int u = 0; u < FETCH_U; ++u) {
-    const int64_t p = p0 + u * FETCH_BLOCK;
-    i[u] = perm[p < n ? p : p0];
-  }
+    for (int u = 0; u < FETCH_U; ++u) {
+      const int64_t p = p0 + u * FETCH_BLOCK;
+      i[u] = perm[p < n ? p : p0];
+    }
 #pragma unroll
-  for (int u = 0; u < FETCH_U; ++u) a[u] = pack[i[u]];
+    for (int u = 0; u < FETCH_U; ++u) a[u] = pack[i[u]];
 #pragma unroll
-  for (int u = 0; u < FETCH_U; ++u) {
-    const int64_t p = p0 + u * FETCH_BLOCK;
-    if (p >= n) continue;
-    if constexpr (K == 0) {
-      out.cx[p] = unpack_words<S>(a[u], 0);
-      out.cy[p] = unpack_words<S>(a[u], 1);
-    }
-    if constexpr (K == (WIDE ? 1 : 0)) {
-      out.cz[p] = unpack_words<S>(a[u], WIDE ? 0 : 2);
-      out.erot[p] = unpack_words<S>(a[u], WIDE ? 1 : 3);
-    }
-    if constexpr (K == (WIDE ? 2 : 1)) {
-      if (has_x) out.x[p] = unpack_words<S>(a[u], 0);
-      if (has_y) out.y[p] = unpack_words<S>(a[u], 1);
-    }
-    if constexpr (K == SORT_PACKS<S> - 1) {
-      out.pid[p] = a[u].w[2];
-      out.vib[p] = (uint8_t)a[u].w[3];
+    for (int u = 0; u < FETCH_U; ++u) {
+      const int64_t p = p0 + u * FETCH_BLOCK;
+      if (p >= n) continue;
+      if constexpr (K == 0) {
+        out.cx[p] = unpack_words<S>(a[u], 0);
+        out.cy[p] = unpack_words<S>(a[u], 1);
+      }
+      if constexpr (K == (WIDE ? 1 : 0)) {
+        out.cz[p] = unpack_words<S>(a[u], WIDE ? 0 : 2);
+        out.erot[p] = unpack_words<S>(a[u], WIDE ? 1 : 3);
+      }
+      if constexpr (K == (WIDE ? 2 : 1)) {
+        if (has_x) out.x[p] = unpack_words<S>(a[u], 0);
+        if (has_y) out.y[p] = unpack_words<S>(a[u], 1);
+      }
+      if constexpr (K == SORT_PACKS<S> - 1) {
+        out.pid[p] = a[u].w[2];
+        out.vib[p] = (uint8_t)a[u].w[3];
+      }
     }
   }
 }
@@ -607,8 +613,9 @@ template <typename S, int K = 0>
 static void fetch_packs(const PartP<S>& in, const PartP<S>& out, SortPack* pack,
                         const uint32_t* perm, bool hx, bool hy, hipStream_t st) {
   if (!(sizeof(S) == 8 && K == 2 && !hy)) {  // a pack of positions alone
-    k_sort_pack<S, K><<<(int)cdiv(in.capacity, FETCH_BLOCK), FETCH_BLOCK, 0, st>>>(in, pack, hx, hy);
-    k_sort_fetch<S, K><<<(int)cdiv(out.capacity, FETCH_BLOCK * FETCH_U), FETCH_BLOCK, 0, st>>>(
+    auto blocks = [](int64_t n) { return (int)(n < FETCH_BLOCKS ? n : FETCH_BLOCKS); };
+    k_sort_pack<S, K><<<blocks(cdiv(in.capacity, FETCH_BLOCK)), FETCH_BLOCK, 0, st>>>(in, pack, hx, hy);
+    k_sort_fetch<S, K><<<blocks(cdiv(out.capacity, FETCH_BLOCK * FETCH_U)), FETCH_BLOCK, 0, st>>>(
         out, pack, perm, hx, hy);
   }
   if constexpr (K + 1 < SORT_PACKS<S>) fetch_packs<S, K + 1>(in, out, pack, perm, hx, hy, st);
