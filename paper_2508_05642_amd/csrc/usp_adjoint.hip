@@ -203,8 +203,8 @@ static hipError_t step_taped(const GridP& g, const GasP& gas, const BcP& bc, dou
                      update_ntiles(UPDATE_STAGE_F64, out.capacity, g.M), UPDATE_STAGE_F64};
   hipError_t e = launch_bin<double>(g, in, out, offsets, in_offsets, ws, L, counters, st, perm, ti);
   if (e != hipSuccess) return e;
-  if ((e = launch_cells<double>(g, gas, in, offsets, mom, dt, nullptr, cs, counters, st, perm,
-                                !update_solo(g))) != hipSuccess)
+  if ((e = launch_cells<double>(g, gas, in, offsets, mom, dt, nullptr, cs, counters, st, perm)) !=
+      hipSuccess)
     return e;
   auto d = [&](size_t at) { return (double*)(tape + at); };
   TapeOut to;

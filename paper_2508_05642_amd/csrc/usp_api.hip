@@ -228,8 +228,7 @@ usp_status do_step(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, d
                              gperm, TileIndex{(int32_t*)(w + L.tiles),
                                               update_ntiles(stage, cap, g.M), stage})) != hipSuccess)
         return USP_EDEVICE;
-      if ((e = launch_cells<S>(g, gp, in, offsets, mom, dt, dt_cell, cs, counters, st, gperm,
-                               !update_solo(g))) !=
+      if ((e = launch_cells<S>(g, gp, in, offsets, mom, dt, dt_cell, cs, counters, st, gperm)) !=
           hipSuccess)
         return USP_EDEVICE;
       if ((e = launch_update<S>(g, gp, bp, dt, cs, offsets, out, seed, sn, w, L, counters, st, &in,

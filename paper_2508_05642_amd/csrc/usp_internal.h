@@ -212,14 +212,13 @@ hipError_t launch_moments(const GridP& g, const PartP<S>& p, const int64_t* offs
 hipError_t launch_cell_coef(const GridP& g, const GasP& gas, double* cs, hipStream_t st);
 hipError_t launch_reconstruct(const GridP& g, const GasP& gas, const double* mom, double dt,
                               const double* dt_cell, double* cs, int64_t* counters, hipStream_t st);
-// launch_moments followed by launch_reconstruct, in fewer launches on grids
-// of few cells.  Without `stencils` (grids that update_solo takes) the
-// stencil words are left to the particle phase.
+// launch_moments followed by launch_reconstruct; on 1D and 2D grids that
+// update_solo takes in one launch, and without the stencil words, which the
+// particle phase of a step makes there.
 template <typename S>
 hipError_t launch_cells(const GridP& g, const GasP& gas, const PartP<S>& p, const int64_t* offsets,
                         double* mom, double dt, const double* dt_cell, double* cs,
-                        int64_t* counters, hipStream_t st, const uint32_t* gather_perm = nullptr,
-                        bool stencils = true);
+                        int64_t* counters, hipStream_t st, const uint32_t* gather_perm = nullptr);
 hipError_t launch_sample_fields(const GridP& g, const double* mom, double* acc, hipStream_t st);
 template <typename S>
 hipError_t launch_collide(const GridP& g, const GasP& gas, const double* cs, const int64_t* offsets,

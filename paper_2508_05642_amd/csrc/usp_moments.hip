@@ -22,8 +22,11 @@ __global__ __launch_bounds__(CELL_BLOCK) void k_moments(GridP g, PartP<S> p, con
 
 // On grids of few cells 16 lanes a cell leave the chip idle: a workgroup takes
 // a cell (block_row_sums: the bits of k_moments), and with `state` one lane
-// goes on to the cell state (a serial chain of some 4 us, for all cells at
-// once), which saves its launch.  200 cells of 1000 particles: 22 + 10 us for
+// goes on to the cell state, which saves its launch where every cell has a CU
+// to itself: the chain holds its workgroup's waves and LDS for some 10 us, and
+// with several cells a CU the chains follow one another (a step of 256 cells
+// of 200 particles: 55 us with its launch, 50 without; of 300 cells 57 and 63;
+// of 4096 cells 131 and 160).  200 cells of 1000 particles: 22 + 10 us for
 // the two kernels before, 14 together; 0.7M FP64 particles in 1800 cells: the
 // moments 38 -> 18 us. (Each lane its own particles in all 20 sums took 12:
 // other bits, which a FP32 state carries on.)
@@ -59,10 +62,19 @@ __global__ __launch_bounds__(BLOCK) void k_moments_wide(GridP g, GasP gas, PartP
 }
 
 // 0: the 16-lane kernel; 1 and 2: a workgroup a cell, of 5 waves, or on the
-// smallest grids of 8 (0D grids keep their two kernels: the cell state of
-// thousands of cells is spread over threads).
+// smallest grids of 8.  The 16 lanes' time is that of the fullest cell, the
+// workgroups' grows with the cells, each of which costs its barriers.  Moments
+// alone, 16 lanes against a workgroup, FP32: cells alike, 1024 x 800
+// particles 9.7 / 10.8 us, 1800 x 220 7.7 / 8.5, 1800 x 800 10 / 18, 2592 x 220
+// 7.8 / 11, 4096 x 200 7.2 / 17, 4096 x 800 12 / 39; with a shock layer of up to
+// a dozen times the mean, 450 x 220 23 / 12, 1800 x 220 26 / 13, 2592 x 220 25 /
+// 16, 4050 x 220 25 / 25 (FP64 34 / 25).  A step of cells alike: 300 x 200 62 /
+// 58, 1024 x 200 73 / 72, 1800 x 200 96 / 100, 4096 x 200 119 / 131.  So up to
+// 1024 cells, and up to 2048 in 2D, whose flows have dense layers (0D grids
+// are batches of cells of any size and keep their two kernels).
 static int moments_shape(const GridP& g) {
-  return g.dim == 0 || g.M > 4096 ? 0 : g.M <= 512 ? 2 : 1;
+  if (g.dim == 0 || g.M > (g.dim == 2 ? 2048 : 1024)) return 0;
+  return g.M <= 512 ? 2 : 1;
 }
 
 template <typename S, int BLOCK, int SC>
@@ -92,8 +104,8 @@ __global__ void k_stencil(GridP g, double* cs) {
   if (c < g.M && g.dim != 0) stencil_cell(g, cs, c);
 }
 
-// Grids of at most CELL_SMALL cells (launch-bound steps): the cell state and
-// then the stencils in one block, the barrier between them standing in for
+// Grids of at most CELL_SMALL cells (usp_reconstruct, and the steps of 0D
+// grids): the cell state and then the stencils in one block, the barrier between them standing in for
 // the launch boundary (the stencils read the neighbours' usability).
 constexpr int64_t CELL_SMALL = 256;
 __global__ __launch_bounds__(256) void k_cell_state_small(GridP g, GasP gas, const double* mom,
@@ -194,25 +206,22 @@ hipError_t launch_reconstruct(const GridP& g, const GasP& gas, const double* mom
 template <typename S>
 hipError_t launch_cells(const GridP& g, const GasP& gas, const PartP<S>& p, const int64_t* offsets,
                         double* mom, double dt, const double* dt_cell, double* cs,
-                        int64_t* counters, hipStream_t st, const uint32_t* gather_perm,
-                        bool stencils) {
-  const int shape = moments_shape(g);
-  if (!shape) {
+                        int64_t* counters, hipStream_t st, const uint32_t* gather_perm) {
+  if (g.dim == 0 || !update_solo(g)) {
     const hipError_t e = launch_moments<S>(g, p, offsets, mom, st, gather_perm);
     return e != hipSuccess ? e : launch_reconstruct(g, gas, mom, dt, dt_cell, cs, counters, st);
   }
-  const hipError_t e = (shape == 2 ? moments_wide<S, 512, 512> : moments_wide<S, MOM_THREADS, 256>)(
-      g, gas, p, offsets, mom, dt, dt_cell, cs, counters, st, gather_perm, 1);
-  if (e != hipSuccess) return e;
-  return stencils ? launch_stencil(g, gas, cs, st) : launch_cell_coef(g, gas, cs, st);
+  const hipError_t e = moments_wide<S, 512, 512>(g, gas, p, offsets, mom, dt, dt_cell, cs, counters,
+                                                 st, gather_perm, 1);
+  return e != hipSuccess ? e : launch_cell_coef(g, gas, cs, st);
 }
 
 template hipError_t launch_cells<float>(const GridP&, const GasP&, const PartP<float>&,
                                         const int64_t*, double*, double, const double*, double*,
-                                        int64_t*, hipStream_t, const uint32_t*, bool);
+                                        int64_t*, hipStream_t, const uint32_t*);
 template hipError_t launch_cells<double>(const GridP&, const GasP&, const PartP<double>&,
                                          const int64_t*, double*, double, const double*, double*,
-                                         int64_t*, hipStream_t, const uint32_t*, bool);
+                                         int64_t*, hipStream_t, const uint32_t*);
 template hipError_t launch_moments<float>(const GridP&, const PartP<float>&, const int64_t*,
                                           double*, hipStream_t, const uint32_t*);
 template hipError_t launch_moments<double>(const GridP&, const PartP<double>&, const int64_t*,
