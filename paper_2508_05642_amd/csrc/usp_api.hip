@@ -180,10 +180,18 @@ usp_status do_step(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, d
   // Cells far larger than the fused particle phase's LDS stage (mean slots
   // per cell above it) would give whole cells to single workgroups: such
   // grids run the separate phase kernels, which spread every particle over
-  // the chip, after a copying bin, with the moments and the conservation's
-  // sums split over chunks of each cell (usp_bigcell.hip).
+  // the chip, after a copying bin.  With fewer than SPLIT_CELLS cells the
+  // moments and the conservation's sums are split over chunks of each cell
+  // (usp_bigcell.hip); with more, a row of lanes or a wave a cell fills the chip,
+  // and the chunks' workgroups a cell, one of whose lanes forms its state,
+  // are the longer way, above all where the cells are small and only the
+  // buffer is roomy.  Split against phases, FP32: 256 2D cells of 2500 128 /
+  // 147 us, of 6000 200 / 266; 1024 of 2500 302 / 297, of 6000 665 / 704, of 20
+  // in 9.4M slots 136 / 94; 4096 of 2500 1798 / 1609, of 300 352 / 242; 0D, 512
+  // cells of 6000 257 / 359, 1024 435 / 478, of 300 92 / 61, 4096 of 2500 578 / 418.
   const int stage = sizeof(S) == 4 ? UPDATE_STAGE_F32 : UPDATE_STAGE_F64;
   const bool big_cells = cdiv(cap, g.M) > stage;
+  constexpr int64_t SPLIT_CELLS = 1024;
   for (int32_t s = 0; s < nsteps; ++s) {
     const uint64_t sn = step + (uint64_t)s;
     if (big_cells) {
@@ -196,9 +204,22 @@ usp_status do_step(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, d
         const usp_particles tmp = *p;
         *p = *p_alt;
         *p_alt = tmp;
-        if ((e = launch_chunks(g, offsets, w, L, st)) != hipSuccess) return USP_EDEVICE;
+        if (g.M < SPLIT_CELLS && (e = launch_chunks(g, offsets, w, L, st)) != hipSuccess)
+          return USP_EDEVICE;
       }
       const PartP<S> q = make_parts<S>(p);
+      if (g.M >= SPLIT_CELLS) {
+        if ((e = launch_cells<S>(g, gp, q, offsets, mom, dt, dt_cell, cs, counters, st)) != hipSuccess)
+          return USP_EDEVICE;
+        if ((e = launch_collide<S>(g, gp, cs, offsets, q, seed, sn, counters, st)) != hipSuccess)
+          return USP_EDEVICE;
+        if ((e = launch_conserve<S>(g, gp, cs, offsets, q, seed, sn, counters, st)) != hipSuccess)
+          return USP_EDEVICE;
+        if (g.dim != 0 &&
+            (e = launch_advect<S>(g, gp, bp, dt, q, seed, sn, w, L, counters, st)) != hipSuccess)
+          return USP_EDEVICE;
+        continue;
+      }
       // in 0D the scalings of a step wait for the next step's moments
       if ((e = launch_cells_split<S>(g, gp, q, offsets, mom, dt, dt_cell, cs, g.dim == 0 && s > 0, w,
                                      L, counters, st)) != hipSuccess)

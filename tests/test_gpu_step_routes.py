@@ -166,3 +166,62 @@ def test_step_reads_this_steps_stencils(f32):
             if b.bufs[b.cur][q] is not None:
                 b.bufs[b.cur][q].copy_(a.bufs[a.cur][q])
         b.bufs[b.cur]["cell"].copy_(a.bufs[a.cur]["cell"])
+
+
+def _roomy(M, dim, f32):
+    """A periodic box (or independent cells) of M cells of 0 to 9 particles in
+    a buffer of more slots a cell than the particle phase's stage."""
+    rng = np.random.default_rng(M)
+    nx, ny = (M, 1) if dim == 0 else (1, M) if dim == 1 else (M // 31 if M % 31 == 0 else 32, 0)
+    if dim == 2:
+        ny = M // nx
+    M = nx * ny
+    h = 1e-4
+    gas = W.Gas()
+    grid = W.Grid(dim=dim, nx=nx, ny=ny, dx=h, dy=h, fnum=1e22 * h * h / 5, volume=np.full(M, h * h),
+                  flags=np.zeros(M, np.uint8))
+    s = np.sqrt(gas.R * 300.0)
+    prob = W.Problem("roomy", gas, grid, W.BC(kind=(W.BC_PERIODIC,) * 4), dt=0.3 * h / s, seed=3, f32=f32)
+    cell = np.repeat(np.arange(M), rng.integers(0, 10, M))
+    n = len(cell)
+    u = 0.001 + 0.998 * rng.random((2, n))
+    parts = dict(n=n, cap=n, x=(cell % nx + u[0]) * h if dim == 2 else None,
+                 y=((cell // nx if dim == 2 else cell) + u[1]) * h if dim else None,
+                 erot=rng.exponential(gas.R * 300.0, n), vib=rng.integers(0, 3, n),
+                 cell=cell.astype(np.int32), pid=np.arange(n, dtype=np.uint32), next_pid=n,
+                 **{k: s * rng.standard_normal(n) for k in ("cx", "cy", "cz")})
+    return prob, parts, M * ((2048 if f32 else 1024) + 1)
+
+
+@pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("M,dim", [(1023, 0), (1023, 1), (1023, 2), (1024, 0), (1024, 1), (1024, 2)])
+def test_step_past_the_stage_by_phases_or_chunks(M, dim, f32):
+    """Buffers of more slots a cell than the stage: from 1024 cells on a step is
+    the single phases (their bits); below, its sums go by chunks of the cells
+    (FP64 sums of at most nine terms in another order: a few 1e-16 of the
+    velocities, which a FP32 state rounds to 6e-8)."""
+    usp = _usp()
+    prob, parts, cap = _roomy(M, dim, f32)
+    print(f"[step routes] roomy M={M} dim={dim} f32={f32} n={parts['n']}", flush=True)
+    a, b = (usp.DeviceState(prob, parts, capacity=cap) for _ in range(2))
+    steps = 3 if M >= 1024 else 1
+    a.step(5, steps)
+    for k in range(steps):
+        if dim or k == 0:
+            b.bin()
+        b.do_moments()
+        b.do_reconstruct()
+        b.collide(5 + k)
+        b.conserve(5 + k)
+        if dim:
+            b.advect(5 + k)
+    if M >= 1024:
+        _same(a, b)
+        assert np.array_equal(a.moments(), b.moments())
+        return
+    sa, sb = a.state(), b.state()
+    assert sa["n"] == sb["n"] and np.array_equal(sa["pid"], sb["pid"])
+    assert np.array_equal(sa["vib"], sb["vib"])
+    v = np.sqrt(prob.gas.R * 300.0)
+    for k in ("cx", "cy", "cz"):
+        assert np.abs(sa[k] - sb[k]).max() <= (1e-5 if f32 else 1e-9) * v, k
