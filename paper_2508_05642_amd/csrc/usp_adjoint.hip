@@ -72,7 +72,8 @@ constexpr int NOBJ = 2, NPAR = 3;
 // add to the fields of the cells below and above (NNBR each)
 constexpr int NSUM = NOWN + 2 * NNBR;
 static_assert(NSUM <= 64, "a lane per sum");
-// workgroups that share a cell's particles in K2, each with its own sums
+// workgroups that share a cell's particles in K2 at most, each with its own
+// sums
 constexpr int K2_PARTS = 2;
 
 struct AdjWsLayout {
@@ -354,14 +355,22 @@ __device__ __forceinline__ double& lam_at(double* lam, int o, int f, int64_t cap
   return lam[((int64_t)o * NLAM + f) * cap + i];
 }
 
-// The reverse kernels take a workgroup per cell, a thread per particle: the
-// differentiable channel has a hundred cells of some hundred particles, and a
-// wave a cell left the chip idle (100 x 500: flight and conservation 40 us).
+// The reverse kernels take a workgroup of B threads per cell, a thread per
+// particle: the differentiable channel has a hundred cells of some hundred
+// particles, and a wave a cell left the chip idle (100 x 500: flight and
+// conservation 40 us).  Many small cells take a wave each instead: with
+// their registers one or two workgroups of 8 waves fit a CU, and most of those
+// waves have no particle.  A reversed and re-run step with 8 waves a cell and
+// with one: 200 x 40 118 / 101 us, 200 x 90 125 / 123, 400 x 20 182 / 125, 1000
+// x 10 309 / 154, 1000 x 90 332 / 190.
 constexpr int ADJ_BLOCK = 512;
-constexpr int ADJ_WAVES = ADJ_BLOCK / 64;
+constexpr int ADJ_SMALL = 64;
+// A wave a cell: past 128 cells (two workgroups of one each fill the CUs) of
+// at most two rounds of a wave.
+static bool small_cells(int64_t M, int64_t cap) { return M > 128 && cap <= 128 * M; }
 
 // Sums of N values over the workgroup, in wave order; every thread gets them.
-template <int N>
+template <int N, int ADJ_WAVES>
 __device__ __forceinline__ void block_sums(double v[N], double (*red)[ADJ_WAVES]) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
@@ -381,10 +390,11 @@ __device__ __forceinline__ void block_sums(double v[N], double (*red)[ADJ_WAVES]
 }
 
 // ---- K1: flight and conservation reversed -------------------------------------
-__global__ __launch_bounds__(ADJ_BLOCK) void k_adj_flight_conserve(
+template <int B>
+__global__ __launch_bounds__(B) void k_adj_flight_conserve(
     GridP g, GasP gas, BcP bc, double dt, TapeP T, int64_t cap, const double* __restrict__ lam_in,
     double* __restrict__ lam1, double* __restrict__ cons, double w_tau, unsigned int* done) {
-  __shared__ double red[10][ADJ_WAVES];
+  __shared__ double red[10][B / 64];
   const int64_t c = blockIdx.x;
   const int64_t M = g.M;
   if (c == 0 && threadIdx.x == 0) *done = 0u;  // counts the workgroups of K3
@@ -417,7 +427,7 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_flight_conserve(
     *ly = lyv;
   };
   if (!coll) {
-    for (int64_t i = o0 + threadIdx.x; i < o1; i += ADJ_BLOCK)
+    for (int64_t i = o0 + threadIdx.x; i < o1; i += B)
       for (int o = 0; o < NOBJ; ++o) {
         double lc[3], le, ly;
         post(i, o, lc, &le, &ly);
@@ -430,14 +440,14 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_flight_conserve(
   // forward scalars of the conservation (the forward's own sums)
   const double Un[3] = {cs[CS_UX * M + c], cs[CS_UY * M + c], cs[CS_UZ * M + c]};
   double s[6] = {0, 0, 0, 0, 0, 0};
-  for (int64_t i = o0 + threadIdx.x; i < o1; i += ADJ_BLOCK) {
+  for (int64_t i = o0 + threadIdx.x; i < o1; i += B) {
     const double d0 = T.ccx[i] - Un[0], d1 = T.ccy[i] - Un[1], d2 = T.ccz[i] - Un[2];
     s[0] += d0; s[1] += d1; s[2] += d2;
     s[3] += d0 * d0 + d1 * d1 + d2 * d2;
     s[4] += T.cerot[i];
     s[5] += (double)T.kvib[i];
   }
-  block_sums<6>(s, red);
+  block_sums<6, B / 64>(s, red);
   const double Nd = (double)N;
   const double m1[3] = {s[0] / Nd, s[1] / Nd, s[2] / Nd};
   const double etr_s = 0.5 * (s[3] / Nd - (m1[0] * m1[0] + m1[1] * m1[1] + m1[2] * m1[2]));
@@ -456,7 +466,7 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_flight_conserve(
   double r[NOBJ * 5];
 #pragma unroll
   for (int k = 0; k < NOBJ * 5; ++k) r[k] = 0.0;
-  for (int64_t i = o0 + threadIdx.x; i < o1; i += ADJ_BLOCK) {
+  for (int64_t i = o0 + threadIdx.x; i < o1; i += B) {
 #pragma unroll
     for (int o = 0; o < NOBJ; ++o) {
       double lc[3], le, ly;
@@ -466,7 +476,7 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_flight_conserve(
       r[5 * o + 2] += lc[0]; r[5 * o + 3] += lc[1]; r[5 * o + 4] += lc[2];
     }
   }
-  block_sums<NOBJ * 5>(r, red);
+  block_sums<NOBJ * 5, B / 64>(r, red);
 #pragma unroll
   for (int o = 0; o < NOBJ; ++o) {
     const double* ro = r + 5 * o;
@@ -485,7 +495,7 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_flight_conserve(
       for (int k = 0; k < 3; ++k) { lUs[k] = -sc * ro[2 + k]; lUn[k] = ro[2 + k]; }
       if (rot) l_erot_t += lerot_a; else l_erot_s += lerot_a;
     }
-    for (int64_t i = o0 + threadIdx.x; i < o1; i += ADJ_BLOCK) {
+    for (int64_t i = o0 + threadIdx.x; i < o1; i += B) {
       double lc[3], le, ly;
       post(i, o, lc, &le, &ly);
       const double cst[3] = {T.ccx[i], T.ccy[i], T.ccz[i]};
@@ -508,20 +518,20 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_flight_conserve(
 // ---- K2: the particle update reversed ------------------------------------------
 // The contributions of a cell's particles to the fields they read (their own
 // cell's, and through the stencil those of the cell below or above) are
-// summed over the workgroup as they are formed, in a fixed order.  Two
-// workgroups of four waves a cell: the kernel holds 250 registers, and a
-// hundred cells would fill 100 of 256 CUs (100 x 500: 45 us for it and the
-// separate sums before, 38 now).
-constexpr int K2_BLOCK = ADJ_BLOCK / K2_PARTS;
-constexpr int K2_WAVES = K2_BLOCK / 64;
-
+// summed over the workgroup as they are formed, in a fixed order.  PARTS
+// workgroups a cell: the kernel holds 358 registers (256 VGPRs and 102 AGPRs),
+// one wave a SIMD, and with one workgroup a cell a hundred cells would fill
+// 100 of 256 CUs (100 x 500: 45 us for it and the separate sums before, 38 as
+// two workgroups of four waves).
+template <int K2_BLOCK, int PARTS>
 __global__ __launch_bounds__(K2_BLOCK) void k_adj_collide(GridP g, GasP gas, TapeP T, int64_t cap,
                                                            uint64_t seed, uint32_t step,
                                                            double* __restrict__ lam1,
                                                            double* __restrict__ csum) {
+  constexpr int K2_WAVES = K2_BLOCK / 64;
   __shared__ double acc[K2_WAVES][NOBJ * NSUM];
-  const int64_t M = g.M, c = blockIdx.x / K2_PARTS;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, half = (int)(blockIdx.x % K2_PARTS);
+  const int64_t M = g.M, c = blockIdx.x / PARTS;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, half = (int)(blockIdx.x % PARTS);
   for (int k = threadIdx.x; k < K2_WAVES * NOBJ * NSUM; k += K2_BLOCK) (&acc[0][0])[k] = 0.0;
   __syncthreads();
   const int64_t o0 = T.offsets[c], o1 = T.offsets[c + 1];
@@ -529,7 +539,7 @@ __global__ __launch_bounds__(K2_BLOCK) void k_adj_collide(GridP g, GasP gas, Tap
   const bool coll = cs[CS_COLLIDE * M + c] != 0.0;  // else identity: lam1 already holds the adjoint
   const PartP<double> p = tape_parts(T, cap);
   // every wave walks the same number of rounds (the sums need whole waves)
-  for (int64_t b = o0 + (half * K2_WAVES + wid) * 64; coll && b < o1; b += ADJ_BLOCK) {
+  for (int64_t b = o0 + (half * K2_WAVES + wid) * 64; coll && b < o1; b += K2_BLOCK * PARTS) {
     const int64_t i = b + lane;
     bool act = i < o1;
     const int64_t iq = act ? i : o0;
@@ -639,10 +649,10 @@ __global__ __launch_bounds__(K2_BLOCK) void k_adj_collide(GridP g, GasP gas, Tap
     }
   }
   __syncthreads();
-  if (threadIdx.x < NOBJ * NSUM) {
-    double t = acc[0][threadIdx.x];
-    for (int w = 1; w < K2_WAVES; ++w) t += acc[w][threadIdx.x];
-    csum[((int64_t)half * NOBJ * NSUM + threadIdx.x) * M + c] = t;
+  for (int k = threadIdx.x; k < NOBJ * NSUM; k += K2_BLOCK) {
+    double t = acc[0][k];
+    for (int w = 1; w < K2_WAVES; ++w) t += acc[w][k];
+    csum[((int64_t)half * NOBJ * NSUM + k) * M + c] = t;
   }
 }
 
@@ -652,7 +662,8 @@ __global__ __launch_bounds__(K2_BLOCK) void k_adj_collide(GridP g, GasP gas, Tap
 // particle takes the moments' adjoints on and undoes the bin.  The workgroup
 // that finishes last adds the cells' parameter partials to grad, in a fixed
 // order.
-__global__ __launch_bounds__(ADJ_BLOCK) void k_adj_moments(
+template <int B, int PARTS>
+__global__ __launch_bounds__(B) void k_adj_moments(
     GridP g, GasP gas, double alpha_vss, TapeP T, int64_t cap, const double* __restrict__ lam1,
     const double* __restrict__ csum, const double* __restrict__ cons, double* __restrict__ lam_out,
     double w_mdot, double* gcell, double* __restrict__ grad, unsigned int* done) {
@@ -682,7 +693,7 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_moments(
     if (lane < NOBJ * NOWN) {
       const int o = lane / NOWN, f = lane % NOWN;
       double t = 0.0;
-      for (int h = 0; h < K2_PARTS; ++h) {
+      for (int h = 0; h < PARTS; ++h) {
         const double* q = csum + (int64_t)(h * NOBJ + o) * NSUM * M;
         t += q[f * M + c];
         if (f < NNBR) {
@@ -725,7 +736,7 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_moments(
   __syncthreads();
   if (threadIdx.x == 0) last = atomicAdd(done, 1u) == (unsigned int)M - 1u;
   const double N = (double)(o1 - o0);
-  for (; i < o1; i += ADJ_BLOCK, fetch(i)) {
+  for (; i < o1; i += B, fetch(i)) {
     const double d[3] = {cx - cs[CS_UX * M + c], cy - cs[CS_UY * M + c], cz - cs[CS_UZ * M + c]};
     if (j < 0) continue;
 #pragma unroll
@@ -746,34 +757,50 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_moments(
   }
   __syncthreads();
   if (!last) return;
-  // wave q: parameter partial q of all cells, lanes striding over them
+  // a wave per parameter partial, lanes striding over the cells
   __threadfence();
-  const int q = threadIdx.x >> 6;
-  if (q >= NOBJ * NPAR) return;
-  double s = 0.0;
-  for (int64_t k = threadIdx.x & 63; k < M; k += 64) s += gcell[(int64_t)q * M + k];
-  s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) grad[q] += s;
+  for (int q = threadIdx.x >> 6; q < NOBJ * NPAR; q += B / 64) {
+    double s = 0.0;
+    for (int64_t k = threadIdx.x & 63; k < M; k += 64) s += gcell[(int64_t)q * M + k];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) grad[q] += s;
+  }
 }
-static_assert(NOBJ * NPAR <= ADJ_WAVES, "a wave per parameter partial");
 
-static hipError_t adjoint_step(const GridP& g, const GasP& gas, const BcP& bc, double alpha_vss,
-                               double dt, const TapeP& T, int64_t cap, uint64_t seed,
-                               uint64_t step, const double* lam_in, double* lam_out,
-                               double w_mdot, double w_tau, double* grad, char* aws,
-                               const AdjWsLayout& W, hipStream_t st) {
+// The three reverse kernels with workgroups of B threads a cell (K2: PARTS of
+// B / PARTS).
+template <int B, int PARTS>
+static hipError_t adjoint_kernels(const GridP& g, const GasP& gas, const BcP& bc, double alpha_vss,
+                                  double dt, const TapeP& T, int64_t cap, uint64_t seed,
+                                  uint64_t step, const double* lam_in, double* lam_out,
+                                  double w_mdot, double w_tau, double* grad, char* aws,
+                                  const AdjWsLayout& W, hipStream_t st) {
+  static_assert(PARTS <= K2_PARTS, "room for the sums");
   double* lam1 = (double*)(aws + W.lam1);
   double* cons = (double*)(aws + W.cons);
   double* csum = (double*)(aws + W.csum);
   double* gcell = (double*)(aws + W.gcell);
   unsigned int* done = (unsigned int*)(aws + W.done);
   const int cells = (int)g.M;
-  k_adj_flight_conserve<<<cells, ADJ_BLOCK, 0, st>>>(g, gas, bc, dt, T, cap, lam_in, lam1, cons,
-                                                     w_tau, done);
-  k_adj_collide<<<K2_PARTS * cells, K2_BLOCK, 0, st>>>(g, gas, T, cap, seed, (uint32_t)step, lam1, csum);
-  k_adj_moments<<<cells, ADJ_BLOCK, 0, st>>>(g, gas, alpha_vss, T, cap, lam1, csum, cons, lam_out,
-                                             w_mdot, gcell, grad, done);
+  k_adj_flight_conserve<B><<<cells, B, 0, st>>>(g, gas, bc, dt, T, cap, lam_in, lam1, cons, w_tau,
+                                                done);
+  k_adj_collide<B / PARTS, PARTS><<<PARTS * cells, B / PARTS, 0, st>>>(g, gas, T, cap, seed,
+                                                                       (uint32_t)step, lam1, csum);
+  k_adj_moments<B, PARTS><<<cells, B, 0, st>>>(g, gas, alpha_vss, T, cap, lam1, csum, cons, lam_out,
+                                               w_mdot, gcell, grad, done);
   return hipGetLastError();
+}
+
+static hipError_t adjoint_step(const GridP& g, const GasP& gas, const BcP& bc, double alpha_vss,
+                               double dt, const TapeP& T, int64_t cap, uint64_t seed,
+                               uint64_t step, const double* lam_in, double* lam_out,
+                               double w_mdot, double w_tau, double* grad, char* aws,
+                               const AdjWsLayout& W, hipStream_t st) {
+  if (small_cells(g.M, cap))
+    return adjoint_kernels<ADJ_SMALL, 1>(g, gas, bc, alpha_vss, dt, T, cap, seed, step, lam_in,
+                                         lam_out, w_mdot, w_tau, grad, aws, W, st);
+  return adjoint_kernels<ADJ_BLOCK, K2_PARTS>(g, gas, bc, alpha_vss, dt, T, cap, seed, step, lam_in,
+                                              lam_out, w_mdot, w_tau, grad, aws, W, st);
 }
 
 }  // namespace usp

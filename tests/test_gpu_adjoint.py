@@ -194,11 +194,12 @@ def test_adjoint_equals_central_differences_full_size():
         assert np.all(rel <= 1e-3), (p, G[:, p], fd)
 
 
-@pytest.mark.parametrize("cells,ppc", [(257, 90), (300, 90), (1100, 90), (6, 1300)])
+@pytest.mark.parametrize("cells,ppc", [(140, 150), (257, 90), (300, 90), (1100, 90), (6, 1300)])
 def test_adjoint_of_every_particle_phase(cells, ppc):
     """The taped particle phase over tiles (more than 256 cells), with its
     order from buckets of cells (more than 1024) and in cells past the FP64
-    stage of 1024 slots: the step it makes is usp_step's (the large cells
+    stage of 1024 slots; the reverse by a wave a cell (more than 128 cells of
+    fewer than 128) and by 8: the step it makes is usp_step's (the large cells
     aside, whose step adds its sums by chunks), and the gradient the
     oracle's.  (No particle's Cholesky test fails on these paths: the oracle's
     autograd has no value where one does.)"""
