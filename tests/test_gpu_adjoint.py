@@ -223,3 +223,30 @@ def test_adjoint_of_every_particle_phase(cells, ppc):
     J = adj.forward(20).cpu().numpy()
     G = adj.backward().cpu().numpy()
     _compare(J, G, Jo, Go, f"{cells} cells of {ppc}")
+
+
+@pytest.mark.parametrize("Z_vib", [50.0, 5.0])
+def test_adjoint_with_vibrational_exchange(Z_vib):
+    """The channel's gas relaxes no vibration (Z_vib 1e14: the exchange factor
+    b is below 1e-12, where forward and reverse take the gammas' vibrational
+    parts as zero); here a hot gas does, so the reverse goes through the
+    relaxed temperature and the secant heat capacity."""
+    from paper_2508_05642_amd.adjoint import PathwiseAdjoint
+    prob = W.poiseuille(kn=0.05, cells=12, ppc=150, f32=False, seed=17)
+    prob.gas = dataclasses.replace(prob.gas, Z_vib=Z_vib)
+    parts = W.particles_for(prob)
+    n, rng = parts["n"], np.random.default_rng(17)
+    s = np.sqrt(prob.gas.R * 6000.0)
+    for k in ("cx", "cy", "cz"):
+        parts[k][:n] = s * rng.standard_normal(n)
+    parts["cx"][:n] += 200.0 * np.sin(np.pi * parts["y"][:n] / 1e-3)
+    parts["cz"][:n] *= 1.1
+    parts["erot"][:n] = rng.exponential(prob.gas.R * 4000.0, n)
+    parts["vib"][:n] = np.floor(rng.exponential(5000.0 / prob.gas.theta_vib, n))
+    prob = dataclasses.replace(prob, dt=prob.dt / 8)
+    _say(f"[adjoint, vibration] Z_vib={Z_vib} n={n}")
+    Jo, Go = A.Path(A.Record(prob, parts, 40, 4)).gradient()
+    adj = PathwiseAdjoint(prob, parts, 4, 3)
+    J = adj.forward(40).cpu().numpy()
+    G = adj.backward().cpu().numpy()
+    _compare(J, G, Jo, Go, f"Z_vib={Z_vib}")
