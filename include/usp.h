@@ -496,18 +496,18 @@ usp_status usp_check(const usp_grid* grid, const usp_particles* p, const double*
    with the weights given by the caller (m fnum/(area K) gives the mass flow
    per unit depth, m fnum/(2 area K dt) the mean shear of the two walls).
    Adjoint arrays `lam` are device double[2][5][capacity]: objective, then
-   y, cx, cy, cz, erot, then particle slot.  Requires particle ids below
-   capacity (1D runs create no particles).  Errors: USP_EINVAL for a grid
+   y, cx, cy, cz, erot, then particle slot.  Errors: USP_EINVAL for a grid
    that is not 1D, a non-FP64 state, the first-order FPM scheme, a
    temperature-dependent collision-number model, a reading switch other
    than USP_GAMMA_PARTICLE and USP_ALPHA_SIGN_PR, or short buffers. */
 size_t usp_tape_bytes(const usp_grid* grid, int64_t capacity);
 size_t usp_adjoint_ws_bytes(const usp_grid* grid, int64_t capacity);
 
-/* One full step (the bits of usp_step) that also writes the tape of the
-   step (bin permutation, binned pre-collision state, cell state, states
-   after the collision and after the conservation) into `tape`
-   (usp_tape_bytes); aws (usp_adjoint_ws_bytes) is scratch.  p and p_alt
+/* One full step (the bits of usp_step; where the mean slots per cell exceed
+   the 1024-slot stage, past which usp_step splits its sums, up to round-off)
+   that also writes the tape of the step (bin permutation, binned
+   pre-collision state, cell state, states after the collision and after the
+   conservation) into `tape` (usp_tape_bytes); aws (usp_adjoint_ws_bytes) is scratch.  p and p_alt
    are swapped as usp_step swaps them; equal capacities; in_offsets as for
    usp_step. */
 usp_status usp_step_taped(const usp_grid* grid, const usp_gas* gas, const usp_bc* bc, double dt,

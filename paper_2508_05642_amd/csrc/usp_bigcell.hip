@@ -8,7 +8,10 @@
 // with them: the particle update sums its chunk's post-collision state, and
 // in 0D the scalings of one step are applied by the pass that sums the next
 // step's moments.  Four launches a 0D step, where separate passes took
-// eight (1e5 particles, FP64: 0.165 -> 0.06 ms).
+// eight (1e5 particles, FP64: 0.165 -> 0.06 ms).  The sums are added in the
+// separate passes' order; products are fused differently (the scalings in
+// k_mom_chunks, the explicit fused products of mom_add), so a state differs from theirs
+// by round-off (1e-15).
 #include "usp_cell.h"
 #include "usp_particle.h"
 

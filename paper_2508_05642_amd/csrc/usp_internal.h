@@ -171,8 +171,12 @@ SortPlan sort_plan(int64_t M, int64_t capacity);
 // at most SORT_BUCKETS cells (one pass, two launches: 19 against 73 us at
 // 1e5 to 1e6 particles, and moves over any number of cells cost the same)
 // and below a state size: the neighbour-group route moves fewer bytes per
-// particle but takes twelve more launches.  Measured on cylinder grids,
-// sort against group route: recording the order, 59 against 62 us at 1.7M
+// particle but takes twelve more launches.  On at most 1024 cells that holds
+// for large states too: 1024 cells in a periodic box, 1M / 4M / 16M particles
+// 49 / 123 / 490 us against 231 / 11,737 / 277,912 (particles that wrap round
+// the box go to far cells, which the group route places cell by cell), and
+// with no particle moved 31 / 85 / 332 against 82 / 271 / 1092.  Measured on
+// cylinder grids, sort against group route: recording the order, 59 against 62 us at 1.7M
 // particles, 111 against 94 at 4.6M, 133 against 92 at 6.6M; copying, 222
 // against 325 at 4.6M and 289 against 250 at 6.6M.  The state size known
 // on the host is the capacity (1.6 times the particles there).
@@ -323,8 +327,13 @@ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // 13/8 of the mean particles per cell (n / M), kept within [stage/8,
 // 7 stage/8], so that most tiles fit the stage; a state too small to fill
 // the chip with such windows is cut into UPDATE_TILES of them (two
-// workgroups on each of 256 CUs, one round): the particle phase of 960
-// particles in 16 cells took 21 us as one tile and takes 15 as eight.
+// workgroups on each of 256 CUs, one round).  A step uncut and cut into 256,
+// 512 and 1024: 4096 cells of 20 FP32 particles 129 / 94 / 94 / 102 us, of 50
+// 106 / 91 / 88 / 96; 8000 of 50 116 / 112 / 107 / 112; 2048 of 400 145 / 145 /
+// 145 / 138; FP64 1024 of 200 133 / 134 / 110 / 122, 2048 of 20 128 / 89 / 96 /
+// 96.  (In a buffer of 47 times the particles the empty tiles come behind
+// two full rounds of CUs instead of one: usp_update of 200,000 FP64 particles
+// in 9.4M slots 70 uncut, 83 cut.)
 constexpr int64_t UPDATE_TILES = 512;
 __host__ __device__ inline int64_t stage_window(int stage, int64_t n, int64_t M) {
   const int64_t ppc = M > 0 ? (n + M - 1) / M : stage;
