@@ -432,8 +432,8 @@ usp_status usp_update_noalloc(const usp_grid* grid, const usp_gas* gas, const us
    usp_bin or usp_step leaves it so).  dt_cell (device double[M], may be
    NULL) overrides dt per cell.  mom and cs as for usp_moments /
    usp_reconstruct; they describe the last step's pre-collision state on
-   return.  tile: particle slots per tile window (512, 1024 or 2048; 0 =
-   1536; FP64 states: 0 or 512).  steps_per_launch: steps each launch runs
+   return.  tile: particle slots per tile window (512, 1024 or 2048; 0 = by
+   the capacity, 256 to 1536; FP64 states: 0 or 512).  steps_per_launch: steps each launch runs
    (0 = all nsteps in one launch).  Errors: USP_EINVAL for dim != 0, a
    null or inconsistent argument, a tile value not listed, or a short ws. */
 usp_status usp_batch(const usp_grid* grid, const usp_gas* gas, double dt, const double* dt_cell,

@@ -11,7 +11,7 @@ import torch
 from . import usp
 
 CANDIDATES_F32 = ((0, 0), (512, 0), (1024, 0), (2048, 0), (512, 1), (1024, 1), (2048, 1))
-CANDIDATES_F64 = ((512, 0), (512, 1))
+CANDIDATES_F64 = ((0, 0), (512, 0), (512, 1))
 
 _cache = {}
 

@@ -10,9 +10,6 @@
 
 namespace usp {
 
-constexpr int UPD_BLOCK = 512;  // workgroup of a batched tile
-constexpr int UPD_WAVES = UPD_BLOCK / 64;
-
 // Where a tile's velocities, rotational energies and levels live: an LDS
 // stage indexed i - base, or the particle arrays themselves (base 0).
 template <typename S>
@@ -87,7 +84,7 @@ __device__ __forceinline__ PartNew<double> update_second(const GridP&, const Gas
 // chunks of CAP particles: first pass thread per particle; the particles
 // it lists (esc_list/nesc, LDS) get the second pass.  Positions and ids
 // are read from p.
-template <typename S, int CAP, bool SAME, int MODE, typename CNT>
+template <typename S, int CAP, bool SAME, int MODE, int BLOCK, typename CNT>
 __device__ __forceinline__ void tile_update(const GridP& g, const GasP& gas,
                                             const double* __restrict__ cs, const PartP<S>& p,
                                             int64_t i0, int64_t i1, const Stage<S>& src,
@@ -97,7 +94,7 @@ __device__ __forceinline__ void tile_update(const GridP& g, const GasP& gas,
     const int64_t ce = cb + CAP < i1 ? cb + CAP : i1;
     if (threadIdx.x == 0) *nesc = 0;
     __syncthreads();
-    for (int64_t i = cb + threadIdx.x; i < ce; i += UPD_BLOCK) {
+    for (int64_t i = cb + threadIdx.x; i < ce; i += BLOCK) {
       const int32_t c = p.cell[i];
       const PartNew<S> in = src.load(i);
       uint32_t ev = 0;
@@ -119,7 +116,7 @@ __device__ __forceinline__ void tile_update(const GridP& g, const GasP& gas,
     }
     __syncthreads();
     const int ne = *nesc;
-    for (int k = threadIdx.x; k < ne; k += UPD_BLOCK) {
+    for (int k = threadIdx.x; k < ne; k += BLOCK) {
       const int64_t i = cb + esc_list[k];
       const PartNew<S> in = src.load(i);
       uint32_t ev = 0;
@@ -134,7 +131,7 @@ __device__ __forceinline__ void tile_update(const GridP& g, const GasP& gas,
 }
 
 // Conservation of the cells [c0, c1), wave per cell, on st.
-template <typename S>
+template <typename S, int BLOCK>
 __device__ __forceinline__ void tile_conserve(const GasP& gas, const double* __restrict__ cs,
                                               int64_t M, const int64_t* __restrict__ offsets,
                                               int64_t c0, int64_t c1, const Stage<S>& st,
@@ -142,7 +139,7 @@ __device__ __forceinline__ void tile_conserve(const GasP& gas, const double* __r
   // the wave's index, made wave-uniform so that the per-cell work of the
   // conservation (loads, draws, integer arithmetic) runs on the scalar unit
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int64_t c = c0 + wid; c < c1; c += UPD_WAVES) {
+  for (int64_t c = c0 + wid; c < c1; c += BLOCK / 64) {
     const int64_t o0 = offsets[c], o1 = offsets[c + 1];
     const ConsIn in = cons_in(cs, M, c, step, seed);
     if (o1 == o0 || !in.collide) continue;
@@ -206,7 +203,7 @@ __device__ __forceinline__ void wave_row_sums(const Stage<S>& st, int64_t o0, in
 // 1121, 1112.
 constexpr int TILE_ROW_MAX = 128;
 
-template <typename S>
+template <typename S, int BLOCK>
 __device__ __forceinline__ void tile_cells(const GridP& g, const GasP& gas, double dt,
                                            const double* dt_cell, double* mom, double* cs,
                                            const int64_t* __restrict__ offsets, int64_t c0,
@@ -217,14 +214,14 @@ __device__ __forceinline__ void tile_cells(const GridP& g, const GasP& gas, doub
   int nth = 0;  // the larger cells go to the waves in turn
   for (int64_t c = c0; c < c1; ++c) {
     const int64_t o0 = offsets[c] - st.base, o1 = offsets[c + 1] - st.base;
-    if (o1 - o0 <= TILE_ROW_MAX || nth++ % UPD_WAVES != wid) continue;
+    if (o1 - o0 <= TILE_ROW_MAX || nth++ % (BLOCK / 64) != wid) continue;
     const double r0 = (double)st.cx[o0], r1 = (double)st.cy[o0], r2 = (double)st.cz[o0];
     double s[20], v[NMOM];
     wave_row_sums<S>(st, o0, o1, r0, r1, r2, s);
     moments_from_sums(s, o1 - o0, r0, r1, r2, v);
     if (lane < MOM_LANES) store_moments(mom, M, c, lane, v);
   }
-  for (int64_t c = c0 + row; c < c1; c += UPD_BLOCK / MOM_LANES) {
+  for (int64_t c = c0 + row; c < c1; c += BLOCK / MOM_LANES) {
     const int64_t o0 = offsets[c] - st.base, o1 = offsets[c + 1] - st.base;
     if (o1 - o0 > TILE_ROW_MAX) continue;
     double v[NMOM];
@@ -232,7 +229,7 @@ __device__ __forceinline__ void tile_cells(const GridP& g, const GasP& gas, doub
     store_moments(mom, M, c, sub, v);
   }
   __syncthreads();
-  for (int64_t c = c0 + threadIdx.x; c < c1; c += UPD_BLOCK)
+  for (int64_t c = c0 + threadIdx.x; c < c1; c += BLOCK)
     reconstruct_cell(g, gas, mom, dt, dt_cell, cs, counters, c);
 }
 

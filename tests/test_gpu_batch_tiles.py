@@ -62,3 +62,41 @@ def test_empty_cells_past_the_last_window(f32, tile, n):
     assert np.array_equal(a.moments(), b.moments())
     assert np.array_equal(a.cellstate(), b.cellstate())
     assert a.cnt() == b.cnt()
+
+
+@pytest.mark.parametrize("f32,tile", [(True, 0), (True, 512), (True, 1024), (True, 2048), (False, 0),
+                                      (False, 512)])
+def test_thousands_of_small_cells_equal_step(f32, tile):
+    """The 4-wave shape of the tiles (thousands of cells; FP32 with 2048 slots
+    keeps the 8-wave one): small cells, and among them cells at its stage's
+    size (2240 FP32, 1200 FP64), one past it and far past it, and empty ones."""
+    from paper_2508_05642_amd import usp
+    M, rng = 3100, np.random.default_rng(6)
+    counts = rng.integers(0, 200, M)
+    edge = 2240 if f32 else 1200
+    counts[[5, 900, 901, 2000, 2500, M - 2]] = [edge, edge + 1, edge - 1, 3 * edge, 1025, 6000]
+    counts[[0, 902, M - 1]] = 0
+    prob, parts = W.batch0d(np.maximum(counts, 1), T_tr=rng.uniform(2000, 20000, M),
+                            T_rot=rng.uniform(200, 1000, M), T_vib=rng.uniform(200, 1000, M),
+                            dens=np.full(M, 1e23), dt=2e-8, f32=f32)
+    n = parts["n"]
+    keep = np.nonzero(counts[parts["cell"][:n]] > 0)[0]  # batch0d puts one in every cell
+    parts = {k: v[keep] if isinstance(v, np.ndarray) else v for k, v in parts.items()}
+    parts["n"] = n = len(keep)
+    assert 300000 <= n <= 400 * M
+    print(f"[batch tiles, small cells] f32={f32} tile={tile} n={n}", flush=True)
+    a, b = (usp.DeviceState(prob, parts, capacity=n) for _ in range(2))
+    for st in (a, b):
+        st.bin()
+        st.mom.fill_(-7.0)
+        st.cs.fill_(-7.0)
+    a.step(10, 3)
+    b.batch(10, 3, tile, 2)
+    torch.cuda.synchronize()
+    sa, sb = a.state(), b.state()
+    for k in sa:
+        if isinstance(sa[k], np.ndarray):
+            assert np.array_equal(sa[k], sb[k]), k
+    assert a.cnt() == b.cnt()
+    assert np.array_equal(a.moments(), b.moments())
+    assert np.array_equal(a.cellstate(), b.cellstate())
