@@ -69,8 +69,9 @@ __device__ __forceinline__ void moments_from_sums(const double s[20], int64_t N,
 // The NMOM moments of the particles [o0, o1) (array indices) on one row of
 // 16 lanes (sub = lane in the row; all 16 lanes call); every lane of the
 // row returns the same v.  With G, slot i is the particle perm[i] of the
-// arrays (a binning that left the particles in place).
-template <typename PS, bool G = false>
+// arrays (a binning that left the particles in place).  Without AHEAD a lane
+// loads its particles one by one.
+template <typename PS, bool G = false, bool AHEAD = true>
 __device__ __forceinline__ void row_moments(const PS* cx, const PS* cy, const PS* cz,
                                             const PS* er, const uint8_t* vb, int64_t o0,
                                             int64_t o1, int sub, double v[NMOM],
@@ -103,7 +104,9 @@ __device__ __forceinline__ void row_moments(const PS* cx, const PS* cy, const PS
     for (int k = 0; k < U; ++k) a[k] = mom_load<PS>(cx, cy, cz, er, vb, j[k]);
   };
   int64_t i = o0 + sub;
-  if (i < o1) {
+  if constexpr (!AHEAD) {
+    for (; i < o1; i += MOM_LANES) mom_add(mom_load<PS>(cx, cy, cz, er, vb, at(i)), r0, r1, r2, s);
+  } else if (i < o1) {
     int64_t j[U];
     MomIn<PS> a[U], b[U];
     slots(i, j);

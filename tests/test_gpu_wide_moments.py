@@ -123,3 +123,33 @@ def test_every_moment_of_few_cells_against_numpy(M, f32):
     scale = np.array([c] * 3 + [e] * 6 + [e, 9.0] + [e * c] * 6 + [9.0 * c] * 3)
     err = np.abs(m - ref).max(axis=1)[1:]
     assert np.all(err <= 1e-10 * scale), (err / scale).tolist()
+
+
+@pytest.mark.parametrize("f32", [True, False])
+def test_rows_load_one_by_one_as_ahead(f32):
+    """Sparse grids (at most ten slots a cell) take the rows' plain loop: the
+    bits of the loop that loads ahead, which a roomier buffer selects, in cells
+    of 0 to 90 particles."""
+    from paper_2508_05642_amd import usp
+    M, rng = 4200, np.random.default_rng(9)
+    counts = rng.integers(0, 8, M)
+    counts[[3, 4, 77, 78, 4199]] = [90, 0, 16, 17, 64]
+    grid = W.Grid(dim=1, nx=1, ny=M, dy=1.0, fnum=1e15, volume=np.ones(M), flags=np.zeros(M, np.uint8))
+    prob = W.Problem("sparse", W.Gas(), grid, W.BC(kind=(W.BC_PERIODIC,) * 4), dt=1e-9, seed=3, f32=f32)
+    cell = np.repeat(np.arange(M), counts)
+    n = len(cell)
+    s = np.sqrt(prob.gas.R * 3000.0)
+    parts = dict(n=n, cap=n, x=None, y=cell + 0.1 + 0.8 * rng.random(n), cell=cell,
+                 erot=rng.exponential(prob.gas.R * 2000.0, n), vib=rng.integers(0, 9, n),
+                 pid=np.arange(n, dtype=np.uint32), next_pid=n,
+                 **{k: s * rng.standard_normal(n) for k in ("cx", "cy", "cz")})
+    out = []
+    for cap in (10 * M, 10 * M + 1):
+        for gather in (False, True):
+            st = usp.DeviceState(prob, parts, capacity=cap)
+            st.bin(gather=gather)
+            st.do_moments()
+            out.append(st.moments())
+    print(f"[sparse rows] n={n} f32={f32}", flush=True)
+    for m in out[1:]:
+        assert np.array_equal(m, out[0])
