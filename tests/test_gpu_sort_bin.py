@@ -160,3 +160,22 @@ def test_packs_carry_positions(nx, ny, dim, f32):
     for k, a in (("x", x), ("y", y)):
         if a is not None:
             assert np.array_equal(got[k], a[order].astype(np.float64)), k
+
+
+@pytest.mark.parametrize("M,n,room", [(7, 1 << 21, 1), (7, (1 << 21) + 1, 1), (1500, (1 << 21) + 1, 3),
+                                      (300, 2049, 900), (1024, 4096, 2000), (1025, 2047, 3000)])
+def test_chunks_follow_the_count_not_the_buffer(M, n, room):
+    """1024 chunks of 2048 slots hold 2^21 particles; one more makes them
+    larger.  A small state is cut finely in any buffer, and again after moves,
+    with its segments."""
+    print(f"[sort bin, chunks] M={M} n={n} cap={n * room}", flush=True)
+    st, parts = _cells_state(M, n, True, seed=M + n, cap=n * room)
+    cell = parts["cell"]
+    st.bin()
+    _check(st, parts, np.nonzero(cell >= 0)[0], cell)
+    s = st.state()
+    rng = np.random.default_rng(2)
+    moved = rng.integers(-1, M, s["n"]).astype(np.int32)
+    st.bufs[st.cur]["cell"][: s["n"]] = torch.as_tensor(moved)
+    st.bin()
+    _check(st, s, np.nonzero(moved >= 0)[0], moved)
